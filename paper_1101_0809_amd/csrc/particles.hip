@@ -19,6 +19,8 @@
 // Precision R = double (FP64 mode: absolute FP64 positions) or float (FP32
 // mode: packed int cell + FP32 offset, FP32 gather, push and current
 // contributions); the LDS current tile is FP64 in both.
+#include <algorithm>
+
 #include "pic_math.h"
 
 namespace pic {
@@ -47,54 +49,85 @@ __device__ __forceinline__ void global_add(double* p, double v)
 }
 
 // ---------------------------------------------------------------------------
-// The 2D3V particle-step kernel (tile kTile2^2, margin kMargin2); every
-// particle deposits its window at once.
+// The 2D3V particle-step kernel (tile T^2, margin M); `split` workgroups share
+// a tile's particles, each with its own LDS field and current tiles; every
+// particle deposits its window at once.  One workgroup of four waves per tile
+// leaves a CU of a 256^2 grid with one wave per SIMD and most CUs of a small
+// grid idle.  Sharing the tiles (grid2), taking the fields' loads in one batch
+// and loading the next particle ahead took a step of 32^2 cells x 4 per cell
+// from 33.3 to 19.4 us and 20 steps of 256^2 x 16 from 1456 to 1389 us (FP64);
+// the large grid is then bound by the LDS (70% of its cycles active, a third
+// of them bank conflicts).
 // ---------------------------------------------------------------------------
-template <class R, int D, int T, int M, int NT>
-__global__ __launch_bounds__(NT) void k_particle_step(GridK g, StepArgs a, const double* __restrict__ fields,
-                                                     const double* __restrict__ bfield, double* __restrict__ Jg)
+template <class R, int T, int M, int NT>
+__global__ __launch_bounds__(NT) void k_particle_step2(GridK g, StepArgs a, const double* __restrict__ fields,
+                                                      const double* __restrict__ bfield, double* __restrict__ Jg,
+                                                      int split)
 {
-    static_assert(D == 2, "the 3D step is k_particle_step3");
     constexpr int LF = T + 2 + 2 * M;  // field region: cells T0-1-M .. T0+T+M
     constexpr int LJ = T + 4 + 2 * M;  // current region: T0-2-M .. T0+T+1+M
-    constexpr int SFY = LF, SFZ = SFY * LF;
-    constexpr int NF = D == 3 ? SFZ * LF : LF * LF;
-    constexpr int NJ = D == 3 ? LJ * LJ * LJ : LJ * LJ;
-    constexpr int SJY = LJ, SJZ = LJ * LJ;
+    constexpr int NF = LF * LF, NJ = LJ * LJ;
     __shared__ R sf[6 * NF];
     __shared__ LdsJ<R, 3 * NJ> sj;
     __shared__ unsigned int n_fallback;
 
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
-    const int tx = tile % g.nt[0];
-    const int ty = (tile / g.nt[0]) % g.nt[1];
-    const int tz = D == 3 ? tile / (g.nt[0] * g.nt[1]) : 0;
-    const int T0[3] = {tx * T, ty * T, tz * T};
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
+    const int tile = unit / split, part = unit - tile * split;
+    const int T0[2] = {(tile % g.nt[0]) * T, (tile / g.nt[0]) * T};
     const int64_t N = g.ncell;
-    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int nx = g.n[0], ny = g.n[1];
+    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    if (begin + part * NT >= end) {  // no particle for this workgroup (all of it)
+        if (part == 0 && threadIdx.x == 0 && a.counters) atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
+        return;
+    }
 
     // every region index lies in [-n, 2n) unless an axis is shorter than the
     // current region; then the general modulo is used
-    const bool small = nx < LJ || ny < LJ || (D == 3 && nz < LJ);
+    const bool small = nx < LJ || ny < LJ;
     auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
 
-    // 1. stage E^n, B^n (+ guard cells) into LDS; B^n is in bfield
-    constexpr int NV = D == 3 ? LF * LF * LF : LF * LF;  // values per component
-    for (int e = threadIdx.x; e < 6 * NV; e += NT) {
-        const int comp = e / NV;
-        const int r = e - comp * NV;
-        const int lx = r % LF;
-        const int ly = (r / LF) % LF;
-        const int lz = D == 3 ? r / (LF * LF) : 0;
-        const int gx = wr(T0[0] - 1 - M + lx, nx);
-        const int gy = wr(T0[1] - 1 - M + ly, ny);
-        const int gz = D == 3 ? wr(T0[2] - 1 - M + lz, nz) : 0;
-        sf[comp * NF + lx + ly * SFY + lz * SFZ] =
-            (R)(comp < 3 ? fields + comp * N : bfield + (comp - 3) * N)[((int64_t)gz * ny + gy) * nx + gx];
+    // the first particle's state loads while the fields are staged
+    struct State {
+        int i0[3];
+        R d0[3], w[3], qp;
+    };
+    auto load = [&](int64_t p, State& st) {
+        PosIO<R, 2>::load(a, p, st.i0, st.d0);
+        for (int ax = 0; ax < 3; ++ax) st.w[ax] = ((const R*)a.mom[ax])[p];
+        st.qp = (R)a.q * ((const R*)a.weight)[p];
+    };
+    int64_t p = begin + part * NT + threadIdx.x;
+    State st{};
+    if (p < end) load(p, st);
+
+    // 1. stage E^n, B^n (+ guard cells) into LDS; B^n is in bfield.  A thread
+    //    takes whole cells: the wrap is computed once for the six components
+    //    and their loads are all in flight together.
+    constexpr int SC = (NF + NT - 1) / NT;
+    double v[SC][6];
+#pragma unroll
+    for (int u = 0; u < SC; ++u) {
+        const int e = (int)threadIdx.x + u * NT;
+        if (e < NF) {
+            const int64_t c = (int64_t)wr(T0[1] - 1 - M + e / LF, ny) * nx + wr(T0[0] - 1 - M + e % LF, nx);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                v[u][k] = fields[k * N + c];
+                v[u][3 + k] = bfield[k * N + c];
+            }
+        }
     }
     // 2. clear the LDS current tile
     for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
     if (threadIdx.x == 0) n_fallback = 0;
+#pragma unroll
+    for (int u = 0; u < SC; ++u) {
+        const int e = (int)threadIdx.x + u * NT;
+        if (e < NF)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) sf[k * NF + e] = (R)v[u][k];
+    }
     __syncthreads();
 
     const R c = (R)g.c;
@@ -102,26 +135,25 @@ __global__ __launch_bounds__(NT) void k_particle_step(GridK g, StepArgs a, const
     const R qmdt2 = (R)(0.5 * a.qm * g.dt);
     const R cfl[3] = {(R)g.cfl[0], (R)g.cfl[1], (R)g.cfl[2]};
     const R bext[3] = {(R)g.bext[0], (R)g.bext[1], (R)g.bext[2]};
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
     unsigned int my_fallback = 0;
 
     // 3. particles
-    for (int64_t p = begin + threadIdx.x; p < end; p += NT) {
-        int i0[3];
-        R d0[3];
-        PosIO<R, D>::load(a, p, i0, d0);
-        R w[3];
-        for (int ax = 0; ax < 3; ++ax) w[ax] = ((const R*)a.mom[ax])[p];
-        const R qp = (R)a.q * ((const R*)a.weight)[p];
+    for (; p < end; p += (int64_t)split * NT) {
+        const State now = st;
+        if (p + (int64_t)split * NT < end) load(p + (int64_t)split * NT, st);
+        const int(&i0)[3] = now.i0;
+        const R(&d0)[3] = now.d0;
+        const R qp = now.qp;
+        R w[3] = {now.w[0], now.w[1], now.w[2]};
 
         Axis<R> ax0[3];
-        for (int ax = 0; ax < D; ++ax) ax0[ax] = form_factor<R>(d0[ax]);
-        if (D == 2) ax0[2] = form_factor<R>(R(0));
+        for (int ax = 0; ax < 2; ++ax) ax0[ax] = form_factor<R>(d0[ax]);
+        ax0[2] = form_factor<R>(R(0));
 
         // position relative to the tile, periodic-corrected
-        int rel[3];
+        int rel[2];
         bool inside = true;
-        for (int ax = 0; ax < D; ++ax) {
+        for (int ax = 0; ax < 2; ++ax) {
             int r = i0[ax] - T0[ax];
             const int n = g.n[ax];
             if (r > n / 2) r -= n;
@@ -129,31 +161,23 @@ __global__ __launch_bounds__(NT) void k_particle_step(GridK g, StepArgs a, const
             rel[ax] = r;
             inside = inside && (r >= -M) && (r <= T - 1 + M);
         }
-        if (D == 2) rel[2] = 0;
 
         R E[3], B[3];
         if (inside) {
-            const int base = (rel[0] + 1 + M) + (rel[1] + 1 + M) * SFY +
-                             (D == 3 ? (rel[2] + 1 + M) * SFZ : 0);
-            auto F = [&](int comp, int da, int db, int dc) -> R {
-                return sf[comp * NF + base + da + db * SFY + (D == 3 ? dc * SFZ : 0)];
-            };
-            if (D == 3) gather3<R>(ax0, F, E, B);
-            else gather2<R>(ax0, F, E, B);
+            const int base = (rel[0] + 1 + M) + (rel[1] + 1 + M) * LF;
+            auto F = [&](int comp, int da, int db, int) -> R { return sf[comp * NF + base + da + db * LF]; };
+            gather2<R>(ax0, F, E, B);
         } else {
             ++my_fallback;
             int xi[3], yj[3];
-            int64_t zk[3];
             for (int o = 0; o < 3; ++o) {
                 xi[o] = wrapi(i0[0] + o - 1, nx);
                 yj[o] = wrapi(i0[1] + o - 1, ny) * nx;
-                zk[o] = D == 3 ? (int64_t)wrapi(i0[2] + o - 1, nz) * nx * ny : 0;
             }
-            auto F = [&](int comp, int da, int db, int dc) -> R {
-                return (R)(comp < 3 ? fields + comp * N : bfield + (comp - 3) * N)[zk[dc + 1] + yj[db + 1] + xi[da + 1]];
+            auto F = [&](int comp, int da, int db, int) -> R {
+                return (R)(comp < 3 ? fields + comp * N : bfield + (comp - 3) * N)[yj[db + 1] + xi[da + 1]];
             };
-            if (D == 3) gather3<R>(ax0, F, E, B);
-            else gather2<R>(ax0, F, E, B);
+            gather2<R>(ax0, F, E, B);
         }
         for (int ax = 0; ax < 3; ++ax) B[ax] += bext[ax];
 
@@ -165,41 +189,33 @@ __global__ __launch_bounds__(NT) void k_particle_step(GridK g, StepArgs a, const
         for (int ax = 0; ax < 3; ++ax) disp[ax] = w[ax] * inv * cfl[ax];
         R d1[3];
         int delta[3] = {0, 0, 0};
-        PosIO<R, D>::move(a, p, g, i0, d0, disp, d1, delta, true);
+        PosIO<R, 2>::move(a, p, g, i0, d0, disp, d1, delta, true);
 
         // deposit
         R jfac[3];
         for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
         R dm[3][4], dp[3][4];
-        for (int ax = 0; ax < D; ++ax) {
+        for (int ax = 0; ax < 2; ++ax) {
             R s1[3];
             cell_weights<R>(d1[ax], s1);
             window<R>(ax0[ax].s, s1, delta[ax], dm[ax], dp[ax]);
         }
-        const R jz2 = D == 2 ? qp * (R)(0.25 * g.inv_vol) * c * w[2] * inv : R(0);
-        int s[3];
-        for (int ax = 0; ax < 3; ++ax) s[ax] = (ax < D) ? rel[ax] + (delta[ax] < 0 ? -1 : 0) - 1 : 0;
+        const R jz2 = qp * (R)(0.25 * g.inv_vol) * c * w[2] * inv;
+        int s[2];
+        for (int ax = 0; ax < 2; ++ax) s[ax] = rel[ax] + (delta[ax] < 0 ? -1 : 0) - 1;
 
         if (inside) {
-            const int jb = (s[0] + 2 + M) + (s[1] + 2 + M) * SJY + (D == 3 ? (s[2] + 2 + M) * SJZ : 0);
-            auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                sj.add(comp * NJ + jb + ix + iy * SJY + (D == 3 ? iz * SJZ : 0), v);
-            };
-            if (D == 3) deposit3<R>(dm, dp, jfac, S);
-            else deposit2<R>(dm, dp, jfac, jz2, S);
+            const int jb = (s[0] + 2 + M) + (s[1] + 2 + M) * LJ;
+            auto S = [&](int comp, int ix, int iy, int, double x) { sj.add(comp * NJ + jb + ix + iy * LJ, x); };
+            deposit2<R>(dm, dp, jfac, jz2, S);
         } else {
             int xi[4], yj[4];
-            int64_t zk[4];
             for (int o = 0; o < 4; ++o) {
                 xi[o] = wrapi(T0[0] + s[0] + o, nx);
                 yj[o] = wrapi(T0[1] + s[1] + o, ny) * nx;
-                zk[o] = D == 3 ? (int64_t)wrapi(T0[2] + s[2] + o, nz) * nx * ny : 0;
             }
-            auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                global_add(&Jg[comp * N + zk[iz] + yj[iy] + xi[ix]], v);
-            };
-            if (D == 3) deposit3<R>(dm, dp, jfac, S);
-            else deposit2<R>(dm, dp, jfac, jz2, S);
+            auto S = [&](int comp, int ix, int iy, int, double x) { global_add(&Jg[comp * N + yj[iy] + xi[ix]], x); };
+            deposit2<R>(dm, dp, jfac, jz2, S);
         }
     }
     if (my_fallback) atomicAdd(&n_fallback, my_fallback);
@@ -207,21 +223,16 @@ __global__ __launch_bounds__(NT) void k_particle_step(GridK g, StepArgs a, const
 
     // 4. flush the LDS current tile
     for (int e = threadIdx.x; e < 3 * NJ; e += NT) {
-        const double v = sj.get(e);
-        if (v == 0.0) continue;
+        const double x = sj.get(e);
+        if (x == 0.0) continue;
         const int comp = e / NJ;
         const int r = e - comp * NJ;
-        const int lx = r % LJ;
-        const int ly = (r / LJ) % LJ;
-        const int lz = D == 3 ? r / (LJ * LJ) : 0;
-        const int gx = wr(T0[0] - 2 - M + lx, nx);
-        const int gy = wr(T0[1] - 2 - M + ly, ny);
-        const int gz = D == 3 ? wr(T0[2] - 2 - M + lz, nz) : 0;
-        global_add(&Jg[comp * N + ((int64_t)gz * ny + gy) * nx + gx], v);
+        const int gx = wr(T0[0] - 2 - M + r % LJ, nx), gy = wr(T0[1] - 2 - M + r / LJ, ny);
+        global_add(&Jg[comp * N + (int64_t)gy * nx + gx], x);
     }
     if (threadIdx.x == 0 && a.counters) {
-        atomicAdd(&a.counters[1], (unsigned long long)n_fallback);
-        atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
+        if (n_fallback) atomicAdd(&a.counters[1], (unsigned long long)n_fallback);
+        if (part == 0) atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
     }
 }
 
@@ -1285,6 +1296,20 @@ constexpr int kThreadsMigf = 1024; // migrant pass, FP32
 constexpr int kThreads2 = 256;
 constexpr int kMargin2 = 2;
 
+// Workgroups of the 2D3V step: several per tile until they fill the chip
+// (four per CU fit its LDS), none with less than one particle per thread on
+// average.  20 steps of 256^2 x 16: 1366, 1294, 1273, 1329, 1379 us at 1, 2, 3,
+// 4 and 8 per tile; 10 steps of 100 x 70 x 8: 384, 307, 281, 257, 250 us; 20
+// steps of 512^2 x 16 (1024 tiles): 3949, 3978, 4031, 4119, 4249 us.
+dim3 grid2(const GridK& k, int64_t n, int* split)
+{
+    int64_t want = (4 * kCus + k.ntiles - 1) / k.ntiles;
+    const int64_t full = (n + (int64_t)k.ntiles * kThreads2 - 1) / ((int64_t)k.ntiles * kThreads2);
+    want = std::min(want, full);
+    *split = (int)std::max<int64_t>(1, std::min<int64_t>(want, 64));
+    return dim3((unsigned)(k.ntiles * *split));
+}
+
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
@@ -1296,6 +1321,7 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
     if (c.g.interp == 1) return launch_particle_step_conv(c, sp, s);
     double* J = c.fields + 6 * c.k.ncell;
     const dim3 grid(c.k.ntiles);
+    int split = 1;
     if (c.g.precision == PIC_FP64) {
         StepArgs a = step_args<double>(c, sp, c.counters);
         if (c.k.dims == 3) {
@@ -1305,8 +1331,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
                                c.fields, c.bn, J);
         }
         else
-            hipLaunchKernelGGL((k_particle_step<double, 2, kTile2, kMargin2, kThreads2>), grid,
-                               dim3(kThreads2), 0, s, c.k, a, c.fields, c.bn, J);
+            hipLaunchKernelGGL((k_particle_step2<double, kTile2, kMargin2, kThreads2>), grid2(c.k, sp.n, &split),
+                               dim3(kThreads2), 0, s, c.k, a, c.fields, c.bn, J, split);
     } else {
         StepArgs a = step_args<float>(c, sp, c.counters);
         if (c.k.dims == 3) {
@@ -1316,8 +1342,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
                                c.fields, c.bn, J);
         }
         else
-            hipLaunchKernelGGL((k_particle_step<float, 2, kTile2, kMargin2, kThreads2>), grid,
-                               dim3(kThreads2), 0, s, c.k, a, c.fields, c.bn, J);
+            hipLaunchKernelGGL((k_particle_step2<float, kTile2, kMargin2, kThreads2>), grid2(c.k, sp.n, &split),
+                               dim3(kThreads2), 0, s, c.k, a, c.fields, c.bn, J, split);
     }
     return hipGetLastError();
 }

@@ -14,6 +14,7 @@ namespace pic {
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kMaxSpecies = 4;
 constexpr size_t kAlign = 256;  // alignment of every carved buffer
+constexpr int kCus = 256;  // MI355X: compute units
 constexpr int kXcds = 8;  // MI355X: 8 accelerator complex dies, each with its own L2
 
 // Tile edge (cells) of the particle-step kernel, per dimensionality.
