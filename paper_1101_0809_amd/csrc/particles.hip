@@ -250,10 +250,13 @@ __global__ __launch_bounds__(NT) void k_particle_step2(GridK g, StepArgs a, cons
 // Lanes of one LDS pass that hold cells of distinct classes read and add in
 // distinct banks.
 //
-// Each wave takes chunks of 64 KC consecutive storage slots (chunks w, w + NW,
-// ... of the tile), so every load and store of a chunk stays within a few
-// cache lines per array however far the particles have drifted since the last
-// sort, and orders its own chunk without a workgroup barrier:
+// Each wave takes chunks of 64 KC consecutive storage slots, so every load and
+// store of a chunk stays within a few cache lines per array however far the
+// particles have drifted since the last sort, and orders its own chunk without
+// a workgroup barrier.  Wave w starts with chunk w and then takes the next
+// chunk no wave has taken: a SIMD serves its oldest wave first, so with a
+// fixed share the first waves finished and then waited for 16 (after a sort)
+// to 32 us (20 steps later) of a 128^3 x 32 tile's 135 us.
 //   (a) every slot's cell is classified (its load was issued during the
 //       previous chunk).  A particle inside the tile region takes a rank among
 //       the chunk's particles of its class (LDS counter per wave and class);
@@ -274,8 +277,12 @@ __global__ __launch_bounds__(NT) void k_particle_step2(GridK g, StepArgs a, cons
 // global reservation per neighbour tile), those whose bucket was full are
 // advanced with global memory (gather from the grid, global atomics), and the
 // crossing pass deposits the queued windows in class-map order, in sections by
-// crossing axis (74 contributions for one axis, 144 for several); the entries
-// a full map column could not take follow in arrival order.  Last, the
+// crossing axis (74 contributions for one axis, 144 for several), whose blocks
+// the waves share like the chunks (a quarter of the waves per section left
+// most of them idle where one axis dominates, as in a laser's field); the
+// entries a full map column could not take follow in arrival order.  Shared
+// chunks and crossing blocks: 20 steps of 128^3 x 32 x 2 species 120.0 ->
+// 114.2 ms, 10 steps of the 128^3 laser slab 17.8 -> 17.0 ms (FP32c).  Last, the
 // non-zero current entries are flushed with global FP64 atomics.  The spare
 // particle copy holds the crossing queue and the migrant lists (idle between
 // sorts); the sort scratch holds the buckets.
@@ -603,6 +610,7 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
     __shared__ unsigned int qc_total, qc_unmapped;
     __shared__ unsigned int qo_n;  // migrants whose bucket was full
     __shared__ unsigned int n_migrant;
+    __shared__ unsigned int next_chunk, next_cross;  // work counters of the waves
 
     const int tile = xcd_tile(blockIdx.x, g.ntiles);
     const int tx = tile % g.nt[0];
@@ -627,6 +635,8 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
         qo_n = 0;
         n_migrant = 0;
         ml_n = 0;
+        next_chunk = NW;
+        next_cross = NW;
     }
     __syncthreads();
 
@@ -637,6 +647,13 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
     uint32_t* mslot = (uint32_t*)a.mlist + begin;   // migrant list: slot offsets
     uint32_t* mword = (uint32_t*)a.mlist2 + begin;  // migrant list: rank | code << 27
     unsigned my_migrant = 0;
+
+    // The next value of a work counter, the same for all lanes of the wave.
+    auto take = [&](unsigned int* counter) -> unsigned {
+        unsigned v = 0;
+        if (lane == 0) v = atomicAdd(counter, 1u);
+        return (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+    };
 
     // Classify slot sl (cell ci): true if its cell lies in the tile region,
     // with its lane class; otherwise the particle joins the tile's migrant
@@ -717,14 +734,16 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
         a.qword[begin + e] = word;
     };
 
-    // 3. wave chunks: wave w takes chunks w, w + NW, ... of WCH slots;
-    //    lane l the slots l + 64 u.  No workgroup barrier inside the loop:
-    //    the class order of a chunk is the wave's own, in its own rows.
+    // 3. wave chunks of WCH slots, lane l the slots l + 64 u: wave w starts
+    //    with chunk w and then takes the next chunk that no wave has taken.
+    //    No workgroup barrier inside the loop: the class order of a chunk is
+    //    the wave's own, in its own rows.
     int ci[KC][3];
 #pragma unroll
     for (int u = 0; u < KC; ++u)
         if (wv * WCH + lane + 64 * u < nt) PosIO<R, 3>::cell(a, begin + wv * WCH + lane + 64 * u, ci[u]);
-    for (int cb = wv * WCH; cb < nt; cb += NW * WCH) {
+    for (int cb = wv * WCH, cn; cb < nt; cb = cn) {
+        cn = (int)take(&next_chunk) * WCH;
         // (a) classify
         int cls[KC];
         unsigned rk[KC];
@@ -773,7 +792,7 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
         // the next chunk's cells load while this chunk is advanced
 #pragma unroll
         for (int u = 0; u < KC; ++u) {
-            const int nsl = cb + NW * WCH + lane + 64 * u;
+            const int nsl = cn + lane + 64 * u;
             if (nsl < nt) PosIO<R, 3>::cell(a, begin + nsl, ci[u]);
         }
         // (d) advance: lane t takes chunk positions t, t + 64, ...
@@ -870,21 +889,26 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
             else if (sec == 2) deposit3_axis<2, R>(dm, dp, jfac, S);
             else deposit3<R>(dm, dp, jfac, S);
         };
-        // the sections run side by side, one group of waves each, so that every
-        // wave runs a single deposit variant
+        // blocks of 64 map entries (four rows) of one section each, the widest
+        // deposit (section 3) first; wave w starts with block w and then takes
+        // the next one, so that every wave runs a single deposit variant at a
+        // time whatever the share of each section
         {
-            constexpr int NG = NT / 64 / 4;  // waves per group
-            const int wv = threadIdx.x >> 6;
-            const int sec = wv & 3;
-            const int gt = (wv >> 2) * 64 + (threadIdx.x & 63);
-            unsigned rows = 0;
-            for (int k = 0; k < CJ; ++k) rows = max(rows, min(qc_n[sec * CJ + k], capc));
-            const int nmap = (int)rows * CJ;
-            for (int sl = gt; sl < nmap; sl += NG * 64) {
-                const int col = sec * CJ + (sl & (CJ - 1));
-                const unsigned row = (unsigned)(sl / CJ);
-                if (row >= min(qc_n[col], capc)) continue;
-                cross(begin + qmap[col + 4 * CJ * row], sec);
+            unsigned rows = min(qc_n[lane], capc);  // lane = section * CJ + column
+#pragma unroll
+            for (int o = 1; o < CJ; o <<= 1) rows = max(rows, (unsigned)__shfl_xor((int)rows, o, 64));
+            constexpr int RPB = 64 / CJ;  // rows per block
+            const int nb = ((int)rows + RPB - 1) / RPB;
+            int last[4];  // blocks of sections 3, 2, 1, 0, cumulated
+            int run = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) last[k] = run += __builtin_amdgcn_readlane(nb, (3 - k) * CJ);
+            for (int blk = wv; blk < run; blk = (int)take(&next_cross)) {
+                const int k = blk < last[0] ? 0 : (blk < last[1] ? 1 : (blk < last[2] ? 2 : 3));
+                const int sec = 3 - k;
+                const int col = sec * CJ + (lane & (CJ - 1));
+                const unsigned row = (unsigned)((blk - (k > 0 ? last[k - 1] : 0)) * RPB + lane / CJ);
+                if (row < min(qc_n[col], capc)) cross(begin + qmap[col + 4 * CJ * row], sec);
             }
         }
         if (qc_unmapped) {

@@ -23,3 +23,24 @@ def test_2d_step_shares_a_tile(nx, ny, ppc, precision, tols):
                                                     bext=(0.0, 0.0, 0.05))
     sim, st, _ = _run_pair(wl, precision, 24, sort_every=12)
     _compare(sim, st, wl, *tols)
+
+
+@pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_3d_crossings_along_one_axis(axis, precision, tols):
+    """3D: nearly every particle crosses cells along one axis (0.32 cells per
+    step), so that one section of the crossing pass holds nearly all of its
+    blocks; tiles of very different fill (a slab of 10 of 20 cells)."""
+    w_th = [0.02] * 3
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=20, ny=16, nz=16, ppc=7, w_th=tuple(w_th), slab=(3, 13))
+    e = picgen.electrons(wl)
+    e.w[axis] += 1.0
+    import oracle
+    from paper_1101_0809_amd import Sim
+    sim = Sim(wl.nx, wl.ny, wl.nz, wl.dt, precision=precision, sort_every=4)
+    sim.add_species(e.q, e.m, e.n)
+    sim.load(0, e.x, e.w, e.weight)
+    st = oracle.State(oracle.Grid(wl.nx, wl.ny, wl.nz, wl.dt), [oracle.Species(e.x, e.w, e.weight, q=e.q, m=e.m)])
+    sim.step(10)
+    st.step(10)
+    _compare(sim, st, wl, *tols)
