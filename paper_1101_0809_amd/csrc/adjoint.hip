@@ -894,10 +894,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
         int rel[2];
         bool inside = true;
         for (int ax = 0; ax < 2; ++ax) {
-            int r = i0[ax] - T0[ax];
-            const int n = g.n[ax];
-            if (r > n / 2) r -= n;
-            if (r < -(n / 2)) r += n;
+            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }
@@ -1011,10 +1008,7 @@ __device__ __forceinline__ bool tile_place3(const GridK& g, const AdjArgs& a, in
         const double fl = floor(x);
         i0[ax] = (int)fl;
         d0[ax] = x - fl;
-        int r = i0[ax] - T0[ax];
-        const int n = g.n[ax];
-        if (r > n / 2) r -= n;
-        if (r < -(n / 2)) r += n;
+        const int r = tile_rel(i0[ax], T0[ax], g.n[ax], kAdjT3);
         rel[ax] = r;
         inside = inside && r >= -kAdjM3 && r <= kAdjT3 - 1 + kAdjM3;
     }

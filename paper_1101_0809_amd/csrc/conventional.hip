@@ -21,14 +21,6 @@ namespace {
 
 __device__ __forceinline__ void add_global(double* p, double v) { unsafeAtomicAdd(p, v); }
 
-__device__ __forceinline__ int rel_of(int i, int t0, int n)
-{
-    int r = i - t0;
-    if (r > n / 2) r -= n;
-    if (r < -(n / 2)) r += n;
-    return r;
-}
-
 constexpr int kCvT2 = kTile2, kCvM2 = 2, kCvNT2 = 256;
 
 __global__ __launch_bounds__(kCvNT2) void k_step_conv2(GridK g, StepArgs a, const double* __restrict__ fields,
@@ -62,7 +54,7 @@ __global__ __launch_bounds__(kCvNT2) void k_step_conv2(GridK g, StepArgs a, cons
         const double qp = a.q * ((const double*)a.weight)[p];
         AxisC<double> ax0[3];
         for (int ax = 0; ax < 3; ++ax) ax0[ax] = form_factor_conv<double>(d0[ax]);
-        const int rel[2] = {rel_of(i0[0], T0[0], nx), rel_of(i0[1], T0[1], ny)};
+        const int rel[2] = {tile_rel(i0[0], T0[0], nx, T), tile_rel(i0[1], T0[1], ny, T)};
         const bool inside = rel[0] >= -M && rel[0] <= T - 1 + M && rel[1] >= -M && rel[1] <= T - 1 + M;
         double E[3], B[3];
         if (inside) {
@@ -155,7 +147,7 @@ __global__ __launch_bounds__(kCvNT3) void k_push_conv3(GridK g, StepArgs a, Part
         int rel[3];
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
-            rel[ax] = rel_of(i0[ax], T0[ax], g.n[ax]);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         my_fallback += inside ? 0 : 1;
@@ -225,7 +217,7 @@ __global__ __launch_bounds__(kCvNT3) void k_deposit_conv3(GridK g, StepArgs a, P
             cell_weights<double>(x1 - floor(x1), s1[ax]);
             window<double>(s0[ax], s1[ax], delta, dm[ax], dp[ax]);
             s[ax] = (delta < 0 ? -1 : 0) - 1;
-            rel[ax] = rel_of(i0[ax], T0[ax], g.n[ax]);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         if (first && !(still && inside)) {

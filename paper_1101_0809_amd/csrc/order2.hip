@@ -90,10 +90,7 @@ __global__ __launch_bounds__(kO2NT2) void k_step_o2(GridK g, StepArgs a, const d
         int rel[3] = {0, 0, 0};
         bool inside = true;
         for (int ax = 0; ax < D; ++ax) {
-            int r = i0[ax] - T0[ax];
-            const int n = g.n[ax];
-            if (r > n / 2) r -= n;
-            if (r < -(n / 2)) r += n;
+            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }
@@ -220,10 +217,7 @@ __global__ __launch_bounds__(kO2NT3) void k_push_o2_3d(GridK g, StepArgs a, Part
         int rel[3];
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
-            int r = i0[ax] - T0[ax];
-            const int n = g.n[ax];
-            if (r > n / 2) r -= n;
-            if (r < -(n / 2)) r += n;
+            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }
@@ -289,10 +283,7 @@ __device__ __forceinline__ bool o2_windows(const GridK& g, const StepArgs& a, co
         mv.still = mv.still && shift == 0;
         window5_reg(e0.s, e1.s, shift, dm[ax], dp[ax]);
         mv.s[ax] = e0.h + (shift < 0 ? shift : 0) - 2;
-        int r = mv.i0[ax] - T0[ax];
-        const int n = g.n[ax];
-        if (r > n / 2) r -= n;
-        if (r < -(n / 2)) r += n;
+        const int r = tile_rel(mv.i0[ax], T0[ax], g.n[ax], kTile3);
         mv.rel[ax] = r;
         inside = inside && r >= -M && r <= kTile3 - 1 + M;
     }

@@ -150,14 +150,11 @@ __global__ __launch_bounds__(NT) void k_particle_step2(GridK g, StepArgs a, cons
         for (int ax = 0; ax < 2; ++ax) ax0[ax] = form_factor<R>(d0[ax]);
         ax0[2] = form_factor<R>(R(0));
 
-        // position relative to the tile, periodic-corrected
+        // position relative to the tile
         int rel[2];
         bool inside = true;
         for (int ax = 0; ax < 2; ++ax) {
-            int r = i0[ax] - T0[ax];
-            const int n = g.n[ax];
-            if (r > n / 2) r -= n;
-            if (r < -(n / 2)) r += n;
+            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             rel[ax] = r;
             inside = inside && (r >= -M) && (r <= T - 1 + M);
         }
@@ -395,7 +392,7 @@ __device__ __forceinline__ void flush_current3(const GridK& g, const int T0[3], 
         }
 }
 
-// Position of cell i0 relative to the tile at T0, periodic-corrected; true if
+// Position of cell i0 relative to the tile at T0 (tile_rel); true if
 // within the tile's margins (MX along x, M along y and z: inside its LDS
 // regions).
 template <class R>
@@ -405,10 +402,7 @@ __device__ __forceinline__ bool relative3(const GridK& g, const int T0[3], const
     bool in = true;
     for (int ax = 0; ax < 3; ++ax) {
         const int m = ax == 0 ? Tile3<R>::MX : Tile3<R>::M;
-        int r = i0[ax] - T0[ax];
-        const int n = g.n[ax];
-        if (r > n / 2) r -= n;
-        if (r < -(n / 2)) r += n;
+        const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
         rel[ax] = r;
         in = in && (r >= -m) && (r <= T - 1 + m);
     }
@@ -1212,10 +1206,7 @@ __global__ __launch_bounds__(NT) void k_rho_tiled(GridK g, PartArrays src, const
         int rel[3] = {0, 0, 0};
         bool inside = true;
         for (int ax = 0; ax < D; ++ax) {
-            int r = i[ax] - T0[ax];
-            const int n = g.n[ax];
-            if (r > n / 2) r -= n;
-            if (r < -(n / 2)) r += n;
+            const int r = tile_rel(i[ax], T0[ax], g.n[ax], T);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }

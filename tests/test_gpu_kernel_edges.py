@@ -44,3 +44,22 @@ def test_3d_crossings_along_one_axis(axis, precision, tols):
     sim.step(10)
     st.step(10)
     _compare(sim, st, wl, *tols)
+
+
+@pytest.mark.parametrize("n,options", [
+    ((13, 10, 11), dict()), ((9, 15, 14), dict(precision="fp32c")), ((13, 10, 11), dict(order=2)),
+    ((13, 10, 11), dict(interp="conventional")), ((17, 31, 1), dict()), ((25, 19, 1), dict(precision="fp32c")),
+    ((17, 25, 1), dict(order=2))])
+def test_short_axes_stay_on_the_tiles(n, options):
+    """On an axis shorter than two tiles every particle lies inside its tile's
+    LDS region right after a sort: none takes the global-memory path (the
+    2D3V conventional step reports no such count)."""
+    from paper_1101_0809_amd import Sim
+    dims = 2 if n[2] == 1 else 3
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=n[0], ny=n[1], nz=n[2], dims=dims, ppc=5, w_th=(0.02,) * 3)
+    e = picgen.electrons(wl)
+    sim = Sim(*n, 0.4, dims=dims, sort_every=1, **options)
+    sim.add_species(e.q, e.m, e.n)
+    sim.load(0, e.x, e.w, e.weight)
+    sim.step(3)
+    assert sim.fallback_fraction() == 0.0 and sim.migrant_fraction() == 0.0
