@@ -573,7 +573,8 @@ __device__ __forceinline__ void advance_global3(const GridK& g, const StepArgs& 
 
 template <class R, int NT, int KC>
 __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, const double* __restrict__ fields,
-                                                      const double* __restrict__ bfield, double* __restrict__ Jg)
+                                                      const double* __restrict__ bfield, double* __restrict__ Jg,
+                                                      int split)
 {
     constexpr int NW = NT / 64;  // waves
     constexpr int WCH = 64 * KC;  // slots per wave chunk
@@ -606,15 +607,23 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
     __shared__ unsigned int n_migrant;
     __shared__ unsigned int next_chunk, next_cross;  // work counters of the waves
 
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
+    const int tile = unit / split;
     const int tx = tile % g.nt[0];
     const int ty = (tile / g.nt[0]) % g.nt[1];
     const int tz = tile / (g.nt[0] * g.nt[1]);
     const int T0[3] = {tx * T, ty * T, tz * T};
     const bool small = g.n[0] < LJX || g.n[1] < LJY || g.n[2] < LJY;
     const int wv = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    if (begin == end) return;  // no particle: nothing to stage, deposit or count (the whole workgroup)
+    // this workgroup's share of the tile's slots: whole wave chunks (all of the
+    // scratch lists below are kept at the slots' own index range)
+    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    if (split > 1) {
+        const int64_t len = ((end - begin + split - 1) / split + WCH - 1) / WCH * WCH;
+        begin += (unit - tile * split) * len;
+        end = min(begin + len, end);
+    }
+    if (begin >= end) return;  // no particle: nothing to stage, deposit or count (the whole workgroup)
 
     // 1. stage E^n and B^n (B^n from bfield) into LDS
     stage_fields3<R, NT>(g, T0, fields, bfield, sf, small);
@@ -1325,6 +1334,30 @@ dim3 grid2(const GridK& k, int64_t n, int* split)
     return dim3((unsigned)(k.ntiles * *split));
 }
 
+// Workgroups of the 3D step: its LDS takes a whole CU, so `split` workgroups
+// per tile run in ceil(tiles * split / CUs) rounds, each costing the staging
+// and the flush (as much as about 1200 particles in FP64, 2200 in FP32 mode)
+// and the tile's share of the particles.  us per step at 1, 2, 3, 4, 8 per
+// tile (FP64): 87, 62, 54, 49, 47 for 24^3 x 8 (27 tiles; 8 taken); 77, 59, 81,
+// 77, 110 for 45 x 37 x 29 x 6 (120 tiles; 2 taken); 101, 134, 163, 198, 329
+// for 64^3 x 2 (512 tiles; 1 taken).
+constexpr int64_t kFixed3 = 1200, kFixed3f = 2200;  // FP64, FP32 mode
+dim3 grid3(const GridK& k, int64_t n, int64_t fixed, int* split)
+{
+    const int64_t avg = n / k.ntiles + 1;
+    int64_t best = 0;
+    *split = 1;
+    for (int w = 1; w <= 16; ++w) {
+        const int64_t rounds = ((int64_t)k.ntiles * w + kCus - 1) / kCus;
+        const int64_t cost = rounds * (fixed + avg / w);
+        if (w == 1 || cost < best) {
+            best = cost;
+            *split = w;
+        }
+    }
+    return dim3((unsigned)(k.ntiles * *split));
+}
+
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
@@ -1340,8 +1373,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
     if (c.g.precision == PIC_FP64) {
         StepArgs a = step_args<double>(c, sp, c.counters);
         if (c.k.dims == 3) {
-            hipLaunchKernelGGL((k_particle_step3<double, kThreads3, kChunk3>), grid, dim3(kThreads3), 0, s, c.k, a,
-                               c.fields, c.bn, J);
+            hipLaunchKernelGGL((k_particle_step3<double, kThreads3, kChunk3>), grid3(c.k, sp.n, kFixed3, &split),
+                               dim3(kThreads3), 0, s, c.k, a, c.fields, c.bn, J, split);
             hipLaunchKernelGGL((k_migrants3<double, kThreadsMig>), grid, dim3(kThreadsMig), 0, s, c.k, a,
                                c.fields, c.bn, J);
         }
@@ -1351,8 +1384,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
     } else {
         StepArgs a = step_args<float>(c, sp, c.counters);
         if (c.k.dims == 3) {
-            hipLaunchKernelGGL((k_particle_step3<float, kThreads3f, kChunk3f>), grid, dim3(kThreads3f), 0, s, c.k, a,
-                               c.fields, c.bn, J);
+            hipLaunchKernelGGL((k_particle_step3<float, kThreads3f, kChunk3f>), grid3(c.k, sp.n, kFixed3f, &split),
+                               dim3(kThreads3f), 0, s, c.k, a, c.fields, c.bn, J, split);
             hipLaunchKernelGGL((k_migrants3<float, kThreadsMigf>), grid, dim3(kThreadsMigf), 0, s, c.k, a,
                                c.fields, c.bn, J);
         }

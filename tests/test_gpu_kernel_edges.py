@@ -46,6 +46,17 @@ def test_3d_crossings_along_one_axis(axis, precision, tols):
     _compare(sim, st, wl, *tols)
 
 
+@pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
+@pytest.mark.parametrize("n,ppc", [((8, 8, 8), 1), ((9, 8, 16), 3), ((13, 14, 17), 3), ((24, 9, 8), 30), ((20, 14, 17), 60)])
+def test_3d_step_shares_a_tile(n, ppc, precision, tols):
+    """3D grids of few tiles, whose particles several workgroups share: shares
+    of less than a wave's chunk, empty shares, and more than one chunk per
+    wave; hot, so that particles cross cells and leave their tiles."""
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=n[0], ny=n[1], nz=n[2], ppc=ppc, w_th=(0.4,) * 3)
+    sim, st, _ = _run_pair(wl, precision, 8, sort_every=4)
+    _compare(sim, st, wl, *tols)
+
+
 @pytest.mark.parametrize("n,options", [
     ((13, 10, 11), dict()), ((9, 15, 14), dict(precision="fp32c")), ((13, 10, 11), dict(order=2)),
     ((13, 10, 11), dict(interp="conventional")), ((17, 31, 1), dict()), ((25, 19, 1), dict(precision="fp32c")),
