@@ -74,3 +74,28 @@ def test_short_axes_stay_on_the_tiles(n, options):
     sim.load(0, e.x, e.w, e.weight)
     sim.step(3)
     assert sim.fallback_fraction() == 0.0 and sim.migrant_fraction() == 0.0
+
+
+@pytest.mark.parametrize("n", [(3, 5, 2), (64, 64, 64), (65, 64, 64), (67, 129, 96), (513, 512, 1)])
+def test_poisson_cells_per_thread(n):
+    """The conjugate-gradient kernels at one cell per thread or fewer, exactly
+    one for every thread (64^3), one more, and several: against the FFT solve
+    of the same charge density (the field bar of test_gpu_poisson.py)."""
+    import numpy as np
+    import oracle
+    from oracle import poisson
+    from paper_1101_0809_amd import Sim
+    dims = 2 if n[2] == 1 else 3
+    rng = np.random.Generator(np.random.PCG64(17))
+    count = 4000
+    x = rng.uniform(0, 1, (3, count)) * np.array(n, dtype=float)[:, None]
+    w, weight = np.zeros((3, count)), np.full(count, 1e-3)
+    sim = Sim(*n, 0.4, dims=dims)
+    sim.add_species(-1.0, 1.0, count)
+    sim.load(0, x, w, weight)
+    it, res = sim.solve_poisson(neutralize=True)
+    assert res <= 1e-13 and it > 0
+    g = oracle.Grid(*n, 0.4)
+    rho = oracle.State(g, [oracle.Species(x, w, weight, q=-1.0, m=1.0)]).rho()
+    E = poisson.e_of_phi(g, poisson.solve(g, rho))
+    assert np.linalg.norm(sim.fields_numpy()[:3] - E) <= 1e-9 * np.linalg.norm(E)
