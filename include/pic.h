@@ -319,7 +319,8 @@ int pic_adjoint_reorder(pic_ctx* ctx, const void* from, const void* to, size_t b
  * needs a neutral total: the mean charge density is removed from the right
  * side, and with neutralize = 1 it is also added, with the opposite sign, to
  * the background as a uniform charge (the uniform neutralizing background of
- * a start without co-located ions).  Conjugate gradients on the GPU to a
+ * a start without co-located ions).  A species just loaded is put into
+ * cell order first (its storage order, pic_sort), as its first step would.  Conjugate gradients on the GPU to a
  * relative residual tol (<= 0: 1e-13); *iterations and *residual (either may
  * be NULL) report the count and the reached relative residual.  The Gauss
  * reference R^0 is recaptured before the next step.  Synchronizes the

