@@ -402,6 +402,74 @@ struct Rows3 {
     const double* x[3];
 };
 
+// The same for a cell-sorted species, one workgroup per tile: particles within M
+// cells of their tile accumulate into an LDS density tile (cells T0-2-M ..
+// T0+T+1+M), added to the grid once; the rest go straight to global memory.
+// 64 global atomics per particle took 944 us of an energy sample at 64^3 x 2;
+// the tile takes 40.
+template <int D, int T, int M, int NT>
+__global__ __launch_bounds__(NT) void k_rho_o2_tiled(GridK g, Rows3 pos, const double* __restrict__ weight,
+                                                     const int64_t* __restrict__ ts, double q,
+                                                     double* __restrict__ rho)
+{
+    constexpr int L = T + 4 + 2 * M, LZ = D == 3 ? L : 1, NL = L * L * LZ;
+    __shared__ double sr[NL];
+    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T,
+                       D == 3 ? (tile / (g.nt[0] * g.nt[1])) * T : 0};
+    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    const int64_t begin = ts[tile], end = ts[tile + 1];
+    if (begin == end) return;
+    for (int e = threadIdx.x; e < NL; e += NT) sr[e] = 0.0;
+    __syncthreads();
+    for (int64_t p = begin + threadIdx.x; p < end; p += NT) {
+        int i0[3] = {0, 0, 0}, rel[3] = {0, 0, 0};
+        Axis2<double> w[3];
+        bool inside = true;
+        for (int ax = 0; ax < 3; ++ax) {
+            double d = 0.0;
+            if (ax < D) {
+                const double x = pos.x[ax][p];
+                const double f = floor(x);
+                i0[ax] = (int)f;
+                d = x - f;
+                rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+                inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
+            }
+            w[ax] = form_factor2<double>(d);
+        }
+        const double qv = q * weight[p] * g.inv_vol;
+        // first point of the window in the LDS tile
+        const int lb = rel[0] + w[0].h + M + L * (rel[1] + w[1].h + M + (D == 3 ? L * (rel[2] + w[2].h + M) : 0));
+#pragma unroll
+        for (int c = 0; c < (D == 3 ? 4 : 1); ++c) {
+            const double wz = D == 3 ? w[2].s[c] : 1.0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const double v = qv * wz * w[1].s[b] * w[0].s[a];
+                    if (inside) {
+                        atomicAdd(&sr[lb + a + L * (b + L * c)], v);
+                    } else {
+                        const int64_t kz = D == 3 ? (int64_t)wrapi(i0[2] + w[2].h - 2 + c, nz) * ny : 0;
+                        add_global(&rho[(kz + wrapi(i0[1] + w[1].h - 2 + b, ny)) * nx + wrapi(i0[0] + w[0].h - 2 + a, nx)],
+                                   v);
+                    }
+                }
+        }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < NL; e += NT) {
+        const double v = sr[e];
+        if (v == 0.0) continue;
+        const int lx = e % L, ly = (e / L) % L, lz = e / (L * L);
+        const int gx = wrapi(T0[0] - 2 - M + lx, nx), gy = wrapi(T0[1] - 2 - M + ly, ny);
+        const int gz = D == 3 ? wrapi(T0[2] - 2 - M + lz, nz) : 0;
+        add_global(&rho[((int64_t)gz * ny + gy) * nx + gx], v);
+    }
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void k_rho_o2(GridK g, Rows3 pos, const double* __restrict__ weight, int64_t n,
                                                 double q, double* __restrict__ rho)
@@ -471,11 +539,17 @@ hipError_t launch_deposit_only_o2(const Ctx& c, const double* x0, const double* 
 }
 
 hipError_t launch_rho_o2(const Ctx& c, const double* const x[3], const double* weight, int64_t n, double q,
-                         double* rho, hipStream_t s)
+                         double* rho, hipStream_t s, const int64_t* tile_start)
 {
     if (n == 0) return hipSuccess;
     Rows3 pos{{x[0], x[1], x[2]}};
-    if (c.k.dims == 3)
+    if (tile_start && c.k.dims == 3)
+        hipLaunchKernelGGL((k_rho_o2_tiled<3, kTile3, 2, 256>), dim3(c.k.ntiles), dim3(256), 0, s, c.k, pos, weight,
+                           tile_start, q, rho);
+    else if (tile_start)
+        hipLaunchKernelGGL((k_rho_o2_tiled<2, kTile2, 2, 256>), dim3(c.k.ntiles), dim3(256), 0, s, c.k, pos, weight,
+                           tile_start, q, rho);
+    else if (c.k.dims == 3)
         hipLaunchKernelGGL(k_rho_o2<3>, dim3(blocks256(n)), dim3(256), 0, s, c.k, pos, weight, n, q, rho);
     else
         hipLaunchKernelGGL(k_rho_o2<2>, dim3(blocks256(n)), dim3(256), 0, s, c.k, pos, weight, n, q, rho);

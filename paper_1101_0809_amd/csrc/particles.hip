@@ -1460,7 +1460,8 @@ hipError_t launch_rho(const Ctx& c, const Species& sp, double* rho, hipStream_t 
     if (c.g.order == 2) {
         const double* x[3] = {(const double*)sp.cur.pos[0], (const double*)sp.cur.pos[1],
                               (const double*)sp.cur.pos[2]};
-        return launch_rho_o2(c, x, (const double*)sp.cur.weight, sp.n, sp.d.q, rho, s);
+        return launch_rho_o2(c, x, (const double*)sp.cur.weight, sp.n, sp.d.q, rho, s,
+                             sp.sorted ? sp.tile_start : nullptr);
     }
     if (sp.sorted) {  // tiles are valid: LDS accumulation per tile
         const dim3 tg(c.k.ntiles);

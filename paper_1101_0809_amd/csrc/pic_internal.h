@@ -179,8 +179,9 @@ hipError_t launch_sort(Ctx& c, Species& sp, hipStream_t s);
 hipError_t launch_particle_step_o2(Ctx& c, Species& sp, hipStream_t s);
 hipError_t launch_deposit_only_o2(const Ctx& c, const double* x0, const double* x1, const double* charge,
                                   int64_t n, double* J, hipStream_t s);
+// tile_start: the tiles of the particles' last sort, or null (any order).
 hipError_t launch_rho_o2(const Ctx& c, const double* const x[3], const double* weight, int64_t n, double q,
-                         double* rho, hipStream_t s);
+                         double* rho, hipStream_t s, const int64_t* tile_start = nullptr);
 // The conventional interpolation of Eq. wrong1 (grid interp 1, order 1, FP64).
 hipError_t launch_particle_step_conv(Ctx& c, Species& sp, hipStream_t s);
 // rho_m (N doubles) and part (diag_partials_doubles) are scratch; null: the workspace's.
