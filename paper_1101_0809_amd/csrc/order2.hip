@@ -13,7 +13,9 @@
 // plus M) in LDS, added to the grid once at the end; in 3D the two regions
 // are handled by two passes.  A particle further than M cells from its tile
 // reads and adds in global memory instead.
-#include "pic_math.h"
+#include <type_traits>
+
+#include "tile_io.h"
 
 namespace pic {
 namespace {
@@ -176,54 +178,81 @@ __global__ __launch_bounds__(kO2NT2) void k_step_o2(GridK g, StepArgs a, const d
 // the single pass could afford (its two regions at margin 0 fill the LDS).
 // Pass 1: gather, push and move with E^n, B^n over cells T0-3 .. T0+T+2 (132
 // KB); the start position goes to the spare particle copy (idle between
-// sorts) and the per-axis cell shifts to its id array.  Pass 2: the current
-// over cells T0-5 .. T0+T+4 (140 KB).
-constexpr int kO2M3a = 1, kO2M3b = 2, kO2NT3 = 512;
+// sorts) and a word on the move (MoveWord) to its id array.  Pass 2: the
+// current over cells T0-5 .. T0+T+4 (140 KB).  Both are bound by the LDS (252
+// reads, 144 or 300 atomics per particle), so both take the particles in
+// class rows (order_rows) of the stencil's first point: the sort's own class
+// order does not serve them, since the stencil starts at int(x + 1/2).  LDS
+// bank conflicts fell from 33 and 19% of the CU-busy cycles to 7 and 5%, the
+// passes from 86 and 98 to 76 and 76 us at 64^3 x 2 per cell (half of it the
+// staging and flush of 1024 particles' tiles), and 20 steps of 64^3 x 6 from
+// 11.6 to 7.0 ms with the energies.  Pass 1 has two waves per SIMD to hide
+// its latencies: 768 threads spill 43 registers and gain nothing.
+constexpr int kO2M3a = 1, kO2M3b = 2;
+constexpr int kO2NTa = 512, kO2Ua = 4;  // pass 1 (200 VGPRs): threads, slots per thread ordered at a time
+constexpr int kO2NTb = 768, kO2Ub = 2;  // pass 2 (150 VGPRs)
+constexpr int64_t kO2Fixed = 800;  // staging and flush, in particles (tile_split)
 
-__global__ __launch_bounds__(kO2NT3) void k_push_o2_3d(GridK g, StepArgs a, PartArrays spare,
+// Pass 1's word on a particle's move: bits 2 ax .. 2 ax + 1 the cell shift plus
+// one, bit 6 int(x + 1/2) unchanged on every axis, bit 7 the particle within
+// the current region's margin of the tile, bits 8 .. 11 the class of its
+// window's first cell there.
+constexpr int kMvStill = 64, kMvInside = 128;
+
+__global__ __launch_bounds__(kO2NTa) void k_push_o2_3d(GridK g, StepArgs a, PartArrays spare,
                                                        const double* __restrict__ fields,
-                                                       const double* __restrict__ bfield)
+                                                       const double* __restrict__ bfield, int split)
 {
-    constexpr int T = kTile3, M = kO2M3a, NT = kO2NT3;
+    constexpr int T = kTile3, M = kO2M3a, NT = kO2NTa;
     constexpr int LF = T + 4 + 2 * M, NF = LF * LF * LF;
+    constexpr int MB = kO2M3b, LJ = T + 6 + 2 * MB;
     __shared__ double sf[6 * NF];
+    __shared__ ClassRows<NT, kO2Ua> rows;
     __shared__ unsigned int n_fallback;
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
+    const int tile = unit / split;
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T, (tile / (g.nt[0] * g.nt[1])) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    for (int e = threadIdx.x; e < 6 * NF; e += NT) {
-        const int comp = e / NF, r = e - comp * NF;
-        const int gx = wrapi(T0[0] - 2 - M + r % LF, nx);
-        const int gy = wrapi(T0[1] - 2 - M + (r / LF) % LF, ny);
-        const int gz = wrapi(T0[2] - 2 - M + r / (LF * LF), nz);
-        const int64_t cell = ((int64_t)gz * ny + gy) * nx + gx;
-        sf[e] = comp < 3 ? fields[comp * N + cell] : bfield[(comp - 3) * N + cell];
+    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    tile_share(unit - tile * split, split, begin, end);
+    if (begin >= end) return;
+    {
+        const bool small = nx < LF || ny < LF || nz < LF;
+        const Columns<LF, LF, LF> cols(g, T0[0] - 2 - M, T0[1] - 2 - M, small);
+        stage_planes<6 * LF, NT, 2, double>(
+            cols,
+            [&](int t) {
+                const int comp = t / LF;
+                return (comp < 3 ? fields + comp * N : bfield + (comp - 3) * N) +
+                       plane_offset(g, T0[2] - 2 - M + t - comp * LF, small);
+            },
+            [&](int t) { return sf + t * (LF * LF); });
     }
     if (threadIdx.x == 0) n_fallback = 0;
-    __syncthreads();
     const double c2 = g.c * g.c;
     const double qmdt2 = 0.5 * a.qm * g.dt;
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    unsigned int my_fallback = 0;
-    for (int64_t p = begin + threadIdx.x; p < end; p += NT) {
-        int i0[3];
-        double d0[3];
+
+    // Cell relative to the tile; true inside the field region.
+    auto place = [&](const int i0[3], int rel[3]) -> bool {
+        bool inside = true;
+        for (int ax = 0; ax < 3; ++ax) {
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
+        }
+        return inside;
+    };
+    auto advance = [&](int64_t p, auto on_tile) {
+        constexpr bool kTileFields = decltype(on_tile)::value;
+        int i0[3], rel[3];
+        double d0[3], w[3];
         PosIO<double, 3>::load(a, p, i0, d0);
-        double w[3];
         for (int ax = 0; ax < 3; ++ax) w[ax] = ((const double*)a.mom[ax])[p];
         Axis2<double> ax0[3];
         for (int ax = 0; ax < 3; ++ax) ax0[ax] = form_factor2<double>(d0[ax]);
-        int rel[3];
-        bool inside = true;
-        for (int ax = 0; ax < 3; ++ax) {
-            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
-            rel[ax] = r;
-            inside = inside && r >= -M && r <= T - 1 + M;
-        }
-        my_fallback += inside ? 0 : 1;
+        place(i0, rel);
         double E[3], B[3];
-        if (inside) {
+        if (kTileFields) {
             const int fb = (rel[0] + 2 + M) + (rel[1] + 2 + M) * LF + (rel[2] + 2 + M) * LF * LF;
             auto F = [&](int comp, int oa, int ob, int oc) -> double {
                 return sf[comp * NF + fb + oa + ob * LF + oc * LF * LF];
@@ -245,11 +274,38 @@ __global__ __launch_bounds__(kO2NT3) void k_push_o2_3d(GridK g, StepArgs a, Part
         for (int ax = 0; ax < 3; ++ax) disp[ax] = w[ax] * inv * g.cfl[ax];
         int delta[3] = {0, 0, 0};
         PosIO<double, 3>::move(a, p, g, i0, d0, disp, d1, delta, true);
-        for (int ax = 0; ax < 3; ++ax) ((double*)spare.pos[ax])[p] = (double)i0[ax] + d0[ax];
-        spare.id[p] = (int64_t)((delta[0] + 1) | ((delta[1] + 1) << 2) | ((delta[2] + 1) << 4));
+        int word = kMvStill | kMvInside, jb = 0;
+        constexpr int stride[3] = {1, LJ, LJ * LJ};
+        for (int ax = 0; ax < 3; ++ax) {
+            ((double*)spare.pos[ax])[p] = (double)i0[ax] + d0[ax];
+            const int shift = delta[ax] + (d1[ax] >= 0.5 ? 1 : 0) - ax0[ax].h;
+            word |= (delta[ax] + 1) << (2 * ax);
+            if (shift != 0) word &= ~kMvStill;
+            if (rel[ax] < -MB || rel[ax] > T - 1 + MB) word &= ~kMvInside;
+            jb += (rel[ax] + ax0[ax].h + (shift < 0 ? shift : 0) + 1 + MB) * stride[ax];
+        }
+        spare.id[p] = (int64_t)(word | (jb & (kRowClasses - 1)) << 8);
+    };
+
+    uint32_t* out = (uint32_t*)spare.weight + 2 * begin;  // particles off the field region (4 bytes of 8 used)
+    for (int64_t cb = begin; cb < end; cb += ClassRows<NT, kO2Ua>::W) {
+        __syncthreads();  // the fields are staged; the last chunk's order is used up
+        const int m = (int)min(end - cb, (int64_t)ClassRows<NT, kO2Ua>::W);
+        const int nin = order_rows(rows, m, [&](int sl) -> int {
+            int i0[3], rel[3];
+            double d0[3];
+            PosIO<double, 3>::load(a, cb + sl, i0, d0);
+            if (!place(i0, rel)) {
+                out[atomicAdd(&n_fallback, 1u)] = (uint32_t)(cb - begin + sl);
+                return -1;
+            }
+            const int h[3] = {d0[0] >= 0.5 ? 1 : 0, d0[1] >= 0.5 ? 1 : 0, d0[2] >= 0.5 ? 1 : 0};
+            return ((rel[0] + M + h[0]) + (rel[1] + M + h[1]) * LF + (rel[2] + M + h[2]) * LF * LF) & (kRowClasses - 1);
+        });
+        for (int q = threadIdx.x; q < nin; q += NT) advance(cb + rows.perm[q], std::true_type{});
     }
-    if (my_fallback) atomicAdd(&n_fallback, my_fallback);
     __syncthreads();
+    for (unsigned q = threadIdx.x; q < n_fallback; q += NT) advance(begin + out[q], std::false_type{});
     if (threadIdx.x == 0 && a.counters) {
         atomicAdd(&a.counters[1], (unsigned long long)n_fallback);
         atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
@@ -257,20 +313,15 @@ __global__ __launch_bounds__(kO2NT3) void k_push_o2_3d(GridK g, StepArgs a, Part
 }
 
 // One particle's windows for the current pass: start position from the spare
-// copy, end position and cell shifts from pass 1.  Returns whether the
-// particle is within the current region's margin of the tile.
+// copy, end position and cell shifts from pass 1.
 struct O2Move {
     int i0[3], rel[3], s[3];
-    bool still;
 };
 
-__device__ __forceinline__ bool o2_windows(const GridK& g, const StepArgs& a, const PartArrays& spare, int64_t p,
-                                           const int T0[3], int M, double (&dm)[3][5], double (&dp)[3][5],
-                                           O2Move& mv)
+__device__ __forceinline__ void o2_windows(const GridK& g, const StepArgs& a, const PartArrays& spare, int64_t p,
+                                           const int T0[3], double (&dm)[3][5], double (&dp)[3][5], O2Move& mv)
 {
     const int64_t code = spare.id[p];
-    bool inside = true;
-    mv.still = true;
     for (int ax = 0; ax < 3; ++ax) {
         const double x0 = ((const double*)spare.pos[ax])[p];
         const double x1 = ((const double*)a.pos[ax])[p];
@@ -280,80 +331,95 @@ __device__ __forceinline__ bool o2_windows(const GridK& g, const StepArgs& a, co
         const Axis2<double> e0 = form_factor2<double>(x0 - f0);
         const Axis2<double> e1 = form_factor2<double>(x1 - f1);
         const int shift = delta + e1.h - e0.h;
-        mv.still = mv.still && shift == 0;
         window5_reg(e0.s, e1.s, shift, dm[ax], dp[ax]);
         mv.s[ax] = e0.h + (shift < 0 ? shift : 0) - 2;
-        const int r = tile_rel(mv.i0[ax], T0[ax], g.n[ax], kTile3);
-        mv.rel[ax] = r;
-        inside = inside && r >= -M && r <= kTile3 - 1 + M;
+        mv.rel[ax] = tile_rel(mv.i0[ax], T0[ax], g.n[ax], kTile3);
     }
-    return inside;
 }
 
-// Pass 2.  Particles whose int(x + 1/2) stays put on every axis (most of
-// them at thermal speeds) deposit their 144 contributions at once; the
-// others are queued (their indices in the spare copy's weight array, at the
-// tile's own index range) and deposit their 300 afterwards, so that a wave
-// does not run both forms for a few lanes.
-__global__ __launch_bounds__(kO2NT3) void k_deposit_o2_3d(GridK g, StepArgs a, PartArrays spare,
-                                                          double* __restrict__ Jg)
+// Pass 2.  First the particles whose int(x + 1/2) stays put on every axis (most
+// of them at thermal speeds; 144 contributions), then the others within the
+// region (300), then those outside it, so that a wave does not run two forms
+// for a few lanes.
+__global__ __launch_bounds__(kO2NTb) void k_deposit_o2_3d(GridK g, StepArgs a, PartArrays spare,
+                                                          double* __restrict__ Jg, int split)
 {
-    constexpr int T = kTile3, M = kO2M3b, NT = kO2NT3;
+    constexpr int T = kTile3, M = kO2M3b, NT = kO2NTb;
     constexpr int LJ = T + 6 + 2 * M, NJ = LJ * LJ * LJ;
     __shared__ double sj[3 * NJ];
-    __shared__ unsigned int qn;
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    __shared__ ClassRows<NT, kO2Ub> rows;
+    __shared__ unsigned int n_cross, n_out;
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
+    const int tile = unit / split;
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T, (tile / (g.nt[0] * g.nt[1])) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    tile_share(unit - tile * split, split, begin, end);
+    if (begin >= end) return;
     for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj[e] = 0.0;
-    if (threadIdx.x == 0) qn = 0;
-    __syncthreads();
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    int64_t* queue = (int64_t*)spare.weight + begin;  // end - begin entries
-    auto deposit = [&](int64_t p, bool allow_still) {
+    if (threadIdx.x == 0) n_cross = n_out = 0;
+    auto deposit = [&](int64_t p, auto form) {  // 0: still, 1: crossing, 2: outside
+        constexpr int kForm = decltype(form)::value;
         double dm[3][5], dp[3][5];
         O2Move mv;
-        const bool inside = o2_windows(g, a, spare, p, T0, M, dm, dp, mv);
-        if (allow_still && !(mv.still && inside)) {
-            queue[atomicAdd(&qn, 1u)] = p;
-            return;
-        }
+        o2_windows(g, a, spare, p, T0, dm, dp, mv);
         const double qp = a.q * ((const double*)a.weight)[p];
         double jfac[3];
         for (int ax = 0; ax < 3; ++ax) jfac[ax] = g.jscale[ax] * qp;
-        if (inside) {
+        if (kForm < 2) {
             const int jb = (mv.rel[0] + mv.s[0] + 3 + M) + (mv.rel[1] + mv.s[1] + 3 + M) * LJ +
                            (mv.rel[2] + mv.s[2] + 3 + M) * LJ * LJ;
             auto S = [&](int comp, int ix, int iy, int iz, double v) {
                 atomicAdd(&sj[comp * NJ + jb + ix + iy * LJ + iz * LJ * LJ], v);
             };
-            if (allow_still) deposit3_o2_still<double>(dm, dp, jfac, S);
+            if (kForm == 0) deposit3_o2_still<double>(dm, dp, jfac, S);
             else deposit3_o2<double>(dm, dp, jfac, S);
         } else {
+            int xi[5], yj[5];
+            int64_t zk[5];
+#pragma unroll
+            for (int o = 0; o < 5; ++o) {
+                xi[o] = wrapi(mv.i0[0] + mv.s[0] + o, nx);
+                yj[o] = wrapi(mv.i0[1] + mv.s[1] + o, ny) * nx;
+                zk[o] = (int64_t)wrapi(mv.i0[2] + mv.s[2] + o, nz) * ny * nx;
+            }
             auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                const int64_t cell =
-                    ((int64_t)wrapi(mv.i0[2] + mv.s[2] + iz, nz) * ny + wrapi(mv.i0[1] + mv.s[1] + iy, ny)) * nx +
-                    wrapi(mv.i0[0] + mv.s[0] + ix, nx);
-                add_global(&Jg[comp * N + cell], v);
+                add_global(&Jg[comp * N + zk[iz] + yj[iy] + xi[ix]], v);
             };
             deposit3_o2<double>(dm, dp, jfac, S);
         }
     };
-    for (int64_t p = begin + threadIdx.x; p < end; p += NT) deposit(p, true);
-    __syncthreads();
-    const int64_t nq = qn;
-    for (int64_t k = threadIdx.x; k < nq; k += NT) deposit(queue[k], false);
-    __syncthreads();
-    for (int e = threadIdx.x; e < 3 * NJ; e += NT) {
-        const double v = sj[e];
-        if (v == 0.0) continue;
-        const int comp = e / NJ, r = e - comp * NJ;
-        const int gx = wrapi(T0[0] - 3 - M + r % LJ, nx);
-        const int gy = wrapi(T0[1] - 3 - M + (r / LJ) % LJ, ny);
-        const int gz = wrapi(T0[2] - 3 - M + r / (LJ * LJ), nz);
-        add_global(&Jg[comp * N + ((int64_t)gz * ny + gy) * nx + gx], v);
-    }
+    auto in_rows = [&](auto form) {
+        constexpr int want = decltype(form)::value == 0 ? kMvStill | kMvInside : kMvInside;
+        for (int64_t cb = begin; cb < end; cb += ClassRows<NT, kO2Ub>::W) {
+            __syncthreads();  // the region is clear; the last chunk's order is used up
+            const int m = (int)min(end - cb, (int64_t)ClassRows<NT, kO2Ub>::W);
+            const int n = order_rows(rows, m, [&](int sl) -> int {
+                const int word = (int)spare.id[cb + sl];
+                if (want & kMvStill) {
+                    if (!(word & kMvInside)) n_out = 1;
+                    else if (!(word & kMvStill)) n_cross = 1;
+                }
+                return (word & (kMvStill | kMvInside)) == want ? (word >> 8) & (kRowClasses - 1) : -1;
+            });
+            for (int q = threadIdx.x; q < n; q += NT) deposit(cb + rows.perm[q], form);
+        }
+        __syncthreads();
+    };
+    in_rows(std::integral_constant<int, 0>{});
+    if (n_cross) in_rows(std::integral_constant<int, 1>{});
+    if (n_out)
+        for (int64_t p = begin + threadIdx.x; p < end; p += NT)
+            if (!((int)spare.id[p] & kMvInside)) deposit(p, std::integral_constant<int, 2>{});
+    const bool small = nx < LJ || ny < LJ || nz < LJ;
+    const Columns<LJ, LJ, LJ> cols(g, T0[0] - 3 - M, T0[1] - 3 - M, small);
+    flush_planes<3 * LJ, NT>(
+        cols, [&](int t) { return sj + t * (LJ * LJ); },
+        [&](int t) {
+            const int comp = t / LJ;
+            return Jg + comp * N + plane_offset(g, T0[2] - 3 - M + t - comp * LJ, small);
+        });
 }
 
 // Current of given moves x0 -> x1 (positions in cell units, x1 not wrapped),
@@ -520,8 +586,10 @@ hipError_t launch_particle_step_o2(Ctx& c, Species& sp, hipStream_t s)
     a.counters = c.counters;
     double* J = c.fields + 6 * c.k.ncell;
     if (c.k.dims == 3) {
-        hipLaunchKernelGGL(k_push_o2_3d, dim3(c.k.ntiles), dim3(kO2NT3), 0, s, c.k, a, sp.alt, c.fields, c.bn);
-        hipLaunchKernelGGL(k_deposit_o2_3d, dim3(c.k.ntiles), dim3(kO2NT3), 0, s, c.k, a, sp.alt, J);
+        const int split = tile_split(c.k.ntiles, sp.n, kO2Fixed);
+        const dim3 grid((unsigned)(c.k.ntiles * split));
+        hipLaunchKernelGGL(k_push_o2_3d, grid, dim3(kO2NTa), 0, s, c.k, a, sp.alt, c.fields, c.bn, split);
+        hipLaunchKernelGGL(k_deposit_o2_3d, grid, dim3(kO2NTb), 0, s, c.k, a, sp.alt, J, split);
     } else
         hipLaunchKernelGGL(k_step_o2<2>, dim3(c.k.ntiles), dim3(kO2NT2), 0, s, c.k, a, c.fields, c.bn, J);
     return hipGetLastError();

@@ -1334,33 +1334,33 @@ dim3 grid2(const GridK& k, int64_t n, int* split)
     return dim3((unsigned)(k.ntiles * *split));
 }
 
-// Workgroups of the 3D step: its LDS takes a whole CU, so `split` workgroups
-// per tile run in ceil(tiles * split / CUs) rounds, each costing the staging
-// and the flush (as much as about 1200 particles in FP64, 2200 in FP32 mode)
-// and the tile's share of the particles.  us per step at 1, 2, 3, 4, 8 per
-// tile (FP64): 87, 62, 54, 49, 47 for 24^3 x 8 (27 tiles; 8 taken); 77, 59, 81,
-// 77, 110 for 45 x 37 x 29 x 6 (120 tiles; 2 taken); 101, 134, 163, 198, 329
-// for 64^3 x 2 (512 tiles; 1 taken).
-constexpr int64_t kFixed3 = 1200, kFixed3f = 2200;  // FP64, FP32 mode
-dim3 grid3(const GridK& k, int64_t n, int64_t fixed, int* split)
-{
-    const int64_t avg = n / k.ntiles + 1;
-    int64_t best = 0;
-    *split = 1;
-    for (int w = 1; w <= 16; ++w) {
-        const int64_t rounds = ((int64_t)k.ntiles * w + kCus - 1) / kCus;
-        const int64_t cost = rounds * (fixed + avg / w);
-        if (w == 1 || cost < best) {
-            best = cost;
-            *split = w;
-        }
-    }
-    return dim3((unsigned)(k.ntiles * *split));
-}
-
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
+// Staging and flush of the 3D step, in particles (tile_split): FP64, FP32 mode.
+constexpr int64_t kFixed3 = 1200, kFixed3f = 2200;
+
 }  // namespace
+
+// Workgroups per tile of a kernel whose LDS takes a whole CU: `split` of them
+// run in ceil(tiles * split / CUs) rounds, each costing the staging and the
+// flush (as much as `fixed` particles) and the tile's share of the particles.
+// The 3D step, us at 1, 2, 3, 4, 8 per tile (FP64): 87, 62, 54, 49, 47 for 24^3
+// x 8 per cell (27 tiles; 8 taken); 77, 59, 81, 77, 110 for 45 x 37 x 29 x 6
+// (120 tiles; 2 taken); 101, 134, 163, 198, 329 for 64^3 x 2 (512 tiles; 1 taken).
+int tile_split(int64_t ntiles, int64_t n, int64_t fixed)
+{
+    const int64_t avg = n / ntiles + 1;
+    int64_t best = 0;
+    int split = 1;
+    for (int w = 1; w <= 16; ++w) {
+        const int64_t cost = (ntiles * w + kCus - 1) / kCus * (fixed + avg / w);
+        if (w == 1 || cost < best) {
+            best = cost;
+            split = w;
+        }
+    }
+    return split;
+}
 
 hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
 {
@@ -1373,7 +1373,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
     if (c.g.precision == PIC_FP64) {
         StepArgs a = step_args<double>(c, sp, c.counters);
         if (c.k.dims == 3) {
-            hipLaunchKernelGGL((k_particle_step3<double, kThreads3, kChunk3>), grid3(c.k, sp.n, kFixed3, &split),
+            split = tile_split(c.k.ntiles, sp.n, kFixed3);
+            hipLaunchKernelGGL((k_particle_step3<double, kThreads3, kChunk3>), dim3(c.k.ntiles * split),
                                dim3(kThreads3), 0, s, c.k, a, c.fields, c.bn, J, split);
             hipLaunchKernelGGL((k_migrants3<double, kThreadsMig>), grid, dim3(kThreadsMig), 0, s, c.k, a,
                                c.fields, c.bn, J);
@@ -1384,7 +1385,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
     } else {
         StepArgs a = step_args<float>(c, sp, c.counters);
         if (c.k.dims == 3) {
-            hipLaunchKernelGGL((k_particle_step3<float, kThreads3f, kChunk3f>), grid3(c.k, sp.n, kFixed3f, &split),
+            split = tile_split(c.k.ntiles, sp.n, kFixed3f);
+            hipLaunchKernelGGL((k_particle_step3<float, kThreads3f, kChunk3f>), dim3(c.k.ntiles * split),
                                dim3(kThreads3f), 0, s, c.k, a, c.fields, c.bn, J, split);
             hipLaunchKernelGGL((k_migrants3<float, kThreadsMigf>), grid, dim3(kThreadsMigf), 0, s, c.k, a,
                                c.fields, c.bn, J);

@@ -164,6 +164,8 @@ hipError_t launch_field_half_a_pair(const Ctx& c, hipStream_t s, unsigned long l
 // B planes = curl_h A (field form 1).
 hipError_t launch_b_of_a(const Ctx& c, hipStream_t s);
 hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s);
+// Workgroups that share a tile of n / ntiles particles on average (host rule).
+int tile_split(int64_t ntiles, int64_t n, int64_t fixed);
 hipError_t launch_load(Ctx& c, Species& sp, int64_t n, const double* x, const double* w,
                        const double* weight, hipStream_t s);
 hipError_t launch_get(const Ctx& c, const Species& sp, double* x, double* w, double* weight,

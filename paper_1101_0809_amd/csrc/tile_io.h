@@ -1,0 +1,176 @@
+// tile_io.h -- moves between the grid and a tile's LDS regions in 3D, and the
+// order in which a workgroup takes a tile's particles so that their LDS
+// accesses do not conflict.
+#pragma once
+
+#include "pic_math.h"
+
+namespace pic {
+namespace {
+
+// The x, y columns of a tile region, dealt to the lanes of every wave: column
+// lane + 64 c at grid offset off[c] within a z plane and at lds[c] within a
+// plane of the region (off < 0: no such column).  A region's planes then go
+// wave by wave with a scalar base address each, so that an element costs its
+// load and its store and no index arithmetic (decoding and wrapping every
+// element took 6 of the 12 us in which a tile of 14^3 cells x 6 was staged).
+template <int LX, int LY, int ROW>
+struct Columns {
+    static constexpr int CH = (LX * LY + 63) / 64;
+    int off[CH], lds[CH];
+    __device__ __forceinline__ Columns(const GridK& g, int fx, int fy, bool small)
+    {
+        auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
+        const int lane = (int)threadIdx.x & 63;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int e = lane + 64 * c, ly = e / LX, lx = e - ly * LX;
+            lds[c] = lx + ly * ROW;
+            off[c] = e < LX * LY ? wr(fy + ly, g.n[1]) * g.n[0] + wr(fx + lx, g.n[0]) : -1;
+        }
+    }
+};
+
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+// Grid offset of z plane gz (in [-n, 2n), or anywhere if the axis is short).
+__device__ __forceinline__ int64_t plane_offset(const GridK& g, int gz, bool small)
+{
+    return (int64_t)(small ? wrapi(gz, g.n[2]) : wrap1(gz, g.n[2])) * g.n[1] * g.n[0];
+}
+
+// Planes 0 .. NP - 1 of a region into LDS by all NT threads: src(t) is plane
+// t's grid plane, dst(t) its place in LDS.  SK planes' loads of a wave are in
+// flight before their values are stored.
+template <int NP, int NT, int SK, class R, class Cols, class Src, class Dst>
+__device__ __forceinline__ void stage_planes(const Cols& cols, Src src, Dst dst)
+{
+    constexpr int NW = NT / 64, CH = Cols::CH;
+    for (int t0 = wave_index(); t0 < NP; t0 += NW * SK) {
+        double v[SK][CH];
+#pragma unroll
+        for (int k = 0; k < SK; ++k) {
+            const int t = t0 + k * NW;
+            if (t < NP) {
+                const double* s = src(t);
+#pragma unroll
+                for (int c = 0; c < CH; ++c)
+                    if (cols.off[c] >= 0) v[k][c] = s[cols.off[c]];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < SK; ++k) {
+            const int t = t0 + k * NW;
+            if (t < NP) {
+                R* o = dst(t);
+#pragma unroll
+                for (int c = 0; c < CH; ++c)
+                    if (cols.off[c] >= 0) o[cols.lds[c]] = (R)v[k][c];
+            }
+        }
+    }
+}
+
+// Adds the non-zero entries of planes 0 .. NP - 1 of an LDS region, src(t), to
+// the grid planes dst(t) with global atomics, by all NT threads.
+template <int NP, int NT, class Cols, class Src, class Dst>
+__device__ __forceinline__ void flush_planes(const Cols& cols, Src src, Dst dst)
+{
+    for (int t = wave_index(); t < NP; t += NT / 64) {
+        const double* s = src(t);
+        double* o = dst(t);
+#pragma unroll
+        for (int c = 0; c < Cols::CH; ++c)
+            if (cols.off[c] >= 0) {
+                const double v = s[cols.lds[c]];
+                if (v != 0.0) unsafeAtomicAdd(o + cols.off[c], v);
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Class rows of a workgroup: an order of up to NT * U particles in which any 16
+// consecutive ones are of distinct lane classes as far as the class counts
+// allow.  A particle's class is its LDS base index modulo 16 (16 lanes of
+// 8-byte values per LDS pass): the same stencil offset of 16 distinct classes
+// lies in 16 distinct banks, and without this order a pass over random cells
+// takes about three times as long.  Row r holds the rank-r particle of every
+// class that has one; ranks follow the storage order (a wave owns a contiguous
+// block and a prefix over the waves orders the blocks), so a row's particles
+// are also near each other in memory.
+// ---------------------------------------------------------------------------
+constexpr int kRowClasses = 16;
+
+template <int NT, int U>
+struct ClassRows {
+    static constexpr int W = NT * U, NW = NT / 64;
+    unsigned cnt[NW][kRowClasses];  // per wave: particles of each class; then their first rank
+    unsigned tot[kRowClasses];
+    uint16_t perm[W];               // position -> slot
+};
+
+// Orders the slots 0 .. m - 1 (m <= W): cls(slot) is the slot's class, or -1
+// to leave it out.  Returns the number of slots placed; perm is valid until
+// the next call.  Called by the whole workgroup; the caller puts a barrier
+// between the last use of perm and the next call.
+template <int NT, int U, class Cls>
+__device__ __forceinline__ int order_rows(ClassRows<NT, U>& s, int m, Cls cls)
+{
+    static_assert(ClassRows<NT, U>::W <= 65536, "16-bit slots");
+    const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
+    if (lane < kRowClasses) s.cnt[wv][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    int c[U];
+    unsigned rk[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int sl = (wv * U + u) * 64 + lane;
+        c[u] = sl < m ? cls(sl) : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (c[u] >= 0) rk[u] = atomicAdd(&s.cnt[wv][c[u]], 1u);
+    __syncthreads();
+    if (t < kRowClasses) {
+        unsigned run = 0;
+        for (int w = 0; w < NT / 64; ++w) {
+            const unsigned x = s.cnt[w][t];
+            s.cnt[w][t] = run;
+            run += x;
+        }
+        s.tot[t] = run;
+    }
+    __syncthreads();
+    unsigned tot[kRowClasses], all = 0;
+#pragma unroll
+    for (int k = 0; k < kRowClasses; ++k) {
+        tot[k] = s.tot[k];
+        all += tot[k];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (c[u] >= 0) {
+            // the rows before this one, then the smaller classes of this row
+            const unsigned r = rk[u] + s.cnt[wv][c[u]];
+            unsigned pos = 0;
+#pragma unroll
+            for (int k = 0; k < kRowClasses; ++k) pos += min(tot[k], r + (k < c[u] ? 1u : 0u));
+            s.perm[pos] = (uint16_t)((wv * U + u) * 64 + lane);
+        }
+    __syncthreads();
+    return (int)all;
+}
+
+// This workgroup's share [begin, end) of a tile's slots, one of `split` equal
+// shares in multiples of 64.
+__device__ __forceinline__ void tile_share(int part, int split, int64_t& begin, int64_t& end)
+{
+    if (split == 1) return;
+    const int64_t len = ((end - begin + split - 1) / split + 63) / 64 * 64;
+    begin += part * len;
+    end = min(begin + len, end);
+}
+
+}  // namespace
+}  // namespace pic
