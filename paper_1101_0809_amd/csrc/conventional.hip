@@ -12,9 +12,11 @@
 // gathers, pushes and moves with the fields staged (margin 1, 105 KB), keeping
 // the start position in the species' spare particle copy and the cell shifts
 // in its id array, and a second pass deposits the current (margin 2, 98 KB):
-// particles that stay in their cell first (54 contributions), the others
-// queued (144).
-#include "pic_math.h"
+// particles that stay in their cell first (54 contributions), then the
+// others (144).
+#include <type_traits>
+
+#include "tile_io.h"
 
 namespace pic {
 namespace {
@@ -108,51 +110,79 @@ __global__ __launch_bounds__(kCvNT2) void k_step_conv2(GridK g, StepArgs a, cons
     }
 }
 
-constexpr int kCvM3a = 1, kCvM3b = 2, kCvNT3 = 512;
+constexpr int kCvM3a = 1, kCvM3b = 2;
+constexpr int kCvNTa = 512, kCvUa = 4;  // pass 1: threads, slots per thread ordered at a time
+constexpr int kCvNTb = 768, kCvUb = 2;  // pass 2
+constexpr int64_t kCvFixed = 800;       // staging and flush, in particles (tile_split)
+// Current region: 16 cells per axis in rows of 17 and planes of 272 + 3 doubles,
+// so that the classes of a tile's cells (first index modulo 16) vary along
+// every axis.
+constexpr int kCvRowJ = 17, kCvPlaneJ = 16 * 17 + 3;
 
-__global__ __launch_bounds__(kCvNT3) void k_push_conv3(GridK g, StepArgs a, PartArrays spare,
+// Pass 1's word on a particle's move: bits 2 ax .. 2 ax + 1 the cell shift plus
+// one, bit 6 no shift on any axis, bit 7 the particle within the current
+// region's margin of the tile, bits 8 .. 11 the class of its window's first
+// cell there.
+constexpr int kCvStill = 64, kCvInside = 128;
+
+// Pass 1 (252 LDS reads per particle) takes the particles in class rows
+// (order_rows) of their cell, pass 2 (54 or 144 LDS atomics) in those of their
+// window: LDS bank conflicts were 36 and 18% of the CU-busy cycles in storage
+// order.  82 and 58 -> 71 and 49 us at 64^3 x 2 per cell; 20 steps of 64^3 x 6
+// per cell with the energies 6.25 -> 5.5 ms, hot (w_th = 0.2) 13.3 -> 10.0 ms.
+__global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, PartArrays spare,
                                                      const double* __restrict__ fields,
-                                                     const double* __restrict__ bfield)
+                                                     const double* __restrict__ bfield, int split)
 {
-    constexpr int T = kTile3, M = kCvM3a, NT = kCvNT3;
+    constexpr int T = kTile3, M = kCvM3a, NT = kCvNTa;
     constexpr int LF = T + 3 + 2 * M, NF = LF * LF * LF;  // cells T0-1-M .. T0+T+1+M
+    constexpr int MB = kCvM3b;
     __shared__ double sf[6 * NF];
+    __shared__ ClassRows<NT, kCvUa> rows;
     __shared__ unsigned int n_fallback;
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
+    const int tile = unit / split;
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T, (tile / (g.nt[0] * g.nt[1])) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    for (int e = threadIdx.x; e < 6 * NF; e += NT) {
-        const int comp = e / NF, r = e - comp * NF;
-        const int gx = wrapi(T0[0] - 1 - M + r % LF, nx);
-        const int gy = wrapi(T0[1] - 1 - M + (r / LF) % LF, ny);
-        const int gz = wrapi(T0[2] - 1 - M + r / (LF * LF), nz);
-        const int64_t cell = ((int64_t)gz * ny + gy) * nx + gx;
-        sf[e] = comp < 3 ? fields[comp * N + cell] : bfield[(comp - 3) * N + cell];
+    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    tile_share(unit - tile * split, split, begin, end);
+    if (begin >= end) return;
+    {
+        const bool small = nx < LF || ny < LF || nz < LF;
+        const Columns<LF, LF, LF> cols(g, T0[0] - 1 - M, T0[1] - 1 - M, small);
+        stage_planes<6 * LF, NT, 2, double>(
+            cols,
+            [&](int t) {
+                const int comp = t / LF;
+                return (comp < 3 ? fields + comp * N : bfield + (comp - 3) * N) +
+                       plane_offset(g, T0[2] - 1 - M + t - comp * LF, small);
+            },
+            [&](int t) { return sf + t * (LF * LF); });
     }
     if (threadIdx.x == 0) n_fallback = 0;
-    __syncthreads();
     const double c2 = g.c * g.c;
     const double qmdt2 = 0.5 * a.qm * g.dt;
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    unsigned int my_fallback = 0;
-    for (int64_t p = begin + threadIdx.x; p < end; p += NT) {
-        int i0[3];
-        double d0[3];
-        PosIO<double, 3>::load(a, p, i0, d0);
-        double w[3];
-        for (int ax = 0; ax < 3; ++ax) w[ax] = ((const double*)a.mom[ax])[p];
-        AxisC<double> ax0[3];
-        for (int ax = 0; ax < 3; ++ax) ax0[ax] = form_factor_conv<double>(d0[ax]);
-        int rel[3];
+
+    auto place = [&](const int i0[3], int rel[3]) -> bool {  // true inside the field region
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
             rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
-        my_fallback += inside ? 0 : 1;
+        return inside;
+    };
+    auto advance = [&](int64_t p, auto on_tile) {
+        constexpr bool kTileFields = decltype(on_tile)::value;
+        int i0[3], rel[3];
+        double d0[3], w[3];
+        PosIO<double, 3>::load(a, p, i0, d0);
+        for (int ax = 0; ax < 3; ++ax) w[ax] = ((const double*)a.mom[ax])[p];
+        AxisC<double> ax0[3];
+        for (int ax = 0; ax < 3; ++ax) ax0[ax] = form_factor_conv<double>(d0[ax]);
+        place(i0, rel);
         double E[3], B[3];
-        if (inside) {
+        if (kTileFields) {
             const int fb = (rel[0] + 1 + M) + (rel[1] + 1 + M) * LF + (rel[2] + 1 + M) * LF * LF;
             auto F = [&](int comp, int oa, int ob, int oc) -> double {
                 return sf[comp * NF + fb + oa + ob * LF + oc * LF * LF];
@@ -174,92 +204,145 @@ __global__ __launch_bounds__(kCvNT3) void k_push_conv3(GridK g, StepArgs a, Part
         for (int ax = 0; ax < 3; ++ax) disp[ax] = w[ax] * inv * g.cfl[ax];
         int delta[3] = {0, 0, 0};
         PosIO<double, 3>::move(a, p, g, i0, d0, disp, d1, delta, true);
-        for (int ax = 0; ax < 3; ++ax) ((double*)spare.pos[ax])[p] = (double)i0[ax] + d0[ax];
-        spare.id[p] = (int64_t)((delta[0] + 1) | ((delta[1] + 1) << 2) | ((delta[2] + 1) << 4));
+        int word = kCvStill | kCvInside, jb = 0;
+        constexpr int stride[3] = {1, kCvRowJ, kCvPlaneJ};
+        for (int ax = 0; ax < 3; ++ax) {
+            ((double*)spare.pos[ax])[p] = (double)i0[ax] + d0[ax];
+            word |= (delta[ax] + 1) << (2 * ax);
+            if (delta[ax] != 0) word &= ~kCvStill;
+            if (rel[ax] < -MB || rel[ax] > T - 1 + MB) word &= ~kCvInside;
+            jb += (rel[ax] + (delta[ax] < 0 ? -1 : 0) + 1 + MB) * stride[ax];
+        }
+        spare.id[p] = (int64_t)(word | (jb & (kRowClasses - 1)) << 8);
+    };
+
+    uint32_t* out = (uint32_t*)spare.weight + 2 * begin;  // particles off the field region (4 bytes of 8 used)
+    for (int64_t cb = begin; cb < end; cb += ClassRows<NT, kCvUa>::W) {
+        __syncthreads();  // the fields are staged; the last chunk's order is used up
+        const int m = (int)min(end - cb, (int64_t)ClassRows<NT, kCvUa>::W);
+        const int nin = order_rows(rows, m, [&](int sl) -> int {
+            int i0[3], rel[3];
+            double d0[3];
+            PosIO<double, 3>::load(a, cb + sl, i0, d0);
+            if (!place(i0, rel)) {
+                out[atomicAdd(&n_fallback, 1u)] = (uint32_t)(cb - begin + sl);
+                return -1;
+            }
+            return (rel[0] + M + (rel[1] + M) * LF + (rel[2] + M) * LF * LF) & (kRowClasses - 1);
+        });
+        for (int q = threadIdx.x; q < nin; q += NT) advance(cb + rows.perm[q], std::true_type{});
     }
-    if (my_fallback) atomicAdd(&n_fallback, my_fallback);
     __syncthreads();
+    for (unsigned q = threadIdx.x; q < n_fallback; q += NT) advance(begin + out[q], std::false_type{});
     if (threadIdx.x == 0 && a.counters) {
         atomicAdd(&a.counters[1], (unsigned long long)n_fallback);
         atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
     }
 }
 
-__global__ __launch_bounds__(kCvNT3) void k_deposit_conv3(GridK g, StepArgs a, PartArrays spare,
-                                                        double* __restrict__ Jg)
+// Pass 2: the particles that stay in their cell, then those that cross within
+// the region, then those outside it (a wave runs one form at a time).
+__global__ __launch_bounds__(kCvNTb) void k_deposit_conv3(GridK g, StepArgs a, PartArrays spare,
+                                                        double* __restrict__ Jg, int split)
 {
-    constexpr int T = kTile3, M = kCvM3b, NT = kCvNT3;
-    constexpr int LJ = T + 4 + 2 * M, NJ = LJ * LJ * LJ;  // cells T0-2-M .. T0+T+1+M
+    constexpr int T = kTile3, M = kCvM3b, NT = kCvNTb;
+    constexpr int LJ = T + 4 + 2 * M;  // cells T0-2-M .. T0+T+1+M
+    constexpr int ROW = kCvRowJ, PLANE = kCvPlaneJ, NJ = LJ * PLANE;
     __shared__ double sj[3 * NJ];
-    __shared__ unsigned int qn;
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    __shared__ ClassRows<NT, kCvUb> rows;
+    __shared__ unsigned int n_cross, n_out;
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
+    const int tile = unit / split;
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T, (tile / (g.nt[0] * g.nt[1])) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    tile_share(unit - tile * split, split, begin, end);
+    if (begin >= end) return;
     for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj[e] = 0.0;
-    if (threadIdx.x == 0) qn = 0;
-    __syncthreads();
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    int64_t* queue = (int64_t*)spare.weight + begin;  // end - begin entries
-    auto deposit = [&](int64_t p, bool first) {
+    if (threadIdx.x == 0) n_cross = n_out = 0;
+    auto deposit = [&](int64_t p, auto form) {  // 0: still, 1: crossing, 2: outside
+        constexpr int kForm = decltype(form)::value;
         const int64_t code = spare.id[p];
         int i0[3], rel[3], s[3];
-        bool inside = true, still = true;
         double dm[3][4], dp[3][4], s0[3][3], s1[3][3];
+#pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             const double x0 = ((const double*)spare.pos[ax])[p];
             const double x1 = ((const double*)a.pos[ax])[p];
             const double f0 = floor(x0);
             i0[ax] = (int)f0;
-            const int delta = (int)((code >> (2 * ax)) & 3) - 1;
-            still = still && delta == 0;
+            const int delta = kForm == 0 ? 0 : (int)((code >> (2 * ax)) & 3) - 1;
             cell_weights<double>(x0 - f0, s0[ax]);
             cell_weights<double>(x1 - floor(x1), s1[ax]);
-            window<double>(s0[ax], s1[ax], delta, dm[ax], dp[ax]);
+            if (kForm != 0) {
+                // in registers first: a select between neighbouring weights
+                // would become a load at a run-time index from scratch memory
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    asm("" : "+v"(s0[ax][k]));
+                    asm("" : "+v"(s1[ax][k]));
+                }
+                window<double>(s0[ax], s1[ax], delta, dm[ax], dp[ax]);
+            }
             s[ax] = (delta < 0 ? -1 : 0) - 1;
             rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
-            inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
-        }
-        if (first && !(still && inside)) {
-            queue[atomicAdd(&qn, 1u)] = p;
-            return;
         }
         const double qp = a.q * ((const double*)a.weight)[p];
         double jfac[3];
         for (int ax = 0; ax < 3; ++ax) jfac[ax] = g.jscale[ax] * qp;
-        if (inside) {
-            const int jb = (rel[0] + s[0] + 2 + M) + (rel[1] + s[1] + 2 + M) * LJ + (rel[2] + s[2] + 2 + M) * LJ * LJ;
+        if (kForm < 2) {
+            const int jb = (rel[0] + s[0] + 2 + M) + (rel[1] + s[1] + 2 + M) * ROW + (rel[2] + s[2] + 2 + M) * PLANE;
             auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                atomicAdd(&sj[comp * NJ + jb + ix + iy * LJ + iz * LJ * LJ], v);
+                atomicAdd(&sj[comp * NJ + jb + ix + iy * ROW + iz * PLANE], v);
             };
-            if (first) {
-                deposit3_still<double>(s0, s1, jfac, S);
-            } else {
-                deposit3<double>(dm, dp, jfac, S);
-            }
+            if (kForm == 0) deposit3_still<double>(s0, s1, jfac, S);
+            else deposit3<double>(dm, dp, jfac, S);
         } else {
+            int xi[4], yj[4];
+            int64_t zk[4];
+#pragma unroll
+            for (int o = 0; o < 4; ++o) {
+                xi[o] = wrapi(i0[0] + s[0] + o, nx);
+                yj[o] = wrapi(i0[1] + s[1] + o, ny) * nx;
+                zk[o] = (int64_t)wrapi(i0[2] + s[2] + o, nz) * ny * nx;
+            }
             auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                const int64_t cell = ((int64_t)wrapi(i0[2] + s[2] + iz, nz) * ny + wrapi(i0[1] + s[1] + iy, ny)) * nx +
-                                     wrapi(i0[0] + s[0] + ix, nx);
-                add_global(&Jg[comp * N + cell], v);
+                add_global(&Jg[comp * N + zk[iz] + yj[iy] + xi[ix]], v);
             };
             deposit3<double>(dm, dp, jfac, S);
         }
     };
-    for (int64_t p = begin + threadIdx.x; p < end; p += NT) deposit(p, true);
-    __syncthreads();
-    const int64_t nq = qn;
-    for (int64_t k = threadIdx.x; k < nq; k += NT) deposit(queue[k], false);
-    __syncthreads();
-    for (int e = threadIdx.x; e < 3 * NJ; e += NT) {
-        const double v = sj[e];
-        if (v == 0.0) continue;
-        const int comp = e / NJ, r = e - comp * NJ;
-        const int gx = wrapi(T0[0] - 2 - M + r % LJ, nx);
-        const int gy = wrapi(T0[1] - 2 - M + (r / LJ) % LJ, ny);
-        const int gz = wrapi(T0[2] - 2 - M + r / (LJ * LJ), nz);
-        add_global(&Jg[comp * N + ((int64_t)gz * ny + gy) * nx + gx], v);
-    }
+    auto in_rows = [&](auto form) {
+        constexpr int want = decltype(form)::value == 0 ? kCvStill | kCvInside : kCvInside;
+        for (int64_t cb = begin; cb < end; cb += ClassRows<NT, kCvUb>::W) {
+            __syncthreads();  // the region is clear; the last chunk's order is used up
+            const int m = (int)min(end - cb, (int64_t)ClassRows<NT, kCvUb>::W);
+            const int n = order_rows(rows, m, [&](int sl) -> int {
+                const int word = (int)spare.id[cb + sl];
+                if (want & kCvStill) {
+                    if (!(word & kCvInside)) n_out = 1;
+                    else if (!(word & kCvStill)) n_cross = 1;
+                }
+                return (word & (kCvStill | kCvInside)) == want ? (word >> 8) & (kRowClasses - 1) : -1;
+            });
+            for (int q = threadIdx.x; q < n; q += NT) deposit(cb + rows.perm[q], form);
+        }
+        __syncthreads();
+    };
+    in_rows(std::integral_constant<int, 0>{});
+    if (n_cross) in_rows(std::integral_constant<int, 1>{});
+    if (n_out)
+        for (int64_t p = begin + threadIdx.x; p < end; p += NT)
+            if (!((int)spare.id[p] & kCvInside)) deposit(p, std::integral_constant<int, 2>{});
+    const bool small = nx < LJ || ny < LJ || nz < LJ;
+    const Columns<LJ, LJ, ROW> cols(g, T0[0] - 2 - M, T0[1] - 2 - M, small);
+    flush_planes<3 * LJ, NT>(
+        cols, [&](int t) { return sj + t * PLANE; },
+        [&](int t) {
+            const int comp = t / LJ;
+            return Jg + comp * N + plane_offset(g, T0[2] - 2 - M + t - comp * LJ, small);
+        });
 }
 
 }  // namespace
@@ -279,8 +362,10 @@ hipError_t launch_particle_step_conv(Ctx& c, Species& sp, hipStream_t s)
     a.counters = c.counters;
     double* J = c.fields + 6 * c.k.ncell;
     if (c.k.dims == 3) {
-        hipLaunchKernelGGL(k_push_conv3, dim3(c.k.ntiles), dim3(kCvNT3), 0, s, c.k, a, sp.alt, c.fields, c.bn);
-        hipLaunchKernelGGL(k_deposit_conv3, dim3(c.k.ntiles), dim3(kCvNT3), 0, s, c.k, a, sp.alt, J);
+        const int split = tile_split(c.k.ntiles, sp.n, kCvFixed);
+        const dim3 grid((unsigned)(c.k.ntiles * split));
+        hipLaunchKernelGGL(k_push_conv3, grid, dim3(kCvNTa), 0, s, c.k, a, sp.alt, c.fields, c.bn, split);
+        hipLaunchKernelGGL(k_deposit_conv3, grid, dim3(kCvNTb), 0, s, c.k, a, sp.alt, J, split);
     } else {
         hipLaunchKernelGGL(k_step_conv2, dim3(c.k.ntiles), dim3(kCvNT2), 0, s, c.k, a, c.fields, c.bn, J);
     }

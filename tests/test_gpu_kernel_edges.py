@@ -99,3 +99,22 @@ def test_poisson_cells_per_thread(n):
     rho = oracle.State(g, [oracle.Species(x, w, weight, q=-1.0, m=1.0)]).rho()
     E = poisson.e_of_phi(g, poisson.solve(g, rho))
     assert np.linalg.norm(sim.fields_numpy()[:3] - E) <= 1e-9 * np.linalg.norm(E)
+
+
+@pytest.mark.parametrize("scheme", ["order2", "conventional"])
+@pytest.mark.parametrize("n,ppc,w_th,sort_every", [
+    ((8, 8, 8), 9, 0.05, 3),      # one tile, more particles than one ordered chunk
+    ((9, 8, 17), 1, 0.1, 2),      # shares of a few particles and none
+    ((13, 14, 17), 6, 0.5, 0),    # unsorted and hot: off the fields' region and off the current's
+    ((24, 8, 9), 20, 0.2, 4)])
+def test_two_pass_steps_in_class_rows(scheme, n, ppc, w_th, sort_every):
+    """The two-pass 3D steps (order 2 1/2, conventional): class rows over
+    several chunks and shares of a tile, particles that stay, cross, and leave
+    either LDS region."""
+    import test_gpu_conventional
+    import test_gpu_order2
+    mod = test_gpu_order2 if scheme == "order2" else test_gpu_conventional
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=n[0], ny=n[1], nz=n[2], ppc=ppc, w_th=(w_th,) * 3,
+                                                  sort_every=sort_every)
+    sim, st = mod._run_pair(wl, 9)
+    mod._compare(sim, st, wl)
