@@ -21,7 +21,7 @@
 // contributions); the LDS current tile is FP64 in both.
 #include <algorithm>
 
-#include "pic_math.h"
+#include "tile_io.h"
 
 namespace pic {
 namespace {
@@ -50,186 +50,274 @@ __device__ __forceinline__ void global_add(double* p, double v)
 
 // ---------------------------------------------------------------------------
 // The 2D3V particle-step kernel (tile T^2, margin M); `split` workgroups share
-// a tile's particles, each with its own LDS field and current tiles; every
-// particle deposits its window at once.  One workgroup of four waves per tile
-// leaves a CU of a 256^2 grid with one wave per SIMD and most CUs of a small
-// grid idle.  Sharing the tiles (grid2), taking the fields' loads in one batch
-// and loading the next particle ahead took a step of 32^2 cells x 4 per cell
-// from 33.3 to 19.4 us and 20 steps of 256^2 x 16 from 1456 to 1389 us (FP64);
-// the large grid is then bound by the LDS (70% of its cycles active, a third
-// of them bank conflicts).
+// a tile's particles, each with its own LDS field and current tiles.  One
+// workgroup of four waves per tile would leave a CU of a 256^2 grid with one
+// wave per SIMD and most CUs of a small grid idle.
+//
+// With ROWS it takes its particles in class rows and the crossing ones apart: a
+// pass over storage order is bound by the LDS, a third of whose cycles are
+// bank conflicts once the particles have drifted, and a particle that stays
+// in its cell has 21 of the 40 contributions.  20 steps of 256^2 x 16 per cell:
+// 1456 us at one workgroup per tile, 1389 shared, 1126 like this (FP64).
+// Without, for shares of at most one particle per thread: one pass, and none
+// of the order's barriers (32^2 x 4 per cell: 19.1 us per step against 22.1).
 // ---------------------------------------------------------------------------
-template <class R, int T, int M, int NT>
-__global__ __launch_bounds__(NT) void k_particle_step2(GridK g, StepArgs a, const double* __restrict__ fields,
+template <class R, int T, int M, int NT, int U, bool ROWS>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2))) void k_particle_step2(GridK g, StepArgs a, const double* __restrict__ fields,
                                                       const double* __restrict__ bfield, double* __restrict__ Jg,
                                                       int split)
 {
     constexpr int LF = T + 2 + 2 * M;  // field region: cells T0-1-M .. T0+T+M
     constexpr int LJ = T + 4 + 2 * M;  // current region: T0-2-M .. T0+T+1+M
-    constexpr int NF = LF * LF, NJ = LJ * LJ;
+    constexpr int ROW = LJ;            // rows of both regions: a cell's two base indices share their residue
+    constexpr int NF = LF * ROW, NJ = LJ * ROW;
+    constexpr int C = lane_classes<R>();
     __shared__ R sf[6 * NF];
     __shared__ LdsJ<R, 3 * NJ> sj;
-    __shared__ unsigned int n_fallback;
+    __shared__ ClassRows<NT, U, C> rows;
+    __shared__ unsigned int n_out, n_cross;
+    using Rows = ClassRows<NT, U, C>;
 
     const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
-    const int tile = unit / split, part = unit - tile * split;
+    const int tile = unit / split;
     const int T0[2] = {(tile % g.nt[0]) * T, (tile / g.nt[0]) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1];
-    const int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    if (begin + part * NT >= end) {  // no particle for this workgroup (all of it)
-        if (part == 0 && threadIdx.x == 0 && a.counters) atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
-        return;
-    }
+    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
+    tile_share(unit - tile * split, split, begin, end);
+    if (begin >= end) return;  // no particle for this workgroup (all of it)
 
     // every region index lies in [-n, 2n) unless an axis is shorter than the
     // current region; then the general modulo is used
     const bool small = nx < LJ || ny < LJ;
     auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
 
-    // the first particle's state loads while the fields are staged
-    struct State {
-        int i0[3];
-        R d0[3], w[3], qp;
-    };
-    auto load = [&](int64_t p, State& st) {
-        PosIO<R, 2>::load(a, p, st.i0, st.d0);
-        for (int ax = 0; ax < 3; ++ax) st.w[ax] = ((const R*)a.mom[ax])[p];
-        st.qp = (R)a.q * ((const R*)a.weight)[p];
-    };
-    int64_t p = begin + part * NT + threadIdx.x;
-    State st{};
-    if (p < end) load(p, st);
-
     // 1. stage E^n, B^n (+ guard cells) into LDS; B^n is in bfield.  A thread
     //    takes whole cells: the wrap is computed once for the six components
     //    and their loads are all in flight together.
-    constexpr int SC = (NF + NT - 1) / NT;
-    double v[SC][6];
+    {
+        constexpr int SC = (LF * LF + NT - 1) / NT;
+        double v[SC][6];
 #pragma unroll
-    for (int u = 0; u < SC; ++u) {
-        const int e = (int)threadIdx.x + u * NT;
-        if (e < NF) {
-            const int64_t c = (int64_t)wr(T0[1] - 1 - M + e / LF, ny) * nx + wr(T0[0] - 1 - M + e % LF, nx);
+        for (int u = 0; u < SC; ++u) {
+            const int e = (int)threadIdx.x + u * NT;
+            if (e < LF * LF) {
+                const int64_t c = (int64_t)wr(T0[1] - 1 - M + e / LF, ny) * nx + wr(T0[0] - 1 - M + e % LF, nx);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                v[u][k] = fields[k * N + c];
-                v[u][3 + k] = bfield[k * N + c];
+                for (int k = 0; k < 3; ++k) {
+                    v[u][k] = fields[k * N + c];
+                    v[u][3 + k] = bfield[k * N + c];
+                }
             }
         }
-    }
-    // 2. clear the LDS current tile
-    for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
-    if (threadIdx.x == 0) n_fallback = 0;
+        // 2. clear the LDS current tile
+        for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
+        if (threadIdx.x == 0) n_out = n_cross = 0;
 #pragma unroll
-    for (int u = 0; u < SC; ++u) {
-        const int e = (int)threadIdx.x + u * NT;
-        if (e < NF)
+        for (int u = 0; u < SC; ++u) {
+            const int e = (int)threadIdx.x + u * NT;
+            if (e < LF * LF)
 #pragma unroll
-            for (int k = 0; k < 6; ++k) sf[k * NF + e] = (R)v[u][k];
+                for (int k = 0; k < 6; ++k) sf[k * NF + e / LF * ROW + e % LF] = (R)v[u][k];
+        }
     }
-    __syncthreads();
 
     const R c = (R)g.c;
     const R c2 = c * c;
     const R qmdt2 = (R)(0.5 * a.qm * g.dt);
-    const R cfl[3] = {(R)g.cfl[0], (R)g.cfl[1], (R)g.cfl[2]};
-    const R bext[3] = {(R)g.bext[0], (R)g.bext[1], (R)g.bext[2]};
-    unsigned int my_fallback = 0;
 
-    // 3. particles
-    for (; p < end; p += (int64_t)split * NT) {
-        const State now = st;
-        if (p + (int64_t)split * NT < end) load(p + (int64_t)split * NT, st);
-        const int(&i0)[3] = now.i0;
-        const R(&d0)[3] = now.d0;
-        const R qp = now.qp;
-        R w[3] = {now.w[0], now.w[1], now.w[2]};
-
-        Axis<R> ax0[3];
-        for (int ax = 0; ax < 2; ++ax) ax0[ax] = form_factor<R>(d0[ax]);
-        ax0[2] = form_factor<R>(R(0));
-
-        // position relative to the tile
-        int rel[2];
+    // Cell relative to the tile; true within its margins.
+    auto place = [&](const int i0[3], int rel[2]) -> bool {
         bool inside = true;
         for (int ax = 0; ax < 2; ++ax) {
-            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
-            rel[ax] = r;
-            inside = inside && (r >= -M) && (r <= T - 1 + M);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
-
+        return inside;
+    };
+    // Gather (F), push and move of particle p; returns its start weights, end
+    // offsets, cell shift, macro charge and J^z factor.
+    struct Move {
+        int i0[3], delta[3];
+        R d0[3], d1[3], qp, jz;
+        Axis<R> ax0[3];
+    };
+    auto advance = [&](int64_t p, Move& mv, auto field_at) {
+        R w[3];
+        PosIO<R, 2>::load(a, p, mv.i0, mv.d0);
+        for (int ax = 0; ax < 3; ++ax) w[ax] = ((const R*)a.mom[ax])[p];
+        mv.qp = (R)a.q * ((const R*)a.weight)[p];
+        for (int ax = 0; ax < 2; ++ax) mv.ax0[ax] = form_factor<R>(mv.d0[ax]);
+        mv.ax0[2] = form_factor<R>(R(0));
         R E[3], B[3];
-        if (inside) {
-            const int base = (rel[0] + 1 + M) + (rel[1] + 1 + M) * LF;
-            auto F = [&](int comp, int da, int db, int) -> R { return sf[comp * NF + base + da + db * LF]; };
-            gather2<R>(ax0, F, E, B);
-        } else {
-            ++my_fallback;
+        gather2<R>(mv.ax0, field_at(mv.i0), E, B);
+        for (int ax = 0; ax < 3; ++ax) B[ax] += (R)g.bext[ax];
+        push<R>(qmdt2, c2, E, B, w);
+        for (int ax = 0; ax < 3; ++ax) ((R*)a.mom[ax])[p] = w[ax];
+        const R inv = over_sqrt<R>(R(1), w[0] * w[0] + w[1] * w[1] + w[2] * w[2] + c2);
+        R disp[3];
+        for (int ax = 0; ax < 3; ++ax) disp[ax] = w[ax] * inv * (R)g.cfl[ax];
+        for (int ax = 0; ax < 3; ++ax) mv.delta[ax] = 0;
+        PosIO<R, 2>::move(a, p, g, mv.i0, mv.d0, disp, mv.d1, mv.delta, true);
+        mv.jz = mv.qp * (R)(0.25 * g.inv_vol) * c * w[2] * inv;
+    };
+    auto windows = [&](const R d0[2], const R d1[2], const int delta[2], R (&dm)[3][4], R (&dp)[3][4]) {
+        for (int ax = 0; ax < 2; ++ax) {
+            R s0[3], s1[3];
+            cell_weights<R>(d0[ax], s0);
+            cell_weights<R>(d1[ax], s1);
+            window<R>(s0, s1, delta[ax], dm[ax], dp[ax]);
+        }
+    };
+
+    // a particle's cell from the tile's LDS fields
+    int rel[2];
+    auto on_tile = [&](const int i0[3]) {
+        place(i0, rel);
+        const int base = (rel[0] + 1 + M) + (rel[1] + 1 + M) * ROW;
+        return [base](int comp, int da, int db, int) -> R { return sf[comp * NF + base + da + db * ROW]; };
+    };
+    uint32_t* out = (uint32_t*)a.mlist + begin;  // particles outside the margins
+    auto inside = [&](int sl) -> bool {
+        int ci[3];
+        PosIO<R, 2>::cell(a, begin + sl, ci);
+        if (place(ci, rel)) return true;
+        out[atomicAdd(&n_out, 1u)] = (uint32_t)sl;
+        return false;
+    };
+
+    if constexpr (!ROWS) {
+        // 3. in storage order, every window at once
+        __syncthreads();  // the fields are staged
+        for (int sl = threadIdx.x; sl < (int)(end - begin); sl += NT) {
+            if (!inside(sl)) continue;
+            Move mv;
+            advance(begin + sl, mv, on_tile);
+            R jfac[3], dm[3][4], dp[3][4];
+            for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * mv.qp;
+            windows(mv.d0, mv.d1, mv.delta, dm, dp);
+            const int jb = (rel[0] + (mv.delta[0] < 0 ? -1 : 0) + 1 + M) + (rel[1] + (mv.delta[1] < 0 ? -1 : 0) + 1 + M) * ROW;
+            deposit2<R>(dm, dp, jfac, mv.jz,
+                        [&](int comp, int ix, int iy, int, double x) { sj.add(comp * NJ + jb + ix + iy * ROW, x); });
+        }
+        __syncthreads();
+    } else {
+        // 3. the particles within the margins, in class rows of their cell:
+        //    those that stay in their cell deposit their 21 contributions at
+        //    once, the others are queued (start offsets, J^z factor, and a
+        //    word: slot, cell offset, shifts) in the spare copy
+        for (int cb = 0; cb < (int)(end - begin); cb += Rows::W) {
+            __syncthreads();  // the fields are staged; the last chunk's order is used up
+            const int m = min((int)(end - begin) - cb, Rows::W);
+            const int nin = order_rows(rows, m, [&](int sl) -> int {
+                return inside(cb + sl) ? (rel[0] + M + (rel[1] + M) * ROW) & (C - 1) : -1;
+            });
+            for (int q = threadIdx.x; q < nin; q += NT) {
+                const int64_t p = begin + cb + rows.perm[q];
+                Move mv;
+                advance(p, mv, on_tile);
+                if ((mv.delta[0] | mv.delta[1]) == 0) {
+                    R jfac[3];
+                    for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * mv.qp;
+                    R s0[2][3], s1[2][3];
+                    for (int ax = 0; ax < 2; ++ax) {
+                        cell_weights<R>(mv.d1[ax], s1[ax]);
+                        for (int k = 0; k < 3; ++k) s0[ax][k] = mv.ax0[ax].s[k];
+                    }
+                    const int jb = (rel[0] + 1 + M) + (rel[1] + 1 + M) * ROW;
+                    deposit2_still<R>(s0, s1, jfac, mv.jz, [&](int comp, int ix, int iy, int, double x) {
+                        sj.add(comp * NJ + jb + ix + iy * ROW, x);
+                    });
+                } else {
+                    const int64_t e = begin + atomicAdd(&n_cross, 1u);
+                    for (int ax = 0; ax < 2; ++ax) ((R*)a.qd0[ax])[e] = mv.d0[ax];
+                    ((R*)a.qd0[2])[e] = mv.jz;
+                    a.qword[e] = (p - begin) | (int64_t)(rel[0] + M) << 32 | (int64_t)(rel[1] + M) << 40 |
+                                 (int64_t)(mv.delta[0] + 1) << 48 | (int64_t)(mv.delta[1] + 1) << 50;
+                }
+            }
+        }
+        __syncthreads();
+
+        // 4. the crossing particles, in class rows of their window's first cell
+        const int nc = (int)n_cross;
+        for (int qb = 0; qb < nc; qb += Rows::W) {
+            auto unpack = [](int64_t word, int s[2], int delta[2]) {
+                for (int ax = 0; ax < 2; ++ax) {
+                    delta[ax] = (int)((word >> (48 + 2 * ax)) & 3) - 1;
+                    // window start in the current region
+                    s[ax] = (int)((word >> (32 + 8 * ax)) & 255) + (delta[ax] < 0 ? -1 : 0) + 1;
+                }
+            };
+            const int n = order_rows(rows, min(nc - qb, Rows::W), [&](int sl) -> int {
+                int s[2], delta[2];
+                unpack(a.qword[begin + qb + sl], s, delta);
+                return (s[0] + s[1] * ROW) & (C - 1);
+            });
+            for (int q = threadIdx.x; q < n; q += NT) {
+                const int64_t e = begin + qb + rows.perm[q];
+                const int64_t word = a.qword[e], p = begin + (word & 0xffffffffll);
+                int s[2], delta[2];
+                unpack(word, s, delta);
+                R d0[2], d1[2], jfac[3], dm[3][4], dp[3][4];
+                const R qp = (R)a.q * ((const R*)a.weight)[p];
+                for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
+                for (int ax = 0; ax < 2; ++ax) {
+                    d0[ax] = ((const R*)a.qd0[ax])[e];
+                    if (sizeof(R) == 8) {  // the stored end position, as in PosIO::move
+                        const double x = ((const double*)a.pos[ax])[p];
+                        d1[ax] = (R)(x - floor(x));
+                    } else {
+                        d1[ax] = ((const R*)a.pos[ax])[p];
+                    }
+                }
+                windows(d0, d1, delta, dm, dp);
+                const int jb = s[0] + s[1] * ROW;
+                deposit2<R>(dm, dp, jfac, ((const R*)a.qd0[2])[e],
+                            [&](int comp, int ix, int iy, int, double x) { sj.add(comp * NJ + jb + ix + iy * ROW, x); });
+            }
+            __syncthreads();
+        }
+    }
+
+    // 5. the particles outside the margins: global memory
+    for (int q = threadIdx.x; q < (int)n_out; q += NT) {
+        Move mv;
+        advance(begin + out[q], mv, [&](const int i0[3]) {
             int xi[3], yj[3];
             for (int o = 0; o < 3; ++o) {
                 xi[o] = wrapi(i0[0] + o - 1, nx);
                 yj[o] = wrapi(i0[1] + o - 1, ny) * nx;
             }
-            auto F = [&](int comp, int da, int db, int) -> R {
+            return [=](int comp, int da, int db, int) -> R {
                 return (R)(comp < 3 ? fields + comp * N : bfield + (comp - 3) * N)[yj[db + 1] + xi[da + 1]];
             };
-            gather2<R>(ax0, F, E, B);
+        });
+        R jfac[3], dm[3][4], dp[3][4];
+        for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * mv.qp;
+        windows(mv.d0, mv.d1, mv.delta, dm, dp);
+        int xi[4], yj[4];
+        for (int o = 0; o < 4; ++o) {
+            xi[o] = wrapi(mv.i0[0] + (mv.delta[0] < 0 ? -1 : 0) - 1 + o, nx);
+            yj[o] = wrapi(mv.i0[1] + (mv.delta[1] < 0 ? -1 : 0) - 1 + o, ny) * nx;
         }
-        for (int ax = 0; ax < 3; ++ax) B[ax] += bext[ax];
-
-        push<R>(qmdt2, c2, E, B, w);
-        for (int ax = 0; ax < 3; ++ax) ((R*)a.mom[ax])[p] = w[ax];
-
-        const R inv = over_sqrt<R>(R(1), w[0] * w[0] + w[1] * w[1] + w[2] * w[2] + c2);
-        R disp[3];
-        for (int ax = 0; ax < 3; ++ax) disp[ax] = w[ax] * inv * cfl[ax];
-        R d1[3];
-        int delta[3] = {0, 0, 0};
-        PosIO<R, 2>::move(a, p, g, i0, d0, disp, d1, delta, true);
-
-        // deposit
-        R jfac[3];
-        for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
-        R dm[3][4], dp[3][4];
-        for (int ax = 0; ax < 2; ++ax) {
-            R s1[3];
-            cell_weights<R>(d1[ax], s1);
-            window<R>(ax0[ax].s, s1, delta[ax], dm[ax], dp[ax]);
-        }
-        const R jz2 = qp * (R)(0.25 * g.inv_vol) * c * w[2] * inv;
-        int s[2];
-        for (int ax = 0; ax < 2; ++ax) s[ax] = rel[ax] + (delta[ax] < 0 ? -1 : 0) - 1;
-
-        if (inside) {
-            const int jb = (s[0] + 2 + M) + (s[1] + 2 + M) * LJ;
-            auto S = [&](int comp, int ix, int iy, int, double x) { sj.add(comp * NJ + jb + ix + iy * LJ, x); };
-            deposit2<R>(dm, dp, jfac, jz2, S);
-        } else {
-            int xi[4], yj[4];
-            for (int o = 0; o < 4; ++o) {
-                xi[o] = wrapi(T0[0] + s[0] + o, nx);
-                yj[o] = wrapi(T0[1] + s[1] + o, ny) * nx;
-            }
-            auto S = [&](int comp, int ix, int iy, int, double x) { global_add(&Jg[comp * N + yj[iy] + xi[ix]], x); };
-            deposit2<R>(dm, dp, jfac, jz2, S);
-        }
+        deposit2<R>(dm, dp, jfac, mv.jz,
+                    [&](int comp, int ix, int iy, int, double x) { global_add(&Jg[comp * N + yj[iy] + xi[ix]], x); });
     }
-    if (my_fallback) atomicAdd(&n_fallback, my_fallback);
-    __syncthreads();
 
-    // 4. flush the LDS current tile
-    for (int e = threadIdx.x; e < 3 * NJ; e += NT) {
-        const double x = sj.get(e);
+    // 6. flush the LDS current tile
+    for (int e = threadIdx.x; e < 3 * LJ * LJ; e += NT) {
+        const int comp = e / (LJ * LJ);
+        const int r = e - comp * (LJ * LJ);
+        const int ly = r / LJ, lx = r - ly * LJ;
+        const double x = sj.get(comp * NJ + ly * ROW + lx);
         if (x == 0.0) continue;
-        const int comp = e / NJ;
-        const int r = e - comp * NJ;
-        const int gx = wr(T0[0] - 2 - M + r % LJ, nx), gy = wr(T0[1] - 2 - M + r / LJ, ny);
+        const int gx = wr(T0[0] - 2 - M + lx, nx), gy = wr(T0[1] - 2 - M + ly, ny);
         global_add(&Jg[comp * N + (int64_t)gy * nx + gx], x);
     }
     if (threadIdx.x == 0 && a.counters) {
-        if (n_fallback) atomicAdd(&a.counters[1], (unsigned long long)n_fallback);
-        if (part == 0) atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
+        if (n_out) atomicAdd(&a.counters[1], (unsigned long long)n_out);
+        atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
     }
 }
 
@@ -1318,20 +1406,35 @@ constexpr int kChunk3f = 3;       // FP32: slots per lane and wave chunk
 constexpr int kThreadsMig = 768;   // migrant pass, FP64 (as many waves as the step kernel)
 constexpr int kThreadsMigf = 1024; // migrant pass, FP32
 constexpr int kThreads2 = 256;
+constexpr int kRows2 = 2;          // 2D: slots per thread ordered at a time
 constexpr int kMargin2 = 2;
 
-// Workgroups of the 2D3V step: several per tile until they fill the chip
-// (four per CU fit its LDS), none with less than one particle per thread on
-// average.  20 steps of 256^2 x 16: 1366, 1294, 1273, 1329, 1379 us at 1, 2, 3,
-// 4 and 8 per tile; 10 steps of 100 x 70 x 8: 384, 307, 281, 257, 250 us; 20
-// steps of 512^2 x 16 (1024 tiles): 3949, 3978, 4031, 4119, 4249 us.
-dim3 grid2(const GridK& k, int64_t n, int* split)
+// Workgroups per tile of the 2D3V step: enough to fill the chip four times over
+// (as many fit a CU's LDS) with two particles per thread each, or once with a
+// particle per two threads.  us per step at 1, 2, 3, 4, 8 workgroups per tile:
+// 78, 61, 56, 57, 69 for 256^2 x 16 per cell (4 taken); 35, 35, 38, 41, 51 for
+// 256^2 x 4 (2 taken); 40, 30, 28, 27, 24 for 100 x 70 x 8 (7 taken); 164, 173,
+// 177, 186, 223 for 512^2 x 16 (1 taken).
+int split2(int64_t ntiles, int64_t n)
 {
-    int64_t want = (4 * kCus + k.ntiles - 1) / k.ntiles;
-    const int64_t full = (n + (int64_t)k.ntiles * kThreads2 - 1) / ((int64_t)k.ntiles * kThreads2);
-    want = std::min(want, full);
-    *split = (int)std::max<int64_t>(1, std::min<int64_t>(want, 64));
-    return dim3((unsigned)(k.ntiles * *split));
+    const int64_t avg = n / ntiles;
+    const int64_t full = std::min<int64_t>(4 * kCus / ntiles, (avg + 2 * kThreads2 - 1) / (2 * kThreads2));
+    const int64_t thin = std::min<int64_t>(kCus / ntiles, (2 * avg + kThreads2 - 1) / kThreads2);
+    return (int)std::max<int64_t>(1, std::max(full, thin));
+}
+
+template <class R>
+void launch_step2(const Ctx& c, const StepArgs& a, int64_t n, hipStream_t s)
+{
+    const int split = split2(c.k.ntiles, n);
+    const dim3 grid((unsigned)(c.k.ntiles * split));
+    double* J = c.fields + 6 * c.k.ncell;
+    if (n / c.k.ntiles / split > kThreads2)
+        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2, kRows2, true>), grid, dim3(kThreads2), 0, s,
+                           c.k, a, c.fields, c.bn, J, split);
+    else
+        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2, kRows2, false>), grid, dim3(kThreads2), 0,
+                           s, c.k, a, c.fields, c.bn, J, split);
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -1380,8 +1483,7 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
                                c.fields, c.bn, J);
         }
         else
-            hipLaunchKernelGGL((k_particle_step2<double, kTile2, kMargin2, kThreads2>), grid2(c.k, sp.n, &split),
-                               dim3(kThreads2), 0, s, c.k, a, c.fields, c.bn, J, split);
+            launch_step2<double>(c, a, sp.n, s);
     } else {
         StepArgs a = step_args<float>(c, sp, c.counters);
         if (c.k.dims == 3) {
@@ -1392,8 +1494,7 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
                                c.fields, c.bn, J);
         }
         else
-            hipLaunchKernelGGL((k_particle_step2<float, kTile2, kMargin2, kThreads2>), grid2(c.k, sp.n, &split),
-                               dim3(kThreads2), 0, s, c.k, a, c.fields, c.bn, J, split);
+            launch_step2<float>(c, a, sp.n, s);
     }
     return hipGetLastError();
 }

@@ -368,6 +368,40 @@ __device__ __forceinline__ void deposit2(const R (&dm)[3][4], const R (&dp)[3][4
     }
 }
 
+// 2D3V particle that stays in its cell: as for deposit3_still, faces s+1, s+2
+// and cells s..s+2 remain, 6 + 6 + 9 contributions with the values of deposit2
+// on the same window.
+template <class R, class Sink>
+__device__ __forceinline__ void deposit2_still(const R (&s0)[2][3], const R (&s1)[2][3], const R jfac[3], R jz,
+                                               Sink S)
+{
+    const R third = R(1) / R(3);
+    R dm[2][3], dp[2][3];
+    for (int a = 0; a < 2; ++a)
+        for (int k = 0; k < 3; ++k) {
+            dm[a][k] = s1[a][k] - s0[a][k];
+            dp[a][k] = s1[a][k] + s0[a][k];
+        }
+    for (int comp = 0; comp < 2; ++comp) {
+        const int u = 1 - comp;
+        R P[2];
+        P[0] = dm[comp][0];
+        P[1] = dm[comp][0] + dm[comp][1];
+        for (int t = 0; t < 2; ++t) P[t] *= R(2) * jfac[comp];
+        for (int b = 0; b < 3; ++b)
+            for (int t = 0; t < 2; ++t) {
+                int ij[2];
+                ij[comp] = t + 1;
+                ij[u] = b;
+                S(comp, ij[0], ij[1], 0, (double)(P[t] * dp[u][b]));
+            }
+    }
+    for (int a = 0; a < 3; ++a) {
+        const R mx = dm[0][a] * third;
+        for (int b = 0; b < 3; ++b) S(2, a, b, 0, (double)(jz * (dp[0][a] * dp[1][b] + mx * dm[1][b])));
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Alternating order 2 1/2 (Section 4.5): with i = int(x + 1/2) and
 // d = x + 1/2 - i, the node factors f_{i-1:i+1} are the quadratic spline

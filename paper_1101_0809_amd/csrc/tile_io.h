@@ -89,23 +89,23 @@ __device__ __forceinline__ void flush_planes(const Cols& cols, Src src, Dst dst)
 }
 
 // ---------------------------------------------------------------------------
-// Class rows of a workgroup: an order of up to NT * U particles in which any 16
+// Class rows of a workgroup: an order of up to NT * U particles in which any C
 // consecutive ones are of distinct lane classes as far as the class counts
-// allow.  A particle's class is its LDS base index modulo 16 (16 lanes of
-// 8-byte values per LDS pass): the same stencil offset of 16 distinct classes
-// lies in 16 distinct banks, and without this order a pass over random cells
-// takes about three times as long.  Row r holds the rank-r particle of every
+// allow.  A particle's class is its LDS base index modulo C (16 lanes of 8-byte
+// values per LDS pass, 32 of 4-byte ones): the same stencil offset of distinct
+// classes lies in distinct banks, and without this order a pass over random
+// cells takes about three times as long.  Row r holds the rank-r particle of every
 // class that has one; ranks follow the storage order (a wave owns a contiguous
 // block and a prefix over the waves orders the blocks), so a row's particles
 // are also near each other in memory.
 // ---------------------------------------------------------------------------
 constexpr int kRowClasses = 16;
 
-template <int NT, int U>
+template <int NT, int U, int C = kRowClasses>
 struct ClassRows {
     static constexpr int W = NT * U, NW = NT / 64;
-    unsigned cnt[NW][kRowClasses];  // per wave: particles of each class; then their first rank
-    unsigned tot[kRowClasses];
+    unsigned cnt[NW][C];  // per wave: particles of each class; then their first rank
+    unsigned tot[C];
     uint16_t perm[W];               // position -> slot
 };
 
@@ -113,26 +113,26 @@ struct ClassRows {
 // to leave it out.  Returns the number of slots placed; perm is valid until
 // the next call.  Called by the whole workgroup; the caller puts a barrier
 // between the last use of perm and the next call.
-template <int NT, int U, class Cls>
-__device__ __forceinline__ int order_rows(ClassRows<NT, U>& s, int m, Cls cls)
+template <int NT, int U, int C, class Cls>
+__device__ __forceinline__ int order_rows(ClassRows<NT, U, C>& s, int m, Cls cls)
 {
-    static_assert(ClassRows<NT, U>::W <= 65536, "16-bit slots");
+    static_assert(ClassRows<NT, U, C>::W <= 65536 && C <= 64, "16-bit slots, a lane per class");
     const int t = threadIdx.x, wv = t >> 6, lane = t & 63;
-    if (lane < kRowClasses) s.cnt[wv][lane] = 0;
+    if (lane < C) s.cnt[wv][lane] = 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    int c[U];
+    int cl[U];
     unsigned rk[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int sl = (wv * U + u) * 64 + lane;
-        c[u] = sl < m ? cls(sl) : -1;
+        cl[u] = sl < m ? cls(sl) : -1;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (c[u] >= 0) rk[u] = atomicAdd(&s.cnt[wv][c[u]], 1u);
+        if (cl[u] >= 0) rk[u] = atomicAdd(&s.cnt[wv][cl[u]], 1u);
     __syncthreads();
-    if (t < kRowClasses) {
+    if (t < C) {
         unsigned run = 0;
         for (int w = 0; w < NT / 64; ++w) {
             const unsigned x = s.cnt[w][t];
@@ -142,20 +142,20 @@ __device__ __forceinline__ int order_rows(ClassRows<NT, U>& s, int m, Cls cls)
         s.tot[t] = run;
     }
     __syncthreads();
-    unsigned tot[kRowClasses], all = 0;
+    unsigned tot[C], all = 0;
 #pragma unroll
-    for (int k = 0; k < kRowClasses; ++k) {
+    for (int k = 0; k < C; ++k) {
         tot[k] = s.tot[k];
         all += tot[k];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        if (c[u] >= 0) {
+        if (cl[u] >= 0) {
             // the rows before this one, then the smaller classes of this row
-            const unsigned r = rk[u] + s.cnt[wv][c[u]];
+            const unsigned r = rk[u] + s.cnt[wv][cl[u]];
             unsigned pos = 0;
 #pragma unroll
-            for (int k = 0; k < kRowClasses; ++k) pos += min(tot[k], r + (k < c[u] ? 1u : 0u));
+            for (int k = 0; k < C; ++k) pos += min(tot[k], r + (k < cl[u] ? 1u : 0u));
             s.perm[pos] = (uint16_t)((wv * U + u) * 64 + lane);
         }
     __syncthreads();

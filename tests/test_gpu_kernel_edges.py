@@ -118,3 +118,17 @@ def test_two_pass_steps_in_class_rows(scheme, n, ppc, w_th, sort_every):
                                                   sort_every=sort_every)
     sim, st = mod._run_pair(wl, 9)
     mod._compare(sim, st, wl)
+
+
+@pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
+@pytest.mark.parametrize("nx,ny,ppc,w_th", [
+    (16, 16, 12, 0.2),    # one tile of a few shares
+    (48, 32, 40, 0.02),   # shares of several ordered chunks, cold
+    (40, 35, 30, 0.8)])   # most particles cross; many leave their tile
+def test_2d_step_in_class_rows(nx, ny, ppc, w_th, precision, tols):
+    """2D3V in class rows: several chunks per share, particles that stay and
+    that cross on one axis or both, and particles outside the margins."""
+    wl = picgen.WORKLOADS["2d3v_32x32_fp64"].scaled(nx=nx, ny=ny, ppc=ppc, w_th=(w_th,) * 3, omega_pe=0.1,
+                                                    drift=0.2, bext=(0.0, 0.0, 0.05))
+    sim, st, _ = _run_pair(wl, precision, 12, sort_every=6)
+    _compare(sim, st, wl, *tols)
