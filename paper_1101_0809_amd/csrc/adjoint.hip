@@ -35,7 +35,7 @@
 // (records), k_inverse / k_permute (particle adjoints between orders).
 #include <algorithm>
 
-#include "pic_math.h"
+#include "tile_io.h"
 
 namespace pic {
 namespace {
@@ -1032,20 +1032,25 @@ __global__ __launch_bounds__(kAdjThreads3) void k_adj_tile3(GridK g, AdjArgs a, 
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T, (tile / (g.nt[0] * g.nt[1])) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    for (int e = threadIdx.x; e < 6 * NF; e += NT) {
-        const int comp = e / NF, r = e - comp * NF;
-        const int gx = wrapi(T0[0] - 1 - M + r % LF, nx);
-        const int gy = wrapi(T0[1] - 1 - M + (r / LF) % LF, ny);
-        const int gz = wrapi(T0[2] - 1 - M + r / (LF * LF), nz);
-        const int64_t cell = ((int64_t)gz * ny + gy) * nx + gx;
-        sf[e] = comp < 3 ? a.E[comp * N + cell] : a.Bn[(comp - 3) * N + cell];
-    }
-    for (int e = threadIdx.x; e < 3 * NJ; e += NT) {
-        const int comp = e / NJ, r = e - comp * NJ;
-        const int gx = wrapi(T0[0] - 2 - M + r % LJ, nx);
-        const int gy = wrapi(T0[1] - 2 - M + (r / LJ) % LJ, ny);
-        const int gz = wrapi(T0[2] - 2 - M + r / (LJ * LJ), nz);
-        sj[e] = a.lamJ[comp * N + ((int64_t)gz * ny + gy) * nx + gx];
+    const bool small = nx < LJ || ny < LJ || nz < LJ;
+    const Columns<LF, LF, LF> fcols(g, T0[0] - 1 - M, T0[1] - 1 - M, small);
+    {
+        stage_planes<6 * LF, NT, 3, double>(
+            fcols,
+            [&](int t) {
+                const int comp = t / LF;
+                return (comp < 3 ? a.E + comp * N : a.Bn + (comp - 3) * N) +
+                       plane_offset(g, T0[2] - 1 - M + t - comp * LF, small);
+            },
+            [&](int t) { return sf + t * (LF * LF); });
+        const Columns<LJ, LJ, LJ> jcols(g, T0[0] - 2 - M, T0[1] - 2 - M, small);
+        stage_planes<3 * LJ, NT, 3, double>(
+            jcols,
+            [&](int t) {
+                const int comp = t / LJ;
+                return a.lamJ + comp * N + plane_offset(g, T0[2] - 2 - M + t - comp * LJ, small);
+            },
+            [&](int t) { return sj + t * (LJ * LJ); });
     }
     if (threadIdx.x < 3) sb[threadIdx.x] = 0.0;
     if (threadIdx.x < C) qn[threadIdx.x] = 0u;
@@ -1148,16 +1153,13 @@ __global__ __launch_bounds__(kAdjThreads3) void k_adj_tile3(GridK g, AdjArgs a, 
         scatter_comp<3, 5>(acc, w, a.scr[5][p]);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 6 * NF; e += NT) {
-        const double v = sf[e];
-        if (v == 0.0) continue;
-        const int comp = e / NF, r = e - comp * NF;
-        const int gx = wrapi(T0[0] - 1 - M + r % LF, nx);
-        const int gy = wrapi(T0[1] - 1 - M + (r / LF) % LF, ny);
-        const int gz = wrapi(T0[2] - 1 - M + r / (LF * LF), nz);
-        const int64_t cell = ((int64_t)gz * ny + gy) * nx + gx;
-        grid_add(comp < 3 ? &a.lamE[comp * N + cell] : &a.lamB[(comp - 3) * N + cell], v);
-    }
+    flush_planes<6 * LF, NT>(
+        fcols, [&](int t) { return sf + t * (LF * LF); },
+        [&](int t) {
+            const int comp = t / LF;
+            return (comp < 3 ? a.lamE + comp * N : a.lamB + (comp - 3) * N) +
+                   plane_offset(g, T0[2] - 1 - M + t - comp * LF, small);
+        });
     flush_bext(sb, lbp, a.lam_bext);
 }
 

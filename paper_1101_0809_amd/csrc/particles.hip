@@ -372,11 +372,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2
 // particle copy holds the crossing queue and the migrant lists (idle between
 // sorts); the sort scratch holds the buckets.
 // ---------------------------------------------------------------------------
-__host__ __device__ constexpr int fplane0(int comp)  // first stored plane of a field component
-{
-    return comp < 2 ? 12 * comp : (comp < 5 ? 24 + 11 * (comp - 2) : 57);
-}
-__host__ __device__ constexpr int fnodez(int comp) { return comp >= 2 && comp <= 4 ? 1 : 0; }
 // Lowest offset of the gather stencil of a component along an axis: 0 where
 // the component takes node factors along it (two points), -1 where it takes
 // cell factors (three points).
@@ -386,7 +381,6 @@ __host__ __device__ constexpr int lo_offset(int comp, int ax)
     const int node = comp == 0 ? 1 : comp == 1 ? 2 : comp == 2 ? 4 : comp == 3 ? 6 : comp == 4 ? 5 : 3;
     return (node >> ax) & 1 ? 0 : -1;
 }
-constexpr int kFieldPlanes3 = 69;  // 12 + 12 + 11 + 11 + 11 + 12
 constexpr int64_t kUnmapped = (int64_t)1 << 62;  // crossing entry not in the class map
 // A migrant bucket this full is advanced with LDS tiles.  Staging the tile and
 // flushing its current cost about as much as 8 particles on the global path
@@ -398,7 +392,9 @@ constexpr unsigned kMigLds = 8;
 // row, each lane one x column, so a lane wraps its x coordinate once and
 // each row is decoded once.  SK rows' loads of a thread are in flight before
 // their stores (one load at a time would wait out the memory latency once per
-// value).
+// value).  A plane per wave (stage_planes) saves most of the index arithmetic
+// and gains 1.6% of a 64^3 x 8 step in FP32 mode, but costs 1.1% at 128^3 x 32
+// and 4% of a 128^3 x 8 step in FP64.
 template <class R, int NT>
 __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], const double* __restrict__ fields,
                                               const double* __restrict__ bfield, R* sf, bool small)
@@ -425,8 +421,8 @@ __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], c
             if (r < NROWS) {
                 const int pl = r / LFY;
                 const int ly = r - pl * LFY;
-                const int comp = pl < 12 ? 0 : (pl < 24 ? 1 : (pl < 35 ? 2 : (pl < 46 ? 3 : (pl < 57 ? 4 : 5))));
-                const int lz = pl - fplane0(comp) + fnodez(comp);
+                int lz;
+                const int comp = field_plane3(pl, lz);
                 const int gy = wr(T0[1] - 1 - M + ly, ny);
                 const int gz = wr(T0[2] - 1 - M + lz, nz);
                 v[u] = (comp < 3 ? fields + comp * N : bfield + (comp - 3) * N)[((int64_t)gz * ny + gy) * nx + gx];
@@ -439,45 +435,27 @@ __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], c
     }
 }
 
-// Flush the LDS current tile of a 3D tile into the grid's J: 16 lanes per
-// row of the tile, one x column each (the padding is never written); the
-// columns of a row beyond 16 (FP32 mode's wider margin) follow, one (row,
-// column) pair per thread.  Only the non-zero entries take a global atomic.
+// Add the LDS current tile of a 3D tile to the grid's J; only the non-zero
+// entries take a global atomic (the padding is never written).  A plane per
+// wave, against a row per 16 lanes with each row decoded: 64^3 x 8 1950 -> 1934
+// us for 10 steps (FP64), 128^3 x 32 x 2 species 114.4 -> 113.5 ms for 20 (FP32
+// mode).
 template <class R, int NT, class LJT>
 __device__ __forceinline__ void flush_current3(const GridK& g, const int T0[3], const LJT& sj,
                                                double* __restrict__ Jg, bool small)
 {
     using TL = Tile3Dims<R>;
-    constexpr int MX = TL::MX, M = TL::M, LJX = TL::LJX, LJY = TL::LJY;
-    constexpr int SJY = TL::JROW, SJZ = TL::JPLANE;
-    constexpr int NJ = TL::NJ;
-    constexpr int RPP = NT / 16;
-    constexpr int NROWS = 3 * LJY * LJY;  // (component, plane, row)
-    constexpr int XT = LJX > 16 ? LJX - 16 : 0;  // columns beyond the 16-lane rows
-    static_assert(LJX <= 32 && NT % 64 == 0, "a current-tile row fits 16 lanes plus a tail");
-    const int64_t N = g.ncell;
-    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
-    auto one = [&](int r, int lx, int gx) {
-        const int comp = r / (LJY * LJY);
-        const int rr = r - comp * (LJY * LJY);
-        const int lz = rr / LJY;
-        const int ly = rr - lz * LJY;
-        const double v = sj.get(comp * NJ + lz * SJZ + ly * SJY + lx);
-        if (v == 0.0) return;
-        const int gy = wr(T0[1] - 2 - M + ly, ny);
-        const int gz = wr(T0[2] - 2 - M + lz, nz);
-        global_add(&Jg[comp * N + ((int64_t)gz * ny + gy) * nx + gx], v);
-    };
-    const int lx = (int)threadIdx.x & 15;
-    const int gx = wr(T0[0] - 2 - MX + (lx < LJX ? lx : 0), nx);
-    for (int r = lx < LJX ? (int)threadIdx.x >> 4 : NROWS; r < NROWS; r += RPP) one(r, lx, gx);
-    if (XT > 0)
-        for (int e = threadIdx.x; e < NROWS * XT; e += NT) {
-            const int r = e / (XT > 0 ? XT : 1);
-            const int cx = 16 + (e - r * XT);
-            one(r, cx, wr(T0[0] - 2 - MX + cx, nx));
-        }
+    const Columns<TL::LJX, TL::LJY, TL::JROW, TL::LJX <= 16> cols(g, T0[0] - 2 - TL::MX, T0[1] - 2 - TL::M, small);
+    flush_planes<3 * TL::LJY, NT>(
+        cols,
+        [&](int t) {
+            const int comp = t / TL::LJY;
+            return sj.v + comp * TL::NJ + (t - comp * TL::LJY) * TL::JPLANE;
+        },
+        [&](int t) {
+            const int comp = t / TL::LJY;
+            return Jg + comp * g.ncell + plane_offset(g, T0[2] - 2 - TL::M + t - comp * TL::LJY, small);
+        });
 }
 
 // Position of cell i0 relative to the tile at T0 (tile_rel); true if

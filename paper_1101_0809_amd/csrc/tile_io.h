@@ -8,15 +8,19 @@
 namespace pic {
 namespace {
 
-// The x, y columns of a tile region, dealt to the lanes of every wave: column
-// lane + 64 c at grid offset off[c] within a z plane and at lds[c] within a
-// plane of the region (off < 0: no such column).  A region's planes then go
+// The x, y columns of a tile region, dealt to the lanes of every wave: the
+// lane's c-th column is at grid offset off[c] within a z plane and at lds[c]
+// within a plane of the region (off < 0: no such column).  Packed, or
+// (ALIGNED, rows of up to 16 columns) with 16 lanes to a row, so that no row is
+// split over two accesses.  A region's planes then go
 // wave by wave with a scalar base address each, so that an element costs its
 // load and its store and no index arithmetic (decoding and wrapping every
 // element took 6 of the 12 us in which a tile of 14^3 cells x 6 was staged).
-template <int LX, int LY, int ROW>
+template <int LX, int LY, int ROW, bool ALIGNED = false>
 struct Columns {
-    static constexpr int CH = (LX * LY + 63) / 64;
+    static_assert(!ALIGNED || LX <= 16, "a row fits 16 lanes");
+    static constexpr int LANES = ALIGNED ? 16 : LX;  // lanes of a row
+    static constexpr int CH = (LANES * LY + 63) / 64;
     int off[CH], lds[CH];
     __device__ __forceinline__ Columns(const GridK& g, int fx, int fy, bool small)
     {
@@ -24,9 +28,9 @@ struct Columns {
         const int lane = (int)threadIdx.x & 63;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            const int e = lane + 64 * c, ly = e / LX, lx = e - ly * LX;
+            const int e = lane + 64 * c, ly = e / LANES, lx = e - ly * LANES;
             lds[c] = lx + ly * ROW;
-            off[c] = e < LX * LY ? wr(fy + ly, g.n[1]) * g.n[0] + wr(fx + lx, g.n[0]) : -1;
+            off[c] = lx < LX && ly < LY ? wr(fy + ly, g.n[1]) * g.n[0] + wr(fx + lx, g.n[0]) : -1;
         }
     }
 };
@@ -86,6 +90,24 @@ __device__ __forceinline__ void flush_planes(const Cols& cols, Src src, Dst dst)
                 if (v != 0.0) unsafeAtomicAdd(o + cols.off[c], v);
             }
     }
+}
+
+// The 3D field tile (Tile3): E^n and B^n on the tile plus its margins and the
+// stencil, in stored planes.  The components that are node-centred in z (E^z,
+// B^x, B^y) never read the first plane and store planes 1..11 only.
+__host__ __device__ constexpr int fplane0(int comp)  // first stored plane of a field component
+{
+    return comp < 2 ? 12 * comp : (comp < 5 ? 24 + 11 * (comp - 2) : 57);
+}
+__host__ __device__ constexpr int fnodez(int comp) { return comp >= 2 && comp <= 4 ? 1 : 0; }
+constexpr int kFieldPlanes3 = 69;  // 12 + 12 + 11 + 11 + 11 + 12
+
+// Stored plane t of the field tile: its component, and its z position.
+__device__ __forceinline__ int field_plane3(int t, int& lz)
+{
+    const int comp = t < 12 ? 0 : (t < 24 ? 1 : (t < 35 ? 2 : (t < 46 ? 3 : (t < 57 ? 4 : 5))));
+    lz = t - fplane0(comp) + fnodez(comp);
+    return comp;
 }
 
 // ---------------------------------------------------------------------------
