@@ -869,17 +869,46 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
     const int T0[2] = {(tile % g.nt[0]) * T, (tile / g.nt[0]) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1];
-    for (int e = threadIdx.x; e < 6 * NF; e += kAdjThreads) {
-        const int comp = e / NF, r = e - comp * NF;
-        const int gx = wrapi(T0[0] - 1 - M + r % LF, nx), gy = wrapi(T0[1] - 1 - M + r / LF, ny);
-        const int64_t cell = (int64_t)gy * nx + gx;
-        sf[e] = comp < 3 ? a.E[comp * N + cell] : a.Bn[(comp - 3) * N + cell];
-        sacc[e] = 0.0;
+    // a thread takes whole cells, all of its loads in flight before the stores
+    const bool small = nx < LJ || ny < LJ;
+    auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
+    constexpr int SF = (NF + kAdjThreads - 1) / kAdjThreads, SJ = (NJ + kAdjThreads - 1) / kAdjThreads;
+    double vf[SF][6], vj[SJ][3];
+#pragma unroll
+    for (int u = 0; u < SF; ++u) {
+        const int e = (int)threadIdx.x + u * kAdjThreads;
+        if (e < NF) {
+            const int64_t cell = (int64_t)wr(T0[1] - 1 - M + e / LF, ny) * nx + wr(T0[0] - 1 - M + e % LF, nx);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                vf[u][k] = a.E[k * N + cell];
+                vf[u][3 + k] = a.Bn[k * N + cell];
+            }
+        }
     }
-    for (int e = threadIdx.x; e < 3 * NJ; e += kAdjThreads) {
-        const int comp = e / NJ, r = e - comp * NJ;
-        const int gx = wrapi(T0[0] - 2 - M + r % LJ, nx), gy = wrapi(T0[1] - 2 - M + r / LJ, ny);
-        sj[e] = a.lamJ[comp * N + (int64_t)gy * nx + gx];
+#pragma unroll
+    for (int u = 0; u < SJ; ++u) {
+        const int e = (int)threadIdx.x + u * kAdjThreads;
+        if (e < NJ) {
+            const int64_t cell = (int64_t)wr(T0[1] - 2 - M + e / LJ, ny) * nx + wr(T0[0] - 2 - M + e % LJ, nx);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) vj[u][k] = a.lamJ[k * N + cell];
+        }
+    }
+    for (int e = threadIdx.x; e < 6 * NF; e += kAdjThreads) sacc[e] = 0.0;
+#pragma unroll
+    for (int u = 0; u < SF; ++u) {
+        const int e = (int)threadIdx.x + u * kAdjThreads;
+        if (e < NF)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) sf[k * NF + e] = vf[u][k];
+    }
+#pragma unroll
+    for (int u = 0; u < SJ; ++u) {
+        const int e = (int)threadIdx.x + u * kAdjThreads;
+        if (e < NJ)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) sj[k * NJ + e] = vj[u][k];
     }
     if (threadIdx.x < 3) sb[threadIdx.x] = 0.0;
     __syncthreads();
@@ -916,7 +945,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
         const double v = sacc[e];
         if (v == 0.0) continue;
         const int comp = e / NF, r = e - comp * NF;
-        const int gx = wrapi(T0[0] - 1 - M + r % LF, nx), gy = wrapi(T0[1] - 1 - M + r / LF, ny);
+        const int gx = wr(T0[0] - 1 - M + r % LF, nx), gy = wr(T0[1] - 1 - M + r / LF, ny);
         const int64_t cell = (int64_t)gy * nx + gx;
         grid_add(comp < 3 ? &a.lamE[comp * N + cell] : &a.lamB[(comp - 3) * N + cell], v);
     }
