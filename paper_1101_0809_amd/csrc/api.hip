@@ -323,6 +323,7 @@ int pic_init_grid(const pic_grid_desc* g, void* fields, size_t field_bytes, void
     c.scan_part = (uint32_t*)take(((size_t)nkeys / 1024 + 2) * 4);
     c.red = (double*)take(diag_partials_doubles(kMaxSpecies) * 8);
     c.counters = (unsigned long long*)take(8 * sizeof(unsigned long long));
+    c.work = (unsigned int*)c.red;  // (4 KB of it) within a step; the reductions run between steps
     c.bn = (double*)take(3 * (size_t)k.ncell * 8);
     c.adj = (double*)take(3 * (size_t)k.ncell * 8);
     if (k.field_form == 1) c.avec = (double*)take(3 * (size_t)k.ncell * 8);

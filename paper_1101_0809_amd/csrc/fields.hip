@@ -73,10 +73,12 @@ __global__ __launch_bounds__(kFieldThreads) void k_half_b(GridK g, double* __res
 __global__ __launch_bounds__(kFieldThreads) void k_half_b_pair(GridK g, double* __restrict__ f,
                                                                double* __restrict__ bn,
                                                                unsigned long long* __restrict__ zero, int nzero,
+                                                               unsigned int* __restrict__ work,
                                                                double* __restrict__ mur)
 {
     const int64_t p = (int64_t)blockIdx.x * kFieldThreads + threadIdx.x;
     if (p < nzero) zero[p] = 0;  // counters of the particle kernels that follow
+    if (p < kMaxSpecies * kXcds) work[p * kWorkStride] = 0;
     if (p >= g.ncell) return;
     const CellIdx c = cell_of(p, g);
     const int64_t N = g.ncell;
@@ -229,10 +231,12 @@ __global__ __launch_bounds__(kFieldThreads) void k_update_e(GridK g, double* __r
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kFieldThreads) void k_advance_a(GridK g, const double* __restrict__ f,
                                                              double* __restrict__ A,
-                                                             unsigned long long* __restrict__ zero, int nzero)
+                                                             unsigned long long* __restrict__ zero, int nzero,
+                                                             unsigned int* __restrict__ work)
 {
     const int64_t p = (int64_t)blockIdx.x * kFieldThreads + threadIdx.x;
     if (p < nzero) zero[p] = 0;  // counters of the particle kernels that follow
+    if (p < kMaxSpecies * kXcds) work[p * kWorkStride] = 0;
     if (p >= g.ncell) return;
     const int64_t N = g.ncell;
     const double cdt = g.c * g.dt;
@@ -291,7 +295,7 @@ hipError_t launch_field_half_b_pair(const Ctx& c, hipStream_t s, unsigned long l
     const unsigned blocks = (unsigned)((std::max<int64_t>(c.k.ncell, nzero) + kFieldThreads - 1) / kFieldThreads);
     double* mur = c.g.xbc == 1 ? c.adj : nullptr;
     hipLaunchKernelGGL(k_half_b_pair, dim3(blocks), dim3(kFieldThreads), 0, s, c.k, c.fields, c.bn, zero, nzero,
-                       mur);
+                       c.work, mur);
     if (mur) {
         const int64_t nyz = (int64_t)c.k.n[1] * c.k.n[2];
         const double cdt = c.g.c * c.g.dt;
@@ -321,7 +325,8 @@ namespace pic {
 hipError_t launch_field_half_a_pair(const Ctx& c, hipStream_t s, unsigned long long* zero, int nzero)
 {
     const unsigned blocks = (unsigned)((std::max<int64_t>(c.k.ncell, nzero) + kFieldThreads - 1) / kFieldThreads);
-    hipLaunchKernelGGL(k_advance_a, dim3(blocks), dim3(kFieldThreads), 0, s, c.k, c.fields, c.avec, zero, nzero);
+    hipLaunchKernelGGL(k_advance_a, dim3(blocks), dim3(kFieldThreads), 0, s, c.k, c.fields, c.avec, zero, nzero,
+                       c.work);
     const unsigned cb = (unsigned)((c.k.ncell + kFieldThreads - 1) / kFieldThreads);
     hipLaunchKernelGGL(k_b_of_a, dim3(cb), dim3(kFieldThreads), 0, s, c.k, c.fields, c.avec, c.bn);
     return hipGetLastError();

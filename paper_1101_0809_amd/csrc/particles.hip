@@ -397,7 +397,7 @@ constexpr unsigned kMigLds = 8;
 // and 4% of a 128^3 x 8 step in FP64.
 template <class R, int NT>
 __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], const double* __restrict__ fields,
-                                              const double* __restrict__ bfield, R* sf, bool small)
+                                              const double* __restrict__ bfield, R* sf, bool small, int tid)
 {
     using TL = Tile3Dims<R>;
     constexpr int MX = TL::MX, M = TL::M, LFX = TL::LFX, LFY = TL::LFY;
@@ -409,9 +409,9 @@ __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], c
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
     auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
-    const int lx = (int)threadIdx.x & 15;
+    const int lx = tid & 15;
     const int gx = wr(T0[0] - 1 - MX + (lx < LFX ? lx : 0), nx);
-    for (int r0 = lx < LFX ? (int)threadIdx.x >> 4 : NROWS; r0 < NROWS; r0 += SK * RPP) {
+    for (int r0 = lx < LFX ? tid >> 4 : NROWS; r0 < NROWS; r0 += SK * RPP) {
         double v[SK];
         int li[SK];
 #pragma unroll
@@ -440,13 +440,13 @@ __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], c
 // wave, against a row per 16 lanes with each row decoded: 64^3 x 8 1950 -> 1934
 // us for 10 steps (FP64), 128^3 x 32 x 2 species 114.4 -> 113.5 ms for 20 (FP32
 // mode).
-template <class R, int NT, class LJT>
-__device__ __forceinline__ void flush_current3(const GridK& g, const int T0[3], const LJT& sj,
-                                               double* __restrict__ Jg, bool small)
+template <class R, int NT, bool CLEAR = false, class LJT>
+__device__ __forceinline__ void flush_current3(const GridK& g, const int T0[3], LJT& sj,
+                                               double* __restrict__ Jg, bool small, int tid)
 {
     using TL = Tile3Dims<R>;
-    const Columns<TL::LJX, TL::LJY, TL::JROW, TL::LJX <= 16> cols(g, T0[0] - 2 - TL::MX, T0[1] - 2 - TL::M, small);
-    flush_planes<3 * TL::LJY, NT>(
+    const Columns<TL::LJX, TL::LJY, TL::JROW, TL::LJX <= 16> cols(g, T0[0] - 2 - TL::MX, T0[1] - 2 - TL::M, small, tid);
+    flush_planes<3 * TL::LJY, NT, CLEAR>(
         cols,
         [&](int t) {
             const int comp = t / TL::LJY;
@@ -637,10 +637,84 @@ __device__ __forceinline__ void advance_global3(const GridK& g, const StepArgs& 
     deposit3<R>(dm, dp, jfac, S);
 }
 
-template <class R, int NT, int KC>
-__global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, const double* __restrict__ fields,
-                                                      const double* __restrict__ bfield, double* __restrict__ Jg,
-                                                      int split)
+// The arguments of k_particle_step3.
+struct Step3Args {
+    GridK g;
+    StepArgs a;
+    const double* fields;
+    const double* bfield;
+    double* Jg;
+    int split;
+};
+using Step3Kernarg = const __attribute__((address_space(4))) Step3Args*;
+
+// A unit is a workgroup's share of a tile's slots: whole chunks of WCH (all of
+// the kernel's scratch lists are kept at the slots' own index range).
+template <int WCH>
+__device__ __forceinline__ void unit_span3(const Step3Args& s, int unit, int64_t& begin, int64_t& end)
+{
+    const int tile = unit / s.split;
+    begin = s.a.tile_start[tile];
+    end = s.a.tile_start[tile + 1];
+    if (s.split > 1) {
+        const int64_t len = ((end - begin + s.split - 1) / s.split + WCH - 1) / WCH * WCH;
+        begin += (unit - tile * s.split) * len;
+        end = min(begin + len, end);
+    }
+}
+
+// XCD x's run of units, [lo, hi): neighbouring tiles share its L2.
+__device__ __forceinline__ void unit_run3(const Step3Args& s, int x, int& lo, int& hi)
+{
+    const int units = s.g.ntiles * s.split, per = units / kXcds, rem = units % kXcds;
+    lo = x * per + min(x, rem);
+    hi = lo + per + (x < rem ? 1 : 0);
+}
+
+// The next unit with particles, by a whole wave: a workgroup starts with a unit
+// of its own XCD's run and takes the following ones from that run's counter,
+// then from the other XCDs'; -1 when all are taken.  (That is seen from one
+// read of all the counters: an atomic takes over a microsecond.)
+template <int WCH>
+__device__ __forceinline__ int next_unit3(const Step3Args& s, int lane)
+{
+    const int x = lane % kXcds;
+    int lo, hi;
+    unit_run3(s, x, lo, hi);
+    lo += ((int)gridDim.x - x + kXcds - 1) / kXcds;  // started with
+    for (int k = (int)blockIdx.x % kXcds;;) {
+        const int lo_k = __builtin_amdgcn_readlane(lo, k), hi_k = __builtin_amdgcn_readlane(hi, k);
+        int u = hi_k;
+        if (lo_k < hi_k) {
+            unsigned v = 0;
+            if (lane == 0) v = atomicAdd(&s.a.work[k * kWorkStride], 1u);
+            u = lo_k + __builtin_amdgcn_readfirstlane((int)v);
+        }
+        if (u < hi_k) {
+            int64_t b, e;
+            unit_span3<WCH>(s, u, b, e);
+            if (b < e) return u;
+            continue;
+        }
+        unsigned v = 0;
+        if (lane < kXcds) v = __hip_atomic_load(&s.a.work[x * kWorkStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t left = __ballot(lane < kXcds && lo + (int)v < hi);
+        if (left == 0) return -1;
+        const uint64_t after = left & ~((2ull << k) - 1);  // the next one in turn
+        k = (int)__ffsll((unsigned long long)(after ? after : left)) - 1;
+    }
+}
+
+// A unit per workgroup, or (PERSIST) a workgroup per CU that takes unit after
+// unit: its waves stage the next unit's fields as they finish the last one's
+// crossings, and a tile without particles costs a look at its slots, not a
+// workgroup of its own with its 160 KB of LDS.  In FP32 mode that takes 64^3 x 8
+// from 1619 to 1594 us for 10 steps, 128^3 x 32 x 2 species from 114.0 to 113.4
+// ms for 20, and a slab of 51 per cell on a fifth of 256 x 128 x 128 from 17.3 to
+// 16.6 ms for 20.  In FP64 the loop costs the particle code its registers (64^3 x
+// 8 1944 us against 1895, 128^3 x 8 14.63 ms against 14.29): a unit each.
+template <class R, int NT, int KC, bool PERSIST>
+__global__ __launch_bounds__(NT) void k_particle_step3(Step3Args kernarg)
 {
     constexpr int NW = NT / 64;  // waves
     constexpr int WCH = 64 * KC;  // slots per wave chunk
@@ -672,329 +746,382 @@ __global__ __launch_bounds__(NT) void k_particle_step3(GridK g, StepArgs a, cons
     __shared__ unsigned int qo_n;  // migrants whose bucket was full
     __shared__ unsigned int n_migrant;
     __shared__ unsigned int next_chunk, next_cross;  // work counters of the waves
+    __shared__ int s_next;                           // the workgroup's next unit
 
-    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
-    const int tile = unit / split;
-    const int tx = tile % g.nt[0];
-    const int ty = (tile / g.nt[0]) % g.nt[1];
-    const int tz = tile / (g.nt[0] * g.nt[1]);
-    const int T0[3] = {tx * T, ty * T, tz * T};
-    const bool small = g.n[0] < LJX || g.n[1] < LJY || g.n[2] < LJY;
-    const int wv = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
-    // this workgroup's share of the tile's slots: whole wave chunks (all of the
-    // scratch lists below are kept at the slots' own index range)
-    int64_t begin = a.tile_start[tile], end = a.tile_start[tile + 1];
-    if (split > 1) {
-        const int64_t len = ((end - begin + split - 1) / split + WCH - 1) / WCH * WCH;
-        begin += (unit - tile * split) * len;
-        end = min(begin + len, end);
-    }
-    if (begin >= end) return;  // no particle: nothing to stage, deposit or count (the whole workgroup)
-
-    // 1. stage E^n and B^n (B^n from bfield) into LDS
-    stage_fields3<R, NT>(g, T0, fields, bfield, sf, small);
-    // 2. clear the LDS current tile, the class counts and the queue counters
-    for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
-    if (lane < C) wcnt[wv][lane] = 0;
-    if (threadIdx.x < 27) mg_n[threadIdx.x] = 0;
-    if (threadIdx.x < 4 * CJ) qc_n[threadIdx.x] = 0;
-    if (threadIdx.x == 0) {
-        qc_total = 0;
-        qc_unmapped = 0;
-        qo_n = 0;
-        n_migrant = 0;
-        ml_n = 0;
-        next_chunk = NW;
-        next_cross = NW;
-    }
-    __syncthreads();
-
-    const int nt = (int)(end - begin);
-    const unsigned capc = (unsigned)(nt / (4 * CJ));
-    uint32_t* qmap = (uint32_t*)a.qmap + begin;
-    uint32_t* qother = (uint32_t*)a.qother + begin;
-    uint32_t* mslot = (uint32_t*)a.mlist + begin;   // migrant list: slot offsets
-    uint32_t* mword = (uint32_t*)a.mlist2 + begin;  // migrant list: rank | code << 27
-    unsigned my_migrant = 0;
-
-    // The next value of a work counter, the same for all lanes of the wave.
-    auto take = [&](unsigned int* counter) -> unsigned {
-        unsigned v = 0;
-        if (lane == 0) v = atomicAdd(counter, 1u);
-        return (unsigned)__builtin_amdgcn_readfirstlane((int)v);
-    };
-
-    // Classify slot sl (cell ci): true if its cell lies in the tile region,
-    // with its lane class; otherwise the particle joins the tile's migrant
-    // list, whose entries are placed after the particle loop (a wave with one
-    // migrant would otherwise run the whole placement with its other lanes
-    // idle).
-    auto classify = [&](int sl, const int ci[3], int& cls) -> bool {
-        int rel[3];
-        if (relative3<R>(g, T0, ci, rel)) {
-            cls = cell_class3<R>(rel[0], rel[1], rel[2]);
-            return true;
-        }
-        mslot[atomicAdd(&ml_n, 1u)] = (uint32_t)sl;
-        return false;
-    };
-
-    // Advance particle p, whose cell lies in the tile region: gather (LDS),
-    // push, move (state stored); a particle that stays in its cell deposits
-    // its 54 non-zero contributions, one that crosses a cell face is queued:
-    // its entry densely, in arrival order, and its place in the class map.
-    // Every lane of the wave that calls it must call it (the queue uses the
-    // wave's ballot); `active` false makes a lane a no-op.
-    auto advance = [&](int64_t p, bool active) {
-        bool still = true;
-        int rel[3] = {0, 0, 0}, delta[3] = {0, 0, 0};
-        R d0[3] = {0, 0, 0};
-        if (active) {
-            int i0[3];
-            PosIO<R, 3>::load(a, p, i0, d0);
-            relative3<R>(g, T0, i0, rel);
-            Axis<R> ax0[3];
-            R d1[3], qp;
-            advance_lds3<R>(g, a, sf, p, i0, d0, rel, ax0, d1, delta, qp);
-            still = (delta[0] | delta[1] | delta[2]) == 0;
-            if (still) {
-                R jfac[3];
-                for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
-                R s1[3][3], s0[3][3];
-                for (int ax = 0; ax < 3; ++ax) {
-                    cell_weights<R>(d1[ax], s1[ax]);
-                    for (int k = 0; k < 3; ++k) s0[ax][k] = ax0[ax].s[k];
-                }
-                const int jb = (rel[0] + 1 + MX) + (rel[1] + 1 + M) * SJY + (rel[2] + 1 + M) * SJZ;
-                auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                    sj.add(comp * NJ + jb + ix + iy * SJY + iz * SJZ, v);
-                };
-                deposit3_still<R>(s0, s1, jfac, S);
-            }
-        }
-        const unsigned long long mask = __ballot(!still);
-        if (!mask) return;
-        const int leader = __ffsll((long long)mask) - 1;
-        unsigned int qbase = 0;
-        if (lane == leader) qbase = atomicAdd(&qc_total, (unsigned int)__popcll(mask));
-        qbase = __shfl(qbase, leader, 64);
-        if (still) return;
-        const unsigned e = qbase + (unsigned)__popcll(mask & ((1ull << lane) - 1ull));
-        for (int ax = 0; ax < 3; ++ax) ((R*)a.qd0[ax])[begin + e] = d0[ax];
-        int64_t word = p - begin;
-        for (int ax = 0; ax < 3; ++ax) {
-            word |= (int64_t)(rel[ax] + (ax == 0 ? MX : M)) << (32 + 4 * ax);
-            word |= (int64_t)(delta[ax] + 1) << (44 + 2 * ax);
-        }
-        // map section: the crossing axis if there is one, 3 if several
-        const int nax = (delta[0] != 0) + (delta[1] != 0) + (delta[2] != 0);
-        const int sec = nax == 1 ? (delta[0] != 0 ? 0 : (delta[1] != 0 ? 1 : 2)) : 3;
-        int sw[3];
-        for (int ax = 0; ax < 3; ++ax) sw[ax] = rel[ax] + (delta[ax] < 0 ? -1 : 0) - 1;
-        const int jw = (sw[0] + 2 + MX) + (sw[1] + 2 + M) * SJY + (sw[2] + 2 + M) * SJZ;
-        const int col = sec * CJ + (jw & (CJ - 1));
-        const unsigned r = atomicAdd(&qc_n[col], 1u);
-        if (r < capc) {
-            qmap[col + 4 * CJ * r] = e;
-        } else {
-            word |= kUnmapped;
-            atomicAdd(&qc_unmapped, 1u);
-        }
-        a.qword[begin + e] = word;
-    };
-
-    // 3. wave chunks of WCH slots, lane l the slots l + 64 u: wave w starts
-    //    with chunk w and then takes the next chunk that no wave has taken.
-    //    No workgroup barrier inside the loop: the class order of a chunk is
-    //    the wave's own, in its own rows.
-    int ci[KC][3];
-#pragma unroll
-    for (int u = 0; u < KC; ++u)
-        if (wv * WCH + lane + 64 * u < nt) PosIO<R, 3>::cell(a, begin + wv * WCH + lane + 64 * u, ci[u]);
-    for (int cb = wv * WCH, cn; cb < nt; cb = cn) {
-        cn = (int)take(&next_chunk) * WCH;
-        // (a) classify
-        int cls[KC];
-        unsigned rk[KC];
-        bool in[KC];
-#pragma unroll
-        for (int u = 0; u < KC; ++u) {
-            const int sl = cb + lane + 64 * u;
-            cls[u] = 0;
-            rk[u] = 0;
-            in[u] = sl < nt && classify(sl, ci[u], cls[u]);
-            if (in[u]) rk[u] = atomicAdd(&wcnt[wv][cls[u]], 1u);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // (b) class rows: row r holds the rank-r particle of each class
-        //     that has one; lane r keeps row r's class mask and first position
-        const unsigned mycnt = lane < C ? wcnt[wv][lane] : 0u;
-        uint32_t rmask = 0;
-        unsigned rstart = 0, rows = 0;
-#pragma unroll
-        for (int r = 0; r < RW; ++r) {
-            const uint32_t m = (uint32_t)__ballot(mycnt > (unsigned)r);
-            rmask = lane == r ? m : rmask;
-            rstart = lane == r ? rows : rstart;
-            rows += (unsigned)__popc(m);
-        }
-        if (lane < C) wcnt[wv][lane] = 0;
-        if (lane == 0) wtail[wv] = 0;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        // (c) chunk order
-#pragma unroll
-        for (int u = 0; u < KC; ++u) {
-            const int rsel = in[u] && rk[u] < (unsigned)RW ? (int)rk[u] : 0;
-            const uint32_t m = (uint32_t)__shfl((int)rmask, rsel, 64);
-            const unsigned st = (unsigned)__shfl((int)rstart, rsel, 64);
-            if (in[u]) {
-                const unsigned pos = rk[u] < (unsigned)RW ? st + (unsigned)__popc(m & ((1u << cls[u]) - 1u))
-                                                          : rows + atomicAdd(&wtail[wv], 1u);
-                wperm[wv][pos] = (uint8_t)(lane + 64 * u);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const int ninside = (int)(rows + wtail[wv]);
-        // the next chunk's cells load while this chunk is advanced
-#pragma unroll
-        for (int u = 0; u < KC; ++u) {
-            const int nsl = cn + lane + 64 * u;
-            if (nsl < nt) PosIO<R, 3>::cell(a, begin + nsl, ci[u]);
-        }
-        // (d) advance: lane t takes chunk positions t, t + 64, ...
-        for (int q0 = 0; q0 < ninside; q0 += 64) {
-            const int q = q0 + lane;
-            advance(begin + cb + (q < ninside ? wperm[wv][q] : 0), q < ninside);
-        }
-    }
-    __syncthreads();
-    // The tile's migrants into the buckets of their new tiles.  First each
-    // migrant's rank among those to its neighbour tile (a tile further away
-    // takes its bucket slot at once); then one reservation per neighbour
-    // tile; then the bucket entries.
-    for (int e = threadIdx.x; e < (int)ml_n; e += NT) {
-        const uint32_t sl = mslot[e];
-        int ci[3];
-        PosIO<R, 3>::cell(a, begin + sl, ci);
-        const int code = neighbour_code3(g, tx, ty, tz, ci);
-        const unsigned r = code >= 0 ? atomicAdd(&mg_n[code], 1u) : 0u;
-        if (code >= 0 && r < (1u << kRankBits)) {
-            mword[e] = r | ((uint32_t)code << kRankBits);
-            continue;
-        }
-        mword[e] = kPlaced;
-        const int dt = tile_of3(g, ci);
-        const unsigned rr = atomicAdd(&a.mig_n[dt], 1u);
-        if (rr < a.mig_cap) {
-            a.mig[(int64_t)dt * a.mig_cap + rr] = (uint32_t)(begin + sl);
-            ++my_migrant;
-        } else {
-            qother[atomicAdd(&qo_n, 1u)] = sl;
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 27 && mg_n[threadIdx.x])
-        mg_base[threadIdx.x] = atomicAdd(&a.mig_n[neighbour_tile3(g, tx, ty, tz, threadIdx.x)], mg_n[threadIdx.x]);
-    __syncthreads();
-    for (int e = threadIdx.x; e < (int)ml_n; e += NT) {
-        const uint32_t word = mword[e];
-        if (word == kPlaced) continue;
-        const int code = (int)(word >> kRankBits);
-        const unsigned r = mg_base[code] + (word & ((1u << kRankBits) - 1u));
-        if (r < a.mig_cap) {
-            a.mig[(int64_t)neighbour_tile3(g, tx, ty, tz, code) * a.mig_cap + r] = (uint32_t)(begin + mslot[e]);
-            ++my_migrant;
-        } else {
-            qother[atomicAdd(&qo_n, 1u)] = mslot[e];
-        }
-    }
-    if (my_migrant) atomicAdd(&n_migrant, my_migrant);
-    __syncthreads();
-
-    // 4. migrants whose bucket was full: global memory
-    for (int q = threadIdx.x; q < (int)qo_n; q += NT)
-        advance_global3<R>(g, a, begin + qother[q], fields, bfield, Jg);
-
-    // 5. pass 3: the crossing queue -- the class map's four sections, then,
-    //    only if a map column was full, the unmapped entries in arrival order
+    int unit;
     {
-        auto cross = [&](int64_t e, int sec) {
-            const int64_t word = a.qword[e];
-            const int64_t p = begin + (word & 0xffffffffll);
-            int rel[3], delta[3];
-            R d0[3], d1[3];
-            for (int ax = 0; ax < 3; ++ax) {
-                rel[ax] = (int)((word >> (32 + 4 * ax)) & 15) - (ax == 0 ? MX : M);
-                delta[ax] = (int)((word >> (44 + 2 * ax)) & 3) - 1;
-                d0[ax] = ((const R*)a.qd0[ax])[e];
-                if (sizeof(R) == 8) {  // the stored end position, as in PosIO::move
-                    const double x = ((const double*)a.pos[ax])[p];
-                    d1[ax] = (R)(x - floor(x));
-                } else {
-                    d1[ax] = ((const R*)a.pos[ax])[p];
+        int hi;
+        unit_run3(kernarg, (int)blockIdx.x % kXcds, unit, hi);
+        unit += (int)blockIdx.x / kXcds;
+        int64_t b, e;
+        unit_span3<WCH>(kernarg, unit, b, e);
+        if (b >= e) {
+            if (!PERSIST || (int)gridDim.x == kernarg.g.ntiles * kernarg.split) return;
+            if (threadIdx.x < 64) {
+                const int u = next_unit3<WCH>(kernarg, (int)threadIdx.x);
+                if (threadIdx.x == 0) s_next = u;
+            }
+            __syncthreads();
+            unit = __builtin_amdgcn_readfirstlane(s_next);
+            if (unit < 0) return;
+            __syncthreads();
+        }
+    }
+    for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
+    if (threadIdx.x < NW * C) wcnt[threadIdx.x / C][threadIdx.x % C] = 0;
+
+    for (int done = -1;;) {  // the unit whose current is still in LDS
+        // Opaque in every turn: else the index arithmetic and the arguments
+        // stay in registers over the loop, and the particle code spills.
+        int tid = (int)threadIdx.x;
+        unsigned zero = 0;
+        Step3Kernarg ap = (Step3Kernarg)__builtin_amdgcn_kernarg_segment_ptr();
+        if (PERSIST) {
+            asm volatile("" : "+v"(tid), "+v"(zero));
+            asm volatile("" : "+s"(ap));
+        }
+        const Step3Args& args = PERSIST ? *(const Step3Args*)ap : kernarg;
+        const GridK& g = args.g;
+        const StepArgs& a = args.a;
+        const double* fields = args.fields;
+        const double* bfield = args.bfield;
+        double* Jg = args.Jg;
+        const bool small = g.n[0] < LJX || g.n[1] < LJY || g.n[2] < LJY;
+        const int wv = tid >> 6, lane = tid & 63;
+        auto origin = [&](int u, int o[3]) {
+            const int tile = u / args.split;
+            o[0] = tile % g.nt[0] * T;
+            o[1] = (tile / g.nt[0]) % g.nt[1] * T;
+            o[2] = tile / (g.nt[0] * g.nt[1]) * T;
+        };
+        // 1. the unit's E^n and B^n (B^n from bfield) into LDS, while other waves
+        //    still deposit the last unit's crossings (which do not read them)
+        int T0[3];
+        origin(unit, T0);
+        if (!PERSIST || unit >= 0) stage_fields3<R, NT>(g, T0, fields, bfield, sf, small, tid);
+        // 2. flush and clear the last unit's current, clear the queue counters
+        auto flush = [&](int u) {
+            __syncthreads();
+            int o[3];
+            origin(u, o);
+            flush_current3<R, NT, PERSIST>(g, o, sj, Jg, small, tid);
+            if (tid == 0 && a.counters) {
+                int64_t b, e;
+                unit_span3<WCH>(args, u, b, e);
+                if (qo_n) atomicAdd(&a.counters[1], (unsigned long long)qo_n);
+                atomicAdd(&a.counters[2], (unsigned long long)(e - b));
+                if (n_migrant) atomicAdd(&a.counters[3], (unsigned long long)n_migrant);
+            }
+        };
+        if (PERSIST && done >= 0) {
+            flush(done);
+            if (unit < 0) return;
+        }
+        int64_t begin, end;
+        unit_span3<WCH>(args, unit, begin, end);
+        const int tx = T0[0] / T, ty = T0[1] / T, tz = T0[2] / T;
+        if (tid < 27) mg_n[tid] = 0;
+        if (tid < 4 * CJ) qc_n[tid] = 0;
+        if (tid == 0) {
+            qc_total = zero;
+            qc_unmapped = zero;
+            qo_n = zero;
+            n_migrant = zero;
+            ml_n = zero;
+            next_chunk = NW;
+            next_cross = NW;
+        }
+        __syncthreads();
+
+        const int nt = (int)(end - begin);
+        const unsigned capc = (unsigned)(nt / (4 * CJ));
+        uint32_t* qmap = (uint32_t*)a.qmap + begin;
+        uint32_t* qother = (uint32_t*)a.qother + begin;
+        uint32_t* mslot = (uint32_t*)a.mlist + begin;   // migrant list: slot offsets
+        uint32_t* mword = (uint32_t*)a.mlist2 + begin;  // migrant list: rank | code << 27
+        unsigned my_migrant = 0;
+
+        // The next value of a work counter, the same for all lanes of the wave.
+        auto take = [&](unsigned int* counter) -> unsigned {
+            unsigned v = 0;
+            if (lane == 0) v = atomicAdd(counter, 1u);
+            return (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+        };
+
+        // Classify slot sl (cell ci): true if its cell lies in the tile region,
+        // with its lane class; otherwise the particle joins the tile's migrant
+        // list, whose entries are placed after the particle loop (a wave with one
+        // migrant would otherwise run the whole placement with its other lanes
+        // idle).
+        auto classify = [&](int sl, const int ci[3], int& cls) -> bool {
+            int rel[3];
+            if (relative3<R>(g, T0, ci, rel)) {
+                cls = cell_class3<R>(rel[0], rel[1], rel[2]);
+                return true;
+            }
+            mslot[atomicAdd(&ml_n, 1u)] = (uint32_t)sl;
+            return false;
+        };
+
+        // Advance particle p, whose cell lies in the tile region: gather (LDS),
+        // push, move (state stored); a particle that stays in its cell deposits
+        // its 54 non-zero contributions, one that crosses a cell face is queued:
+        // its entry densely, in arrival order, and its place in the class map.
+        // Every lane of the wave that calls it must call it (the queue uses the
+        // wave's ballot); `active` false makes a lane a no-op.
+        auto advance = [&](int64_t p, bool active) {
+            bool still = true;
+            int rel[3] = {0, 0, 0}, delta[3] = {0, 0, 0};
+            R d0[3] = {0, 0, 0};
+            if (active) {
+                int i0[3];
+                PosIO<R, 3>::load(a, p, i0, d0);
+                relative3<R>(g, T0, i0, rel);
+                Axis<R> ax0[3];
+                R d1[3], qp;
+                advance_lds3<R>(g, a, sf, p, i0, d0, rel, ax0, d1, delta, qp);
+                still = (delta[0] | delta[1] | delta[2]) == 0;
+                if (still) {
+                    R jfac[3];
+                    for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
+                    R s1[3][3], s0[3][3];
+                    for (int ax = 0; ax < 3; ++ax) {
+                        cell_weights<R>(d1[ax], s1[ax]);
+                        for (int k = 0; k < 3; ++k) s0[ax][k] = ax0[ax].s[k];
+                    }
+                    const int jb = (rel[0] + 1 + MX) + (rel[1] + 1 + M) * SJY + (rel[2] + 1 + M) * SJZ;
+                    auto S = [&](int comp, int ix, int iy, int iz, double v) {
+                        sj.add(comp * NJ + jb + ix + iy * SJY + iz * SJZ, v);
+                    };
+                    deposit3_still<R>(s0, s1, jfac, S);
                 }
             }
-            const R qp = (R)a.q * ((const R*)a.weight)[p];
-            R jfac[3];
-            for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
-            R dm[3][4], dp[3][4];
+            const unsigned long long mask = __ballot(!still);
+            if (!mask) return;
+            const int leader = __ffsll((long long)mask) - 1;
+            unsigned int qbase = 0;
+            if (lane == leader) qbase = atomicAdd(&qc_total, (unsigned int)__popcll(mask));
+            qbase = __shfl(qbase, leader, 64);
+            if (still) return;
+            const unsigned e = qbase + (unsigned)__popcll(mask & ((1ull << lane) - 1ull));
+            for (int ax = 0; ax < 3; ++ax) ((R*)a.qd0[ax])[begin + e] = d0[ax];
+            int64_t word = p - begin;
             for (int ax = 0; ax < 3; ++ax) {
-                R s0[3], s1[3];
-                cell_weights<R>(d0[ax], s0);
-                cell_weights<R>(d1[ax], s1);
-                window<R>(s0, s1, delta[ax], dm[ax], dp[ax]);
+                word |= (int64_t)(rel[ax] + (ax == 0 ? MX : M)) << (32 + 4 * ax);
+                word |= (int64_t)(delta[ax] + 1) << (44 + 2 * ax);
             }
+            // map section: the crossing axis if there is one, 3 if several
+            const int nax = (delta[0] != 0) + (delta[1] != 0) + (delta[2] != 0);
+            const int sec = nax == 1 ? (delta[0] != 0 ? 0 : (delta[1] != 0 ? 1 : 2)) : 3;
             int sw[3];
             for (int ax = 0; ax < 3; ++ax) sw[ax] = rel[ax] + (delta[ax] < 0 ? -1 : 0) - 1;
-            const int jb = (sw[0] + 2 + MX) + (sw[1] + 2 + M) * SJY + (sw[2] + 2 + M) * SJZ;
-            auto S = [&](int comp, int ix, int iy, int iz, double v) {
-                sj.add(comp * NJ + jb + ix + iy * SJY + iz * SJZ, v);
-            };
-            if (sec == 0) deposit3_axis<0, R>(dm, dp, jfac, S);
-            else if (sec == 1) deposit3_axis<1, R>(dm, dp, jfac, S);
-            else if (sec == 2) deposit3_axis<2, R>(dm, dp, jfac, S);
-            else deposit3<R>(dm, dp, jfac, S);
+            const int jw = (sw[0] + 2 + MX) + (sw[1] + 2 + M) * SJY + (sw[2] + 2 + M) * SJZ;
+            const int col = sec * CJ + (jw & (CJ - 1));
+            const unsigned r = atomicAdd(&qc_n[col], 1u);
+            if (r < capc) {
+                qmap[col + 4 * CJ * r] = e;
+            } else {
+                word |= kUnmapped;
+                atomicAdd(&qc_unmapped, 1u);
+            }
+            a.qword[begin + e] = word;
         };
-        // blocks of 64 map entries (four rows) of one section each, the widest
-        // deposit (section 3) first; wave w starts with block w and then takes
-        // the next one, so that every wave runs a single deposit variant at a
-        // time whatever the share of each section
-        {
-            unsigned rows = min(qc_n[lane], capc);  // lane = section * CJ + column
+
+        // 3. wave chunks of WCH slots, lane l the slots l + 64 u: wave w starts
+        //    with chunk w and then takes the next chunk that no wave has taken.
+        //    No workgroup barrier inside the loop: the class order of a chunk is
+        //    the wave's own, in its own rows.
+        int ci[KC][3];
 #pragma unroll
-            for (int o = 1; o < CJ; o <<= 1) rows = max(rows, (unsigned)__shfl_xor((int)rows, o, 64));
-            constexpr int RPB = 64 / CJ;  // rows per block
-            const int nb = ((int)rows + RPB - 1) / RPB;
-            int last[4];  // blocks of sections 3, 2, 1, 0, cumulated
-            int run = 0;
+        for (int u = 0; u < KC; ++u)
+            if (wv * WCH + lane + 64 * u < nt) PosIO<R, 3>::cell(a, begin + wv * WCH + lane + 64 * u, ci[u]);
+        for (int cb = wv * WCH, cn; cb < nt; cb = cn) {
+            cn = (int)take(&next_chunk) * WCH;
+            // (a) classify
+            int cls[KC];
+            unsigned rk[KC];
+            bool in[KC];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) last[k] = run += __builtin_amdgcn_readlane(nb, (3 - k) * CJ);
-            for (int blk = wv; blk < run; blk = (int)take(&next_cross)) {
-                const int k = blk < last[0] ? 0 : (blk < last[1] ? 1 : (blk < last[2] ? 2 : 3));
-                const int sec = 3 - k;
-                const int col = sec * CJ + (lane & (CJ - 1));
-                const unsigned row = (unsigned)((blk - (k > 0 ? last[k - 1] : 0)) * RPB + lane / CJ);
-                if (row < min(qc_n[col], capc)) cross(begin + qmap[col + 4 * CJ * row], sec);
+            for (int u = 0; u < KC; ++u) {
+                const int sl = cb + lane + 64 * u;
+                cls[u] = 0;
+                rk[u] = 0;
+                in[u] = sl < nt && classify(sl, ci[u], cls[u]);
+                if (in[u]) rk[u] = atomicAdd(&wcnt[wv][cls[u]], 1u);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            // (b) class rows: row r holds the rank-r particle of each class
+            //     that has one; lane r keeps row r's class mask and first position
+            const unsigned mycnt = lane < C ? wcnt[wv][lane] : 0u;
+            uint32_t rmask = 0;
+            unsigned rstart = 0, rows = 0;
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                const uint32_t m = (uint32_t)__ballot(mycnt > (unsigned)r);
+                rmask = lane == r ? m : rmask;
+                rstart = lane == r ? rows : rstart;
+                rows += (unsigned)__popc(m);
+            }
+            if (lane < C) wcnt[wv][lane] = 0;
+            if (lane == 0) wtail[wv] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            // (c) chunk order
+#pragma unroll
+            for (int u = 0; u < KC; ++u) {
+                const int rsel = in[u] && rk[u] < (unsigned)RW ? (int)rk[u] : 0;
+                const uint32_t m = (uint32_t)__shfl((int)rmask, rsel, 64);
+                const unsigned st = (unsigned)__shfl((int)rstart, rsel, 64);
+                if (in[u]) {
+                    const unsigned pos = rk[u] < (unsigned)RW ? st + (unsigned)__popc(m & ((1u << cls[u]) - 1u))
+                                                              : rows + atomicAdd(&wtail[wv], 1u);
+                    wperm[wv][pos] = (uint8_t)(lane + 64 * u);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int ninside = (int)(rows + wtail[wv]);
+            // the next chunk's cells load while this chunk is advanced
+#pragma unroll
+            for (int u = 0; u < KC; ++u) {
+                const int nsl = cn + lane + 64 * u;
+                if (nsl < nt) PosIO<R, 3>::cell(a, begin + nsl, ci[u]);
+            }
+            // (d) advance: lane t takes chunk positions t, t + 64, ...
+            for (int q0 = 0; q0 < ninside; q0 += 64) {
+                const int q = q0 + lane;
+                advance(begin + cb + (q < ninside ? wperm[wv][q] : 0), q < ninside);
             }
         }
-        if (qc_unmapped) {
-            for (int q = threadIdx.x; q < (int)qc_total; q += NT) {
-                const int64_t e = begin + q;
-                if (a.qword[e] & kUnmapped) cross(e, 3);
+        if (PERSIST && wave_index() == 0) {  // before the barrier: others are still at their chunks
+            const int u = (int)gridDim.x < g.ntiles * args.split ? next_unit3<WCH>(args, lane) : -1;
+            if (lane == 0) s_next = u;
+        }
+        __syncthreads();
+        // The tile's migrants into the buckets of their new tiles.  First each
+        // migrant's rank among those to its neighbour tile (a tile further away
+        // takes its bucket slot at once); then one reservation per neighbour
+        // tile; then the bucket entries.
+        for (int e = tid; e < (int)ml_n; e += NT) {
+            const uint32_t sl = mslot[e];
+            int ci[3];
+            PosIO<R, 3>::cell(a, begin + sl, ci);
+            const int code = neighbour_code3(g, tx, ty, tz, ci);
+            const unsigned r = code >= 0 ? atomicAdd(&mg_n[code], 1u) : 0u;
+            if (code >= 0 && r < (1u << kRankBits)) {
+                mword[e] = r | ((uint32_t)code << kRankBits);
+                continue;
+            }
+            mword[e] = kPlaced;
+            const int dt = tile_of3(g, ci);
+            const unsigned rr = atomicAdd(&a.mig_n[dt], 1u);
+            if (rr < a.mig_cap) {
+                a.mig[(int64_t)dt * a.mig_cap + rr] = (uint32_t)(begin + sl);
+                ++my_migrant;
+            } else {
+                qother[atomicAdd(&qo_n, 1u)] = sl;
             }
         }
         __syncthreads();
-    }
+        if (tid < 27 && mg_n[tid])
+            mg_base[tid] = atomicAdd(&a.mig_n[neighbour_tile3(g, tx, ty, tz, tid)], mg_n[tid]);
+        __syncthreads();
+        for (int e = tid; e < (int)ml_n; e += NT) {
+            const uint32_t word = mword[e];
+            if (word == kPlaced) continue;
+            const int code = (int)(word >> kRankBits);
+            const unsigned r = mg_base[code] + (word & ((1u << kRankBits) - 1u));
+            if (r < a.mig_cap) {
+                a.mig[(int64_t)neighbour_tile3(g, tx, ty, tz, code) * a.mig_cap + r] = (uint32_t)(begin + mslot[e]);
+                ++my_migrant;
+            } else {
+                qother[atomicAdd(&qo_n, 1u)] = mslot[e];
+            }
+        }
+        if (my_migrant) atomicAdd(&n_migrant, my_migrant);
+        __syncthreads();
 
-    // 6. flush the LDS current tile
-    flush_current3<R, NT>(g, T0, sj, Jg, small);
-    if (threadIdx.x == 0 && a.counters) {
-        atomicAdd(&a.counters[1], (unsigned long long)qo_n);
-        atomicAdd(&a.counters[2], (unsigned long long)(end - begin));
-        atomicAdd(&a.counters[3], (unsigned long long)n_migrant);
+        // 4. migrants whose bucket was full: global memory
+        for (int q = tid; q < (int)qo_n; q += NT)
+            advance_global3<R>(g, a, begin + qother[q], fields, bfield, Jg);
+
+        // 5. pass 3: the crossing queue -- the class map's four sections, then,
+        //    only if a map column was full, the unmapped entries in arrival order
+        {
+            auto cross = [&](int64_t e, int sec) {
+                const int64_t word = a.qword[e];
+                const int64_t p = begin + (word & 0xffffffffll);
+                int rel[3], delta[3];
+                R d0[3], d1[3];
+                for (int ax = 0; ax < 3; ++ax) {
+                    rel[ax] = (int)((word >> (32 + 4 * ax)) & 15) - (ax == 0 ? MX : M);
+                    delta[ax] = (int)((word >> (44 + 2 * ax)) & 3) - 1;
+                    d0[ax] = ((const R*)a.qd0[ax])[e];
+                    if (sizeof(R) == 8) {  // the stored end position, as in PosIO::move
+                        const double x = ((const double*)a.pos[ax])[p];
+                        d1[ax] = (R)(x - floor(x));
+                    } else {
+                        d1[ax] = ((const R*)a.pos[ax])[p];
+                    }
+                }
+                const R qp = (R)a.q * ((const R*)a.weight)[p];
+                R jfac[3];
+                for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * qp;
+                R dm[3][4], dp[3][4];
+                for (int ax = 0; ax < 3; ++ax) {
+                    R s0[3], s1[3];
+                    cell_weights<R>(d0[ax], s0);
+                    cell_weights<R>(d1[ax], s1);
+                    window<R>(s0, s1, delta[ax], dm[ax], dp[ax]);
+                }
+                int sw[3];
+                for (int ax = 0; ax < 3; ++ax) sw[ax] = rel[ax] + (delta[ax] < 0 ? -1 : 0) - 1;
+                const int jb = (sw[0] + 2 + MX) + (sw[1] + 2 + M) * SJY + (sw[2] + 2 + M) * SJZ;
+                auto S = [&](int comp, int ix, int iy, int iz, double v) {
+                    sj.add(comp * NJ + jb + ix + iy * SJY + iz * SJZ, v);
+                };
+                if (sec == 0) deposit3_axis<0, R>(dm, dp, jfac, S);
+                else if (sec == 1) deposit3_axis<1, R>(dm, dp, jfac, S);
+                else if (sec == 2) deposit3_axis<2, R>(dm, dp, jfac, S);
+                else deposit3<R>(dm, dp, jfac, S);
+            };
+            // blocks of 64 map entries (four rows) of one section each, the widest
+            // deposit (section 3) first; wave w starts with block w and then takes
+            // the next one, so that every wave runs a single deposit variant at a
+            // time whatever the share of each section
+            {
+                unsigned rows = min(qc_n[lane], capc);  // lane = section * CJ + column
+#pragma unroll
+                for (int o = 1; o < CJ; o <<= 1) rows = max(rows, (unsigned)__shfl_xor((int)rows, o, 64));
+                constexpr int RPB = 64 / CJ;  // rows per block
+                const int nb = ((int)rows + RPB - 1) / RPB;
+                int last[4];  // blocks of sections 3, 2, 1, 0, cumulated
+                int run = 0;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) last[k] = run += __builtin_amdgcn_readlane(nb, (3 - k) * CJ);
+                for (int blk = wv; blk < run; blk = (int)take(&next_cross)) {
+                    const int k = blk < last[0] ? 0 : (blk < last[1] ? 1 : (blk < last[2] ? 2 : 3));
+                    const int sec = 3 - k;
+                    const int col = sec * CJ + (lane & (CJ - 1));
+                    const unsigned row = (unsigned)((blk - (k > 0 ? last[k - 1] : 0)) * RPB + lane / CJ);
+                    if (row < min(qc_n[col], capc)) cross(begin + qmap[col + 4 * CJ * row], sec);
+                }
+            }
+            if (qc_unmapped) {
+                for (int q = tid; q < (int)qc_total; q += NT) {
+                    const int64_t e = begin + q;
+                    if (a.qword[e] & kUnmapped) cross(e, 3);
+                }
+            }
+        }
+
+        if (!PERSIST) {
+            flush(unit);
+            return;
+        }
+        done = unit;
+        unit = __builtin_amdgcn_readfirstlane(s_next);
     }
 }
 
@@ -1036,7 +1163,7 @@ __global__ __launch_bounds__(NT) void k_migrants3(GridK g, StepArgs a, const dou
     const int tz = tile / (g.nt[0] * g.nt[1]);
     const int T0[3] = {tx * T, ty * T, tz * T};
     const bool small = g.n[0] < TL::LJX || g.n[1] < TL::LJY || g.n[2] < TL::LJY;
-    stage_fields3<R, NT>(g, T0, fields, bfield, sf, small);
+    stage_fields3<R, NT>(g, T0, fields, bfield, sf, small, (int)threadIdx.x);
     for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
     if (threadIdx.x == 0) n_global = 0;
     __syncthreads();
@@ -1074,7 +1201,7 @@ __global__ __launch_bounds__(NT) void k_migrants3(GridK g, StepArgs a, const dou
     }
     if (my_global) atomicAdd(&n_global, my_global);
     __syncthreads();
-    flush_current3<R, NT>(g, T0, sj, Jg, small);
+    flush_current3<R, NT>(g, T0, sj, Jg, small, (int)threadIdx.x);
     if (threadIdx.x == 0) {
         a.mig_n[tile] = 0;
         if (a.counters && n_global) atomicAdd(&a.counters[1], (unsigned long long)n_global);
@@ -1367,6 +1494,7 @@ StepArgs step_args(const Ctx& c, const Species& sp, unsigned long long* counters
     a.mig = sp.key;
     a.mig_cap = (uint32_t)(((size_t)((char*)sp.tile_start - (char*)sp.key) / 4) / (size_t)c.k.ntiles);
     a.mig_n = c.mig_n;
+    a.work = c.work + kXcds * kWorkStride * (int)(&sp - c.sp);
     for (int ax = 0; ax < 3; ++ax) a.qd0[ax] = sp.alt.pos[ax];
     a.qword = sp.alt.id;
     a.qmap = (void*)sp.alt.weight;
@@ -1455,8 +1583,8 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
         StepArgs a = step_args<double>(c, sp, c.counters);
         if (c.k.dims == 3) {
             split = tile_split(c.k.ntiles, sp.n, kFixed3);
-            hipLaunchKernelGGL((k_particle_step3<double, kThreads3, kChunk3>), dim3(c.k.ntiles * split),
-                               dim3(kThreads3), 0, s, c.k, a, c.fields, c.bn, J, split);
+            hipLaunchKernelGGL((k_particle_step3<double, kThreads3, kChunk3, false>), dim3(c.k.ntiles * split),
+                               dim3(kThreads3), 0, s, Step3Args{c.k, a, c.fields, c.bn, J, split});
             hipLaunchKernelGGL((k_migrants3<double, kThreadsMig>), grid, dim3(kThreadsMig), 0, s, c.k, a,
                                c.fields, c.bn, J);
         }
@@ -1466,8 +1594,10 @@ hipError_t launch_particle_step(Ctx& c, Species& sp, hipStream_t s)
         StepArgs a = step_args<float>(c, sp, c.counters);
         if (c.k.dims == 3) {
             split = tile_split(c.k.ntiles, sp.n, kFixed3f);
-            hipLaunchKernelGGL((k_particle_step3<float, kThreads3f, kChunk3f>), dim3(c.k.ntiles * split),
-                               dim3(kThreads3f), 0, s, c.k, a, c.fields, c.bn, J, split);
+            const int64_t units = (int64_t)c.k.ntiles * split;
+            hipLaunchKernelGGL((k_particle_step3<float, kThreads3f, kChunk3f, true>),
+                               dim3((unsigned)std::min<int64_t>(kCus, units)), dim3(kThreads3f), 0, s,
+                               Step3Args{c.k, a, c.fields, c.bn, J, split});
             hipLaunchKernelGGL((k_migrants3<float, kThreadsMigf>), grid, dim3(kThreadsMigf), 0, s, c.k, a,
                                c.fields, c.bn, J);
         }

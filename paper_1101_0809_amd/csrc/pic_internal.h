@@ -15,6 +15,7 @@ constexpr double kPi = 3.14159265358979323846;
 constexpr int kMaxSpecies = 4;
 constexpr size_t kAlign = 256;  // alignment of every carved buffer
 constexpr int kCus = 256;  // MI355X: compute units
+constexpr int kWorkStride = 32;  // work counters lie in cache lines of their own
 constexpr int kXcds = 8;  // MI355X: 8 accelerator complex dies, each with its own L2
 
 // Tile edge (cells) of the particle-step kernel, per dimensionality.
@@ -141,6 +142,7 @@ struct Ctx {
     unsigned long long* counters = nullptr;  // [0] range errors, [1] fallback particles,
                                              // [2] particles processed, [3] migrants
     unsigned int* mig_n = nullptr;  // per-tile migrant bucket counters (3D particle step)
+    unsigned int* work = nullptr;   // per species and XCD: units of the 3D step taken, cleared each step
     uint32_t nkeys = 0;
     Species sp[kMaxSpecies];
     int nsp = 0;

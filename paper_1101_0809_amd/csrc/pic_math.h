@@ -827,6 +827,7 @@ struct StepArgs {
     uint32_t* mig;
     unsigned int* mig_n;
     uint32_t mig_cap;
+    unsigned int* work;  // 3D: the XCDs' work counters (kXcds x kWorkStride, zero at the start of the step)
 };
 
 __device__ __forceinline__ int wrapi(int v, int n)

@@ -22,10 +22,10 @@ struct Columns {
     static constexpr int LANES = ALIGNED ? 16 : LX;  // lanes of a row
     static constexpr int CH = (LANES * LY + 63) / 64;
     int off[CH], lds[CH];
-    __device__ __forceinline__ Columns(const GridK& g, int fx, int fy, bool small)
+    __device__ __forceinline__ Columns(const GridK& g, int fx, int fy, bool small, int tid = (int)threadIdx.x)
     {
         auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
-        const int lane = (int)threadIdx.x & 63;
+        const int lane = tid & 63;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int e = lane + 64 * c, ly = e / LANES, lx = e - ly * LANES;
@@ -76,18 +76,22 @@ __device__ __forceinline__ void stage_planes(const Cols& cols, Src src, Dst dst)
 }
 
 // Adds the non-zero entries of planes 0 .. NP - 1 of an LDS region, src(t), to
-// the grid planes dst(t) with global atomics, by all NT threads.
-template <int NP, int NT, class Cols, class Src, class Dst>
+// the grid planes dst(t) with global atomics, by all NT threads; CLEAR: and
+// clears them.
+template <int NP, int NT, bool CLEAR = false, class Cols, class Src, class Dst>
 __device__ __forceinline__ void flush_planes(const Cols& cols, Src src, Dst dst)
 {
     for (int t = wave_index(); t < NP; t += NT / 64) {
-        const double* s = src(t);
+        double* s = src(t);
         double* o = dst(t);
 #pragma unroll
         for (int c = 0; c < Cols::CH; ++c)
             if (cols.off[c] >= 0) {
                 const double v = s[cols.lds[c]];
-                if (v != 0.0) unsafeAtomicAdd(o + cols.off[c], v);
+                if (v != 0.0) {
+                    unsafeAtomicAdd(o + cols.off[c], v);
+                    if (CLEAR) s[cols.lds[c]] = 0.0;
+                }
             }
     }
 }

@@ -57,6 +57,29 @@ def test_3d_step_shares_a_tile(n, ppc, precision, tols):
     _compare(sim, st, wl, *tols)
 
 
+@pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
+@pytest.mark.parametrize("n,slab", [((64, 48, 56), (20, 44)), ((65, 41, 67), (0, 9)), ((64, 64, 40), None)])
+def test_3d_more_tiles_than_workgroups(n, slab, precision, tols):
+    """3D grids of more tiles than the chip has CUs, two species: with tiles
+    without particles (also the ones that a workgroup begins with), with all
+    particles in one XCD's share of the tiles or two, and filled evenly."""
+    import oracle
+    from paper_1101_0809_amd import Sim
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=n[0], ny=n[1], nz=n[2], ppc=1, w_th=(0.2,) * 3, slab=slab)
+    e = picgen.electrons(wl)
+    sim = Sim(*n, wl.dt, precision=precision, sort_every=3)
+    parts = []
+    for k, (q, m) in enumerate([(e.q, e.m), (-e.q, 2.0 * e.m)]):
+        sim.add_species(q, m, e.n)
+        x, w, weight = e.x.copy(), e.w * (1 - 2 * k), e.weight * (1 - 0.5 * k)
+        sim.load(k, x, w, weight)
+        parts.append(oracle.Species(x, w, weight, q=q, m=m))
+    st = oracle.State(oracle.Grid(*n, wl.dt), parts)
+    sim.step(5)
+    st.step(5)
+    _compare(sim, st, wl, *tols)
+
+
 @pytest.mark.parametrize("n,options", [
     ((13, 10, 11), dict()), ((9, 15, 14), dict(precision="fp32c")), ((13, 10, 11), dict(order=2)),
     ((13, 10, 11), dict(interp="conventional")), ((17, 31, 1), dict()), ((25, 19, 1), dict(precision="fp32c")),
