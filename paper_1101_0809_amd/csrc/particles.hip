@@ -710,8 +710,8 @@ __device__ __forceinline__ int next_unit3(const Step3Args& s, int lane)
 // crossings, and a tile without particles costs a look at its slots, not a
 // workgroup of its own with its 160 KB of LDS.  In FP32 mode that takes 64^3 x 8
 // from 1619 to 1594 us for 10 steps, 128^3 x 32 x 2 species from 114.0 to 113.4
-// ms for 20, and a slab of 51 per cell on a fifth of 256 x 128 x 128 from 17.3 to
-// 16.6 ms for 20.  In FP64 the loop costs the particle code its registers (64^3 x
+// ms for 20, and 16.8 million electrons in half of 128^3 under a laser from 17.3
+// to 16.6 ms for 10.  In FP64 the loop costs the particle code its registers (64^3 x
 // 8 1944 us against 1895, 128^3 x 8 14.63 ms against 14.29): a unit each.
 template <class R, int NT, int KC, bool PERSIST>
 __global__ __launch_bounds__(NT) void k_particle_step3(Step3Args kernarg)

@@ -67,7 +67,7 @@ constexpr int lane_classes() { return sizeof(R) == 8 ? 16 : 32; }
 // Class of a cell at offset rel from its tile's first cell (rel inside the
 // tile region): its field-tile base index modulo the lane classes.
 template <class R>
-__host__ __device__ inline int cell_class3(int rx, int ry, int rz)
+__host__ __device__ constexpr int cell_class3(int rx, int ry, int rz)
 {
     using L = Tile3<R>;
     return ((rx + 1 + L::MX) + (ry + 1 + L::M) * L::FROW + (rz + 1 + L::M) * L::FPLANE) & (lane_classes<R>() - 1);

@@ -80,6 +80,57 @@ def test_3d_more_tiles_than_workgroups(n, slab, precision, tols):
     _compare(sim, st, wl, *tols)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32c"])
+@pytest.mark.parametrize("n,count", [((16, 8, 8), 80_000), ((168, 168, 168), 300_000), ((9, 17, 8), 7),
+                                     ((32, 16, 1), 80_000), ((1040, 1040, 1), 300_000), ((17, 16, 1), 5)])
+def test_sort_moves_particles_whole(n, count, precision):
+    """The sort with more particles in a tile than its histogram holds in
+    registers, with more groups of tiles than a workgroup has threads, and with
+    nearly no particles, from a fresh load and after the particles have moved:
+    every particle keeps its values, tiles are in order, and the order inside a
+    tile is that of test_sort_order (lane classes in as many home slots as the
+    counts allow in 3D, rank levels in 2D)."""
+    import numpy as np
+    from paper_1101_0809_amd import Sim
+    dims = 2 if n[2] == 1 else 3
+    T = 16 if dims == 2 else 8
+    rng = np.random.Generator(np.random.PCG64(23))
+    x = rng.uniform(0, 1, (3, count)) * np.array(n, dtype=float)[:, None]
+    w, weight = rng.normal(0, 0.4, (3, count)), rng.uniform(0.5, 1.5, count) * 1e-6
+    sim = Sim(*n, 0.4, dims=dims, precision=precision, sort_every=0)
+    sim.add_species(-1.0, 1.0, count)
+    sim.load(0, x, w, weight)
+    for moves in range(2):
+        before = sim.particles(0)
+        sim.sort()
+        after = sim.particles(0)
+        for a, b in zip(before, after):
+            assert np.array_equal(a, b)
+        xs, _, _, ids = sim.particles(0, raw=True)
+        assert np.array_equal(np.sort(ids), np.arange(count))
+        cell = np.floor(xs).astype(np.int64)
+        if dims == 2:
+            cell[2] = 0
+        nt = [-(-k // T) for k in n]
+        tile = ((cell[2] // T) * nt[1] + cell[1] // T) * nt[0] + cell[0] // T
+        assert np.all(np.diff(tile) >= 0)
+        l = cell % T
+        for t in np.unique(tile)[:40]:
+            sel = tile == t
+            n_t, slot = int(sel.sum()), np.arange(int(sel.sum()))
+            if dims == 3:
+                C, row, plane, o = (16, 14, 168, 2) if precision == "fp64" else (32, 18, 216, 4)
+                k = ((l[0] + o) + row * (l[1] + 2) + plane * (l[2] + 2))[sel] % C
+                counts, rows = np.bincount(k, minlength=C), (n_t - np.arange(C) + C - 1) // C
+                assert (k == slot % C).sum() == np.minimum(counts, rows).sum()
+            else:
+                local = (l[1] * T + l[0])[sel]
+                level = np.concatenate([[0], np.cumsum(np.diff(local) <= 0)])
+                counts = np.bincount(local, minlength=T * T)
+                assert np.array_equal(np.bincount(level), [(counts > v).sum() for v in range(counts.max())])
+        sim.step(2)
+
+
 @pytest.mark.parametrize("n,options", [
     ((13, 10, 11), dict()), ((9, 15, 14), dict(precision="fp32c")), ((13, 10, 11), dict(order=2)),
     ((13, 10, 11), dict(interp="conventional")), ((17, 31, 1), dict()), ((25, 19, 1), dict(precision="fp32c")),
