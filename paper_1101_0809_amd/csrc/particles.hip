@@ -386,6 +386,12 @@ constexpr int64_t kUnmapped = (int64_t)1 << 62;  // crossing entry not in the cl
 // flushing its current cost about as much as 8 particles on the global path
 // (144 global atomics each).
 constexpr unsigned kMigLds = 8;
+// One this full is advanced in class rows: in storage order its LDS accesses
+// conflict (as much as a random order's), which with two waves or more of
+// particles costs more than the ordering (5 us a tile).  16.8 million electrons
+// in half of 128^3 under a laser, 4.3% migrants: 3.25 -> 2.77 ms of 16.2 for 10
+// steps; 64^3 x 8, tens in a bucket, in rows: 1858.5 -> 1861.5 us, so not there.
+constexpr unsigned kMigRows = 128;
 
 // Stage E^n and B^n of the 3D tile region into LDS.  The region is a set of
 // rows of at most 16 x values (69 stored planes x LFY rows): 16 lanes take a
@@ -1143,6 +1149,7 @@ __global__ __launch_bounds__(NT) void k_migrants3(GridK g, StepArgs a, const dou
     constexpr int NJ = TL::NJ;
     __shared__ R sf[kFieldPlanes3 * TL::FPLANE];
     __shared__ LdsJ<R, 3 * NJ> sj;
+    __shared__ ClassRows<NT, 1, lane_classes<R>()> rows;
     __shared__ unsigned int n_global;
 
     const int tile = xcd_tile(blockIdx.x, g.ntiles);
@@ -1167,18 +1174,12 @@ __global__ __launch_bounds__(NT) void k_migrants3(GridK g, StepArgs a, const dou
     for (int e = threadIdx.x; e < 3 * NJ; e += NT) sj.zero(e);
     if (threadIdx.x == 0) n_global = 0;
     __syncthreads();
-    unsigned my_global = 0;
-    for (unsigned q = threadIdx.x; q < cnt; q += NT) {
-        const int64_t p = bucket[q];
+    auto advance = [&](int64_t p) {
         int i0[3];
         R d0[3];
         PosIO<R, 3>::load(a, p, i0, d0);
         int rel[3];
-        if (!relative3<R>(g, T0, i0, rel)) {  // not a cell of this tile (non-finite input): global memory
-            advance_global3<R>(g, a, p, fields, bfield, Jg);
-            ++my_global;
-            continue;
-        }
+        relative3<R>(g, T0, i0, rel);
         Axis<R> ax0[3];
         R d1[3], qp;
         int delta[3];
@@ -1198,9 +1199,37 @@ __global__ __launch_bounds__(NT) void k_migrants3(GridK g, StepArgs a, const dou
             sj.add(comp * NJ + jb + ix + iy * SJY + iz * SJZ, v);
         };
         deposit3<R>(dm, dp, jfac, S);
+    };
+    auto inside = [&](int64_t p, int& cls) -> bool {
+        int ci[3], rel[3];
+        PosIO<R, 3>::cell(a, p, ci);
+        if (!relative3<R>(g, T0, ci, rel)) return false;
+        cls = cell_class3<R>(rel[0], rel[1], rel[2]);
+        return true;
+    };
+    auto cls_of = [&](int64_t p) -> int {
+        int cls;
+        if (inside(p, cls)) return cls;
+        atomicAdd(&n_global, 1u);
+        return -1;
+    };
+    for (unsigned cb = 0; cb < cnt; cb += NT) {
+        const int m = (int)min(cnt - cb, (unsigned)NT), t = (int)threadIdx.x;
+        int sl = -1;
+        if (cnt >= kMigRows) {
+            const int n = order_rows(rows, m, [&](int q) -> int { return cls_of(bucket[cb + q]); });
+            if (t < n) sl = rows.perm[t];
+        } else if (t < m && cls_of(bucket[cb + t]) >= 0) {
+            sl = t;
+        }
+        if (sl >= 0) advance(bucket[cb + sl]);
+        __syncthreads();  // the order is used up
     }
-    if (my_global) atomicAdd(&n_global, my_global);
-    __syncthreads();
+    if (n_global)  // not cells of this tile (non-finite input): global memory
+        for (unsigned q = threadIdx.x; q < cnt; q += NT) {
+            int cls;
+            if (!inside(bucket[q], cls)) advance_global3<R>(g, a, bucket[q], fields, bfield, Jg);
+        }
     flush_current3<R, NT>(g, T0, sj, Jg, small, (int)threadIdx.x);
     if (threadIdx.x == 0) {
         a.mig_n[tile] = 0;

@@ -131,6 +131,34 @@ def test_sort_moves_particles_whole(n, count, precision):
         sim.step(2)
 
 
+@pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
+@pytest.mark.parametrize("axis,ppc", [(0, 0.5), (1, 2), (2, 12)])
+def test_3d_migrant_buckets(axis, ppc, precision, tols):
+    """3D: a fast drift along one axis without a sort in between, so that a
+    tile's bucket of migrants grows through the sizes at which they are taken
+    from global memory, in order of arrival and in class rows, up to several
+    chunks of rows."""
+    import numpy as np
+    import oracle
+    from paper_1101_0809_amd import Sim
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=24, ny=25, nz=24, ppc=1, w_th=(0.05,) * 3)
+    e = picgen.electrons(wl)
+    rng = np.random.Generator(np.random.PCG64(31))
+    count = int(e.n * ppc)
+    x = rng.uniform(0, 1, (3, count)) * np.array([[wl.nx], [wl.ny], [wl.nz]], dtype=float)
+    w = rng.normal(0, 0.05, (3, count))
+    w[axis] += 3.0
+    weight = np.full(count, float(e.weight[0]) / ppc)
+    sim = Sim(wl.nx, wl.ny, wl.nz, wl.dt, precision=precision, sort_every=30)
+    sim.add_species(e.q, e.m, count)
+    sim.load(0, x, w, weight)
+    st = oracle.State(oracle.Grid(wl.nx, wl.ny, wl.nz, wl.dt), [oracle.Species(x, w, weight, q=e.q, m=e.m)])
+    sim.step(12)
+    st.step(12)
+    assert sim.migrant_fraction() > 0  # the mean over the steps: the first ones have none
+    _compare(sim, st, wl, *tols)
+
+
 @pytest.mark.parametrize("n,options", [
     ((13, 10, 11), dict()), ((9, 15, 14), dict(precision="fp32c")), ((13, 10, 11), dict(order=2)),
     ((13, 10, 11), dict(interp="conventional")), ((17, 31, 1), dict()), ((25, 19, 1), dict(precision="fp32c")),
