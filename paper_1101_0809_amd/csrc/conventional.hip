@@ -130,6 +130,7 @@ constexpr int kCvStill = 64, kCvInside = 128;
 // window: LDS bank conflicts were 36 and 18% of the CU-busy cycles in storage
 // order.  82 and 58 -> 71 and 49 us at 64^3 x 2 per cell; 20 steps of 64^3 x 6
 // per cell with the energies 6.25 -> 5.5 ms, hot (w_th = 0.2) 13.3 -> 10.0 ms.
+// All fields of a tile in flight at once: 20 steps of 64^3 x 2 2830 -> 2655 us.
 __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, PartArrays spare,
                                                      const double* __restrict__ fields,
                                                      const double* __restrict__ bfield, int split)
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
     {
         const bool small = nx < LF || ny < LF || nz < LF;
         const Columns<LF, LF, LF> cols(g, T0[0] - 1 - M, T0[1] - 1 - M, small);
-        stage_planes<6 * LF, NT, 2, double>(
+        stage_planes<6 * LF, NT, kAllPlanes<6 * LF, NT>, double>(
             cols,
             [&](int t) {
                 const int comp = t / LF;

@@ -187,7 +187,8 @@ __global__ __launch_bounds__(kO2NT2) void k_step_o2(GridK g, StepArgs a, const d
 // passes from 86 and 98 to 76 and 76 us at 64^3 x 2 per cell (half of it the
 // staging and flush of 1024 particles' tiles), and 20 steps of 64^3 x 6 from
 // 11.6 to 7.0 ms with the energies.  Pass 1 has two waves per SIMD to hide
-// its latencies: 768 threads spill 43 registers and gain nothing.
+// its latencies: 768 threads spill 43 registers and gain nothing.  All fields
+// of a tile in flight at once: 20 steps of 64^3 x 2 3530 -> 3300 us.
 constexpr int kO2M3a = 1, kO2M3b = 2;
 constexpr int kO2NTa = 512, kO2Ua = 4;  // pass 1 (200 VGPRs): threads, slots per thread ordered at a time
 constexpr int kO2NTb = 768, kO2Ub = 2;  // pass 2 (150 VGPRs)
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kO2NTa) void k_push_o2_3d(GridK g, StepArgs a, Part
     {
         const bool small = nx < LF || ny < LF || nz < LF;
         const Columns<LF, LF, LF> cols(g, T0[0] - 2 - M, T0[1] - 2 - M, small);
-        stage_planes<6 * LF, NT, 2, double>(
+        stage_planes<6 * LF, NT, kAllPlanes<6 * LF, NT>, double>(
             cols,
             [&](int t) {
                 const int comp = t / LF;

@@ -410,7 +410,10 @@ __device__ __forceinline__ void stage_fields3(const GridK& g, const int T0[3], c
     constexpr int SFY = TL::FROW, SFZ = TL::FPLANE;
     constexpr int RPP = NT / 16;                 // rows per pass of the workgroup
     constexpr int NROWS = kFieldPlanes3 * LFY;  // (stored plane, row) pairs
-    constexpr int SK = 7;
+    // rows of a thread in flight: all 18 in FP64 (64^3 x 8 1857 -> 1844 us for 10
+    // steps, 24^3 x 8 417 -> 407); in FP32 mode 7 of 13, with more the loop
+    // around it compiles to a slower one (64^3 x 8 1546 -> 1556 us)
+    constexpr int SK = sizeof(R) == 8 ? (NROWS + RPP - 1) / RPP : 7;
     static_assert(LFX <= 16 && NT % 64 == 0, "a field-tile row fits 16 lanes");
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
