@@ -6,9 +6,10 @@
 // so that div_h E = 4 pi rho cell by cell.  The operator is symmetric and
 // positive definite on grid functions of zero mean; the right side has its
 // mean removed (a uniform background) and conjugate gradients run on that
-// subspace.  Scalars (alpha, beta, residual norms) stay on the device: each
-// iteration is two launches with no host round trip; the host reads the
-// residual every kCheck iterations to stop.
+// subspace.  Scalars (alpha, beta, residual norms) stay on the device.  Grids
+// of up to 524288 cells take all iterations in one launch (k_cg_run); on others
+// each iteration is two launches with no host round trip, and the host reads
+// the residual every kCheck iterations to stop.
 //
 // What bounds an iteration on the usual grids is launches, not bytes (64^3:
 // ten planes of 2 MB, cache resident).  The reductions are therefore finished
@@ -18,7 +19,9 @@
 // Six launches became two: 32 -> 14 us per iteration at 64^3 (the check of the
 // residual included), 68 -> 42 us at 128^3.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <cstring>
 
 #include "pic_internal.h"
 
@@ -30,7 +33,8 @@ constexpr int kBlocks = 1024;  // reduction workgroups
 constexpr int kCheck = 16;
 
 // device scalars: [0], [1] r.r of even and odd iterations  [2] target r.r
-// [4] b.b  [5] sum rho  [6] r.r for the host
+// [4] b.b  [5] sum rho  [6] r.r for the host  [7] r.r before it (k_cg_run)
+// [8], [9] status of k_cg_run  [16] .. its slots
 
 // Sum of v over the workgroup, in a fixed order (a binary tree: across the
 // waves in LDS, then inside the first wave), returned to every thread.
@@ -212,6 +216,198 @@ __global__ __launch_bounds__(kThreads) void k_cg_update(int64_t n, int it, int n
     if (threadIdx.x == 0) part_r[blockIdx.x] = t;
 }
 
+// ---------------------------------------------------------------------------
+// The iterations in one launch, for grids whose state fits the registers of
+// one workgroup per CU.  A workgroup keeps kRunThreads x CPT consecutive cells:
+// r (also in LDS, for neighbours among them, and in memory, for the other
+// workgroups), phi, and p of each cell and of its six neighbours, which is
+// formed again from the neighbours' r as in k_cg_apply, so that r is all that
+// is exchanged.  In place of the two kernel boundaries of an iteration the
+// workgroups exchange their partial sums: each stores its own in a slot and
+// reads everybody's, which is at once the reduction (in the same order
+// everywhere) and the barrier.  Slots and r go past the XCDs' L2s: stored and
+// loaded by atomics of agent scope, each wave's stores of r having ended before
+// its workgroup's slot is written.  Bound by those round trips (three or four of
+// about a microsecond per exchange).  A solve at 24^3, 64^3 and 80^3, and at
+// 128^2 and 512^2: 1.17, 3.77, 6.17, 3.77, 21.0 -> 0.51, 2.07, 3.60, 1.22, 10.0
+// ms.  Larger grids (128^3: 42 us an iteration in two launches) would spill, and
+// wait less for launches.
+// ---------------------------------------------------------------------------
+constexpr int kRunThreads = 1024, kRunCells = 2;  // cells per thread at most (4 spill)
+constexpr int kRunIters = 2048;                  // iterations of a launch at most
+constexpr int kRunPolls = 1 << 15;               // reads of a slot (a microsecond each) before giving up
+constexpr unsigned long long kEmpty = 0xfff8dead00000001ull;  // a slot not written yet (a NaN no sum yields)
+
+// status[0]: iterations done; status[1]: nonzero if a workgroup gave up.
+__global__ void k_run_prepare(unsigned long long* slots, int n, unsigned long long* status)
+{
+    const int t = blockIdx.x * kThreads + threadIdx.x;
+    if (t < n) slots[t] = kEmpty;
+    if (t < 2) status[t] = 0;
+}
+
+__device__ __forceinline__ void store_agent(unsigned long long* p, unsigned long long v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_agent(const double* p)
+{
+    return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long*)p, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// v of the lane that the DPP control CTRL names, 0.0 where there is none or the
+// row (of 16 lanes) is not in ROWS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
+}
+
+// Sum over the wave, in lane 63 (four row shifts and two row broadcasts, which
+// need no LDS: the sums are on the path between the workgroups).
+__device__ __forceinline__ double wave_sum63(double v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v);  // row_shr:1
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Iterations it0 .. it1 - 1, fewer once r.r has reached the target s[2].  s[6]:
+// r.r before and after.
+template <int CPT>
+__global__ __launch_bounds__(kRunThreads) void k_cg_run(GridK g, int it0, int it1, double* __restrict__ s,
+                                                        unsigned long long* slots, unsigned long long* status,
+                                                        double* r, double* __restrict__ phi, double* __restrict__ p)
+{
+    constexpr int NT = kRunThreads, NW = NT / 64, K = NT * CPT;
+    static_assert(kCus <= NT && kCus % 64 == 0, "a thread per slot");
+    __shared__ double lr[K], mine[NW], all[NW];
+    __shared__ int gave_up;
+    const int t = threadIdx.x, wv = t >> 6;
+    const int W = gridDim.x;
+    const uint32_t n = (uint32_t)g.ncell, base = blockIdx.x * K;
+    if (t == 0) gave_up = 0;
+    // Publish the workgroup's sum of v for epoch e, after the stores of all of
+    // its waves; clear the slot of epoch e + 2 (that of e - 2, which everybody
+    // has read: everybody has published e - 1).
+    auto publish = [&](double v, int e) {
+        v = wave_sum63(v);
+        if ((t & 63) == 63) mine[wv] = v;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (t == 0) {
+            double sum = 0.0;
+            for (int w = 0; w < NW; ++w) sum += mine[w];
+            store_agent(slots + (e & 3) * kCus + blockIdx.x,
+                        sum != sum ? 0x7ff8000000000000ull : (unsigned long long)__double_as_longlong(sum));
+            store_agent(slots + ((e + 2) & 3) * kCus + blockIdx.x, kEmpty);
+        }
+    };
+    // Sum of everybody's sums of epoch e; false if one did not come.
+    auto collect = [&](int e, double& sum) -> bool {
+        double v = 0.0;
+        if (t < W) {
+            const double* slot = (const double*)slots + (e & 3) * kCus + t;
+            int polls = 0;
+            do v = load_agent(slot);
+            while ((unsigned long long)__double_as_longlong(v) == kEmpty && ++polls < kRunPolls);
+            if ((unsigned long long)__double_as_longlong(v) == kEmpty) gave_up = 1;
+        }
+        if (t < kCus) {
+            v = wave_sum63(v);
+            if ((t & 63) == 63) all[wv] = v;
+        }
+        __syncthreads();
+        sum = 0.0;
+        for (int w = 0; w < kCus / 64; ++w) sum += all[w];
+        return !gave_up;
+    };
+
+    double rv[CPT], f[CPT], pv[CPT][7];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        const uint32_t c = base + t + u * NT;
+        rv[u] = f[u] = 0.0;
+        for (int k = 0; k < 7; ++k) pv[u][k] = 0.0;
+        if (c < n) {
+            rv[u] = r[c];
+            f[u] = phi[c];
+            if (it0 > 0) {
+                const Star st = star_of(g, c);
+#pragma unroll
+                for (int k = 0; k < 7; ++k) pv[u][k] = p[st.q[k]];
+            }
+        }
+        lr[t + u * NT] = rv[u];
+    }
+    __syncthreads();
+    const double target = s[2];
+    double rr = s[6], rr_old = s[7];
+    int it = it0, e = 0;
+    bool good = true;
+    while (rr > target && it < it1) {
+        const double beta = it == 0 ? 0.0 : rr / rr_old;
+        double ap[CPT], v = 0.0;
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) {
+            const uint32_t c = base + t + u * NT;
+            ap[u] = 0.0;
+            if (c >= n) continue;
+            const Star st = star_of(g, c);
+            double x[7];
+            x[0] = rv[u];
+#pragma unroll
+            for (int k = 1; k < 7; ++k) x[k] = st.q[k] - base < (uint32_t)K ? lr[st.q[k] - base] : load_agent(r + st.q[k]);
+#pragma unroll
+            for (int k = 0; k < 7; ++k) pv[u][k] = it == 0 ? x[k] : x[k] + beta * pv[u][k];
+            ap[u] = neg_lap(g, pv[u]);
+            v += pv[u][0] * ap[u];
+        }
+        publish(v, e);
+        double pap;
+        good = collect(e++, pap);
+        if (!good) break;
+        const double alpha = pap > 0.0 ? rr / pap : 0.0;
+        v = 0.0;
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) {
+            const uint32_t c = base + t + u * NT;
+            f[u] += alpha * pv[u][0];
+            rv[u] -= alpha * ap[u];
+            v += rv[u] * rv[u];
+            if (c < n) store_agent((unsigned long long*)r + c, (unsigned long long)__double_as_longlong(rv[u]));
+            lr[t + u * NT] = rv[u];
+        }
+        publish(v, e);
+        rr_old = rr;
+        good = collect(e++, rr);
+        if (!good) break;
+        ++it;
+    }
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {
+        const uint32_t c = base + t + u * NT;
+        if (c < n) {
+            phi[c] = f[u];
+            p[c] = pv[u][0];
+        }
+    }
+    if (t == 0 && !good) atomicExch(&status[1], 1ull);
+    if (t == 0 && blockIdx.x == 0) {
+        s[6] = rr;
+        s[7] = rr_old;
+        status[0] = (unsigned long long)it;
+    }
+}
+
 // s[dst] = f s[src]
 __global__ void k_scale(double* s, int dst, int src, double f)
 {
@@ -245,6 +441,31 @@ __global__ __launch_bounds__(kThreads) void k_add_const(double* __restrict__ x, 
     for (int64_t p = (int64_t)blockIdx.x * kThreads + threadIdx.x; p < n; p += (int64_t)gridDim.x * kThreads) x[p] += v;
 }
 
+// The one-launch form of a device is one solve's at a time: of two, each could
+// hold half of the CUs and wait for the other.  The solve that finds it taken
+// (from another thread) runs in separate launches.
+class RunTurn {
+  public:
+    RunTurn()
+    {
+        static std::atomic<bool> taken[kDevices];
+        int dev = -1;
+        if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kDevices && !taken[dev].exchange(true))
+            flag_ = &taken[dev];
+    }
+    ~RunTurn()
+    {
+        if (flag_) flag_->store(false);
+    }
+    RunTurn(const RunTurn&) = delete;
+    RunTurn& operator=(const RunTurn&) = delete;
+    bool mine() const { return flag_ != nullptr; }
+
+  private:
+    static constexpr int kDevices = 64;
+    std::atomic<bool>* flag_ = nullptr;
+};
+
 unsigned grid_for(int64_t n) { return (unsigned)std::min<int64_t>(kBlocks, (n + kThreads - 1) / kThreads); }
 
 }  // namespace
@@ -271,7 +492,8 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
     hipLaunchKernelGGL(k_cg_init, dim3(gb), dim3(kThreads), 0, s, n, rho, sc, phi, r, part);
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(kThreads), 0, s, part, nb, sc, 4);
     hipLaunchKernelGGL(k_scale, dim3(1), dim3(64), 0, s, sc, 2, 4, tol * tol);  // target r.r
-    double host[7] = {0, 0, 0, 0, 0, 0, 0};
+    const unsigned long long* status = (const unsigned long long*)(sc + 8);
+    double host[10] = {0};
     hipError_t e = hipMemcpyAsync(host, sc, sizeof(host), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
@@ -279,6 +501,40 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
     int64_t it = 0;
     double rr = bb;
     const double target = tol * tol * bb;
+    // In one launch: one workgroup per CU at most, all of which have to be
+    // running at once.  If one is kept waiting too long (by another process on
+    // the GPU) all give up, and the solve starts again in separate launches.
+    const RunTurn turn;
+    const int cells = (int)((n + (int64_t)kCus * kRunThreads - 1) / ((int64_t)kCus * kRunThreads));
+    if (turn.mine() && bb > 0.0 && rr > target && it < max_iter && n <= (int64_t)kCus * kRunThreads * kRunCells) {
+        unsigned long long* slots = (unsigned long long*)(sc + 16);
+        const int cpt = cells <= 1 ? 1 : kRunCells;
+        const dim3 grid((unsigned)((n + kRunThreads * cpt - 1) / (kRunThreads * cpt)));
+        hipLaunchKernelGGL(k_scale, dim3(1), dim3(64), 0, s, sc, 6, 4, 1.0);
+        while (rr > target && it < max_iter) {
+            hipLaunchKernelGGL(k_run_prepare, dim3(4 * kCus / kThreads), dim3(kThreads), 0, s, slots, 4 * kCus,
+                               (unsigned long long*)status);
+            const int last = (int)std::min<int64_t>(max_iter, it + kRunIters);
+            auto* run = cpt == 1 ? k_cg_run<1> : k_cg_run<kRunCells>;
+            hipLaunchKernelGGL(run, grid, dim3(kRunThreads), 0, s, c.k, (int)it, last, sc, slots,
+                               (unsigned long long*)status, r, phi, p[0]);
+            e = hipMemcpyAsync(host, sc, sizeof(host), hipMemcpyDeviceToHost, s);
+            if (e == hipSuccess) e = hipStreamSynchronize(s);
+            if (e != hipSuccess) return e;
+            unsigned long long st[2];
+            std::memcpy(st, host + 8, sizeof(st));
+            if (st[1]) {
+                it = 0;
+                rr = bb;
+                hipLaunchKernelGGL(k_cg_init, dim3(gb), dim3(kThreads), 0, s, n, rho, sc, phi, r, part);
+                break;
+            }
+            it = (int64_t)st[0];
+            rr = host[6];
+        }
+        // counted in whole checks, as by the launches below
+        if (!(rr > target)) it = std::min(max_iter, (it + kCheck - 1) / kCheck * kCheck);
+    }
     while (bb > 0.0 && rr > target && it < max_iter) {
         for (int q = 0; q < kCheck && it < max_iter; ++q, ++it) {
             hipLaunchKernelGGL(k_cg_apply, dim3(gb), dim3(kThreads), 0, s, c.k, (int)it, nb, sc, part, r, p[it & 1],

@@ -234,3 +234,59 @@ def test_2d_step_in_class_rows(nx, ny, ppc, w_th, precision, tols):
                                                     drift=0.2, bext=(0.0, 0.0, 0.05))
     sim, st, _ = _run_pair(wl, precision, 12, sort_every=6)
     _compare(sim, st, wl, *tols)
+
+
+def _poisson_case(n, seed):
+    import numpy as np
+    import oracle
+    from oracle import poisson
+    from paper_1101_0809_amd import Sim
+    rng = np.random.Generator(np.random.PCG64(seed))
+    count = 3000
+    x = rng.uniform(0, 1, (3, count)) * np.array(n, dtype=float)[:, None]
+    w, weight = np.zeros((3, count)), np.full(count, 1e-3)
+    sim = Sim(*n, 0.4, dims=2 if n[2] == 1 else 3)
+    sim.add_species(-1.0, 1.0, count)
+    sim.load(0, x, w, weight)
+    g = oracle.Grid(*n, 0.4)
+    return sim, poisson.e_of_phi(g, poisson.solve(g, oracle.State(g, [oracle.Species(x, w, weight, q=-1.0, m=1.0)]).rho()))
+
+
+@pytest.mark.parametrize("n", [(16, 8, 8), (41, 25, 1), (7, 5, 1), (64, 64, 65), (128, 64, 64), (128, 64, 65)])
+def test_poisson_one_launch(n):
+    """The solve in one launch with exactly one workgroup, one cell more, a
+    partly filled one, two cells per thread, its largest grid, and the next one
+    (in separate launches), as in test_poisson_cells_per_thread; solved twice."""
+    import numpy as np
+    sim, E = _poisson_case(n, 29)
+    for _ in range(2):
+        it, res = sim.solve_poisson(neutralize=True)
+        assert res <= 1e-13 and it % 16 == 0
+        assert np.linalg.norm(sim.fields_numpy()[:3] - E) <= 1e-9 * np.linalg.norm(E)
+
+
+def test_poisson_from_two_threads():
+    """Two threads on streams of their own: the second of two solves at a time
+    takes separate launches."""
+    import threading
+    import numpy as np
+    import torch
+    cases = [_poisson_case((48, 48, 48), 31), _poisson_case((64, 64, 64), 37)]
+    torch.cuda.synchronize()
+    done = [0, 0]
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(4):
+                _, res = cases[k][0].solve_poisson(neutralize=True)
+                done[k] += res <= 1e-13
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert done == [4, 4]
+    for sim, E in cases:
+        assert np.linalg.norm(sim.fields_numpy()[:3] - E) <= 1e-9 * np.linalg.norm(E)
