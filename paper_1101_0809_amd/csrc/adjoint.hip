@@ -1325,6 +1325,19 @@ __global__ __launch_bounds__(256) void k_permute(const int64_t* __restrict__ id_
     }
 }
 
+// out[id[k]] = in[k]: from a record's order to id order, an array per grid row.
+__global__ __launch_bounds__(256) void k_to_id_order(const int64_t* __restrict__ id, int64_t n,
+                                                  const double* __restrict__ in_x, const double* __restrict__ in_w,
+                                                  double* __restrict__ out_x, double* __restrict__ out_w)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= n) return;
+    const int row = (int)blockIdx.y % 3;
+    const double* in = (blockIdx.y < 3 ? in_x : in_w) + row * n;
+    double* out = (blockIdx.y < 3 ? out_x : out_w) + row * n;
+    out[id[k]] = in[k];
+}
+
 }  // namespace
 
 size_t adjoint_record_bytes(const Ctx& c) { return carve_record(c, nullptr, nullptr); }
@@ -1367,6 +1380,11 @@ hipError_t launch_adjoint_reorder(Ctx& c, const void* from, const void* to, cons
         Species& sp = c.sp[i];
         if (!sp.d.mobile || sp.n == 0) continue;
         const unsigned pb = (unsigned)((sp.n + 255) / 256);
+        if (from && !to) {
+            hipLaunchKernelGGL(k_to_id_order, dim3(pb, 6), dim3(256), 0, s, vf.sp[i].id, sp.n, in_x[i], in_w[i],
+                               out_x[i], out_w[i]);
+            continue;
+        }
         uint32_t* pos = nullptr;
         if (from) {
             pos = sp.key;  // sort scratch, capacity >= n entries
