@@ -1549,15 +1549,16 @@ constexpr int kMargin2 = 2;
 
 // Workgroups per tile of the 2D3V step: enough to fill the chip four times over
 // (as many fit a CU's LDS) with two particles per thread each, or once with a
-// particle per two threads.  us per step at 1, 2, 3, 4, 8 workgroups per tile:
-// 78, 61, 56, 57, 69 for 256^2 x 16 per cell (4 taken); 35, 35, 38, 41, 51 for
-// 256^2 x 4 (2 taken); 40, 30, 28, 27, 24 for 100 x 70 x 8 (7 taken); 164, 173,
-// 177, 186, 223 for 512^2 x 16 (1 taken).
+// particle per eight threads (with 128, 64 and 32 particles to a workgroup 32^2 x
+// 4 takes 18.2, 17.7 and 17.3 us per step, 16^2 x 1 13.7, 13.3 and 13.2).  us per
+// step at 1, 2, 3, 4, 8 workgroups per tile: 78, 61, 56, 57, 69 for 256^2 x 16 per
+// cell (4 taken); 35, 35, 38, 41, 51 for 256^2 x 4 (2 taken); 40, 30, 28, 27, 24
+// for 100 x 70 x 8 (7 taken); 164, 173, 177, 186, 223 for 512^2 x 16 (1 taken).
 int split2(int64_t ntiles, int64_t n)
 {
     const int64_t avg = n / ntiles;
     const int64_t full = std::min<int64_t>(4 * kCus / ntiles, (avg + 2 * kThreads2 - 1) / (2 * kThreads2));
-    const int64_t thin = std::min<int64_t>(kCus / ntiles, (2 * avg + kThreads2 - 1) / kThreads2);
+    const int64_t thin = std::min<int64_t>(kCus / ntiles, (8 * avg + kThreads2 - 1) / kThreads2);
     return (int)std::max<int64_t>(1, std::max(full, thin));
 }
 
@@ -1588,6 +1589,10 @@ constexpr int64_t kFixed3 = 1200, kFixed3f = 2200;
 // The 3D step, us at 1, 2, 3, 4, 8 per tile (FP64): 87, 62, 54, 49, 47 for 24^3
 // x 8 per cell (27 tiles; 8 taken); 77, 59, 81, 77, 110 for 45 x 37 x 29 x 6
 // (120 tiles; 2 taken); 101, 134, 163, 198, 329 for 64^3 x 2 (512 tiles; 1 taken).
+// More than one has to promise 4%: with a little more tiles than CUs, many of
+// them partly filled, one to a tile ends earlier than in whole rounds (58 x 26 x
+// 74 x 8, 320 tiles: 121 us at 1, 132 at 2, which promises 2.4%; 41 x 51 x 56 x
+// 14, 294 tiles: 217 and 201, 12%).
 int tile_split(int64_t ntiles, int64_t n, int64_t fixed)
 {
     const int64_t avg = n / ntiles + 1;
@@ -1596,7 +1601,7 @@ int tile_split(int64_t ntiles, int64_t n, int64_t fixed)
     for (int w = 1; w <= 16; ++w) {
         const int64_t cost = (ntiles * w + kCus - 1) / kCus * (fixed + avg / w);
         if (w == 1 || cost < best) {
-            best = cost;
+            best = w == 1 ? cost - cost / 25 : cost;
             split = w;
         }
     }
