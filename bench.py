@@ -342,7 +342,7 @@ def roofline(res, precision, wl, copy_gbs=None, order=1, interp="alternating"):
     bytes_launch = (res["n"] * particle_bytes(precision, wl.dims)
                     + nlaunch * wl.ncell * grid_bytes_particle_kernel()) / nlaunch
     achieved = bytes_launch / (per_launch_ms * 1e-3) / 1e9
-    kernel = "k_particle_step3" if wl.dims == 3 else "k_particle_step"
+    kernel = "k_particle_step3" if wl.dims == 3 else "k_particle_step2"
     traffic = measured_traffic(precision, wl.name)
     if order == 2:
         kernel = "k_push_o2_3d + k_deposit_o2_3d" if wl.dims == 3 else "k_step_o2<2>"

@@ -32,7 +32,8 @@
 // Kernels: k_adj_seed_b/e (loss seed), k_adj_pre (B^n, lambda_J, lambda_B),
 // k_adj_curl (lambda_E), k_adj_tile2 / k_adj_tile3 (particles by tile),
 // k_adj_particles (particles of an unsorted context), k_copy_segments
-// (records), k_inverse / k_permute (particle adjoints between orders).
+// (records), k_inverse / k_permute / k_to_id_order (particle adjoints between
+// orders).
 #include <algorithm>
 
 #include "tile_io.h"
