@@ -132,6 +132,8 @@ __device__ __forceinline__ void gather_e(const GridK& g, int scheme, const doubl
     const int64_t N = g.ncell;
     const bool small = g.n[0] < 4 || g.n[1] < 4 || (D == 3 && g.n[2] < 4);
     auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
+    int c0[3];  // the cell, in the grid whatever was given
+    for (int a = 0; a < D; ++a) c0[a] = min(max(i0[a], 0), g.n[a]);
     // the grid around cell i0 + h: offsets -2 .. 2 from it, given from i0
     struct Around {
         const double* f;
@@ -146,9 +148,9 @@ __device__ __forceinline__ void gather_e(const GridK& g, int scheme, const doubl
         Around F{f, N, {}, {}, {}, {hx, hy, hz}};
 #pragma unroll
         for (int o = 0; o < 5; ++o) {
-            F.x[o] = wr(i0[0] + hx + o - 2, g.n[0]);
-            F.y[o] = wr(i0[1] + hy + o - 2, g.n[1]) * g.n[0];
-            F.z[o] = D == 3 ? (int64_t)wr(i0[2] + hz + o - 2, g.n[2]) * g.n[1] * g.n[0] : 0;
+            F.x[o] = wr(c0[0] + hx + o - 2, g.n[0]);
+            F.y[o] = wr(c0[1] + hy + o - 2, g.n[1]) * g.n[0];
+            F.z[o] = D == 3 ? (int64_t)wr(c0[2] + hz + o - 2, g.n[2]) * g.n[1] * g.n[0] : 0;
         }
         return F;
     };
