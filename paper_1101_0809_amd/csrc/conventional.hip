@@ -113,6 +113,10 @@ __global__ __launch_bounds__(kCvNT2) void k_step_conv2(GridK g, StepArgs a, cons
 constexpr int kCvM3a = 1, kCvM3b = 2;
 constexpr int kCvNTa = 512, kCvUa = 4;  // pass 1: threads, slots per thread ordered at a time
 constexpr int kCvNTb = 768, kCvUb = 2;  // pass 2
+// From kCvFull particles in a workgroup's share on, pass 2 has four waves per
+// SIMD (128 VGPRs, no spills): 64^3 x 8 333 -> 320 us a step, 89 x 30 x 88 x 4
+// (1780 a tile) 225 -> 216, but 64^3 x 2 (1024) 124.3 -> 125.4.
+constexpr int kCvNTbFull = 1024, kCvFull = 1400;
 constexpr int64_t kCvFixed = 800;       // staging and flush, in particles (tile_split)
 // Current region: 16 cells per axis in rows of 17 and planes of 272 + 3 doubles,
 // so that the classes of a tile's cells (first index modulo 16) vary along
@@ -243,10 +247,11 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
 
 // Pass 2: the particles that stay in their cell, then those that cross within
 // the region, then those outside it (a wave runs one form at a time).
-__global__ __launch_bounds__(kCvNTb) void k_deposit_conv3(GridK g, StepArgs a, PartArrays spare,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_deposit_conv3(GridK g, StepArgs a, PartArrays spare,
                                                         double* __restrict__ Jg, int split)
 {
-    constexpr int T = kTile3, M = kCvM3b, NT = kCvNTb;
+    constexpr int T = kTile3, M = kCvM3b;
     constexpr int LJ = T + 4 + 2 * M;  // cells T0-2-M .. T0+T+1+M
     constexpr int ROW = kCvRowJ, PLANE = kCvPlaneJ, NJ = LJ * PLANE;
     __shared__ double sj[3 * NJ];
@@ -366,7 +371,10 @@ hipError_t launch_particle_step_conv(Ctx& c, Species& sp, hipStream_t s)
         const int split = tile_split(c.k.ntiles, sp.n, kCvFixed);
         const dim3 grid((unsigned)(c.k.ntiles * split));
         hipLaunchKernelGGL(k_push_conv3, grid, dim3(kCvNTa), 0, s, c.k, a, sp.alt, c.fields, c.bn, split);
-        hipLaunchKernelGGL(k_deposit_conv3, grid, dim3(kCvNTb), 0, s, c.k, a, sp.alt, J, split);
+        if (sp.n / c.k.ntiles / split >= kCvFull)
+            hipLaunchKernelGGL(k_deposit_conv3<kCvNTbFull>, grid, dim3(kCvNTbFull), 0, s, c.k, a, sp.alt, J, split);
+        else
+            hipLaunchKernelGGL(k_deposit_conv3<kCvNTb>, grid, dim3(kCvNTb), 0, s, c.k, a, sp.alt, J, split);
     } else {
         hipLaunchKernelGGL(k_step_conv2, dim3(c.k.ntiles), dim3(kCvNT2), 0, s, c.k, a, c.fields, c.bn, J);
     }

@@ -191,7 +191,11 @@ __global__ __launch_bounds__(kO2NT2) void k_step_o2(GridK g, StepArgs a, const d
 // of a tile in flight at once: 20 steps of 64^3 x 2 3530 -> 3300 us.
 constexpr int kO2M3a = 1, kO2M3b = 2;
 constexpr int kO2NTa = 512, kO2Ua = 4;  // pass 1 (200 VGPRs): threads, slots per thread ordered at a time
-constexpr int kO2NTb = 768, kO2Ub = 2;  // pass 2 (150 VGPRs)
+constexpr int kO2NTb = 768, kO2Ub = 2;  // pass 2 (134 VGPRs)
+// From kO2Full particles in a workgroup's share on, pass 2 has four waves per
+// SIMD (128 VGPRs, two spilled): 64^3 x 8 401 -> 389 us a step, 89 x 30 x 88 x 4
+// (1780 a tile) 289 -> 277, but 40 x 36 x 30 x 3 (648 a share) 69.6 -> 70.0.
+constexpr int kO2NTbFull = 1024, kO2Full = 1400;
 constexpr int64_t kO2Fixed = 800;  // staging and flush, in particles (tile_split)
 
 // Pass 1's word on a particle's move: bits 2 ax .. 2 ax + 1 the cell shift plus
@@ -342,10 +346,11 @@ __device__ __forceinline__ void o2_windows(const GridK& g, const StepArgs& a, co
 // of them at thermal speeds; 144 contributions), then the others within the
 // region (300), then those outside it, so that a wave does not run two forms
 // for a few lanes.
-__global__ __launch_bounds__(kO2NTb) void k_deposit_o2_3d(GridK g, StepArgs a, PartArrays spare,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_deposit_o2_3d(GridK g, StepArgs a, PartArrays spare,
                                                           double* __restrict__ Jg, int split)
 {
-    constexpr int T = kTile3, M = kO2M3b, NT = kO2NTb;
+    constexpr int T = kTile3, M = kO2M3b;
     constexpr int LJ = T + 6 + 2 * M, NJ = LJ * LJ * LJ;
     __shared__ double sj[3 * NJ];
     __shared__ ClassRows<NT, kO2Ub> rows;
@@ -590,7 +595,10 @@ hipError_t launch_particle_step_o2(Ctx& c, Species& sp, hipStream_t s)
         const int split = tile_split(c.k.ntiles, sp.n, kO2Fixed);
         const dim3 grid((unsigned)(c.k.ntiles * split));
         hipLaunchKernelGGL(k_push_o2_3d, grid, dim3(kO2NTa), 0, s, c.k, a, sp.alt, c.fields, c.bn, split);
-        hipLaunchKernelGGL(k_deposit_o2_3d, grid, dim3(kO2NTb), 0, s, c.k, a, sp.alt, J, split);
+        if (sp.n / c.k.ntiles / split >= kO2Full)
+            hipLaunchKernelGGL(k_deposit_o2_3d<kO2NTbFull>, grid, dim3(kO2NTbFull), 0, s, c.k, a, sp.alt, J, split);
+        else
+            hipLaunchKernelGGL(k_deposit_o2_3d<kO2NTb>, grid, dim3(kO2NTb), 0, s, c.k, a, sp.alt, J, split);
     } else
         hipLaunchKernelGGL(k_step_o2<2>, dim3(c.k.ntiles), dim3(kO2NT2), 0, s, c.k, a, c.fields, c.bn, J);
     return hipGetLastError();

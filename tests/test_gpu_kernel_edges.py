@@ -222,6 +222,20 @@ def test_two_pass_steps_in_class_rows(scheme, n, ppc, w_th, sort_every):
     mod._compare(sim, st, wl)
 
 
+@pytest.mark.parametrize("scheme", ["order2", "conventional"])
+@pytest.mark.parametrize("n,ppc", [((16, 16, 16), 42), ((16, 16, 16), 48), ((20, 15, 16), 60)])
+def test_two_pass_full_shares(scheme, n, ppc):
+    """The two-pass steps with shares of a tile just below and above the size
+    from which the current pass has four waves per SIMD, and unevenly filled
+    tiles; hot."""
+    import test_gpu_conventional
+    import test_gpu_order2
+    mod = test_gpu_order2 if scheme == "order2" else test_gpu_conventional
+    wl = picgen.WORKLOADS["3d_64cube_8ppc"].scaled(nx=n[0], ny=n[1], nz=n[2], ppc=ppc, w_th=(0.3,) * 3, sort_every=3)
+    sim, st = mod._run_pair(wl, 5)
+    mod._compare(sim, st, wl)
+
+
 @pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
 @pytest.mark.parametrize("nx,ny,ppc,w_th", [
     (16, 16, 12, 0.2),    # one tile of a few shares
