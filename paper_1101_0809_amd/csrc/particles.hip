@@ -1562,18 +1562,34 @@ int split2(int64_t ntiles, int64_t n)
     return (int)std::max<int64_t>(1, std::max(full, thin));
 }
 
+// Where those are several per tile, or take less than a particle per thread, they
+// have 512 threads, and half as many of them if they then still are one per CU:
+// the same waves with half the staging and flushes.  256 threads against 512, us
+// per step: 256^2 x 16 50.2 and 47.8 (FP64), 47.4 and 43.1 (FP32 mode); 160^2 x 20
+// 40.6 and 32.6; 400 x 300 x 6 47.8 and 40.5; 48^2 x 60 27.5 and 24.0; 100 x 70 x 8
+// 19.2 and 17.8; 32^2 x 4 17.1 and 16.4.  1024 threads and a quarter as many are
+// slower (160^2 x 20 42.5, 256^2 x 16 49.7), and so are 512 where a tile has one
+// (512^2 x 16 162 -> 166: the LDS holds four tiles a CU, the registers 16 waves).
+constexpr int kThreads2Wide = 512;
+
 template <class R>
 void launch_step2(const Ctx& c, const StepArgs& a, int64_t n, hipStream_t s)
 {
-    const int split = split2(c.k.ntiles, n);
-    const dim3 grid((unsigned)(c.k.ntiles * split));
     double* J = c.fields + 6 * c.k.ncell;
-    if (n / c.k.ntiles / split > kThreads2)
+    int split = split2(c.k.ntiles, n);
+    const bool rows = n / c.k.ntiles / split > kThreads2;
+    const bool wide = !rows || split > 1;
+    if (rows && wide) split = std::max((split + 1) / 2, kCus / c.k.ntiles);
+    const dim3 grid((unsigned)(c.k.ntiles * split));
+    if (!rows)
+        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2Wide, kRows2, false>), grid,
+                           dim3(kThreads2Wide), 0, s, c.k, a, c.fields, c.bn, J, split);
+    else if (wide)
+        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2Wide, kRows2, true>), grid,
+                           dim3(kThreads2Wide), 0, s, c.k, a, c.fields, c.bn, J, split);
+    else
         hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2, kRows2, true>), grid, dim3(kThreads2), 0, s,
                            c.k, a, c.fields, c.bn, J, split);
-    else
-        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2, kRows2, false>), grid, dim3(kThreads2), 0,
-                           s, c.k, a, c.fields, c.bn, J, split);
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }

@@ -26,6 +26,17 @@ def test_2d_step_shares_a_tile(nx, ny, ppc, precision, tols):
 
 
 @pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
+@pytest.mark.parametrize("nx,ny,ppc", [(368, 369, 2), (128, 128, 9), (48, 33, 60), (250, 200, 6)])
+def test_2d_step_widths(nx, ny, ppc, precision, tols):
+    """2D3V: one workgroup of 256 threads to a tile, and shares of 512 threads
+    as many as, half as many as and more than half as many as those of 256."""
+    wl = picgen.WORKLOADS["2d3v_32x32_fp64"].scaled(nx=nx, ny=ny, ppc=ppc, w_th=(0.3,) * 3, omega_pe=0.1,
+                                                    bext=(0.0, 0.0, 0.05))
+    sim, st, _ = _run_pair(wl, precision, 6, sort_every=4)
+    _compare(sim, st, wl, *tols)
+
+
+@pytest.mark.parametrize("precision,tols", [("fp64", FP64), ("fp32c", FP32C)])
 @pytest.mark.parametrize("axis", [0, 1, 2])
 def test_3d_crossings_along_one_axis(axis, precision, tols):
     """3D: nearly every particle crosses cells along one axis (0.32 cells per
