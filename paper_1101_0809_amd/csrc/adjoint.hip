@@ -857,7 +857,11 @@ struct LdsAcc2 {
     }
 };
 
-__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_tile2(GridK g, AdjArgs a, const int64_t* __restrict__ tile_start,
+// 256 VGPRs, two waves per SIMD: one workgroup of 512 threads to a CU, so that the
+// staging and the flush are done once for its eight waves (two of 256 threads:
+// a gradient through 8 steps of 256^2 x 16 1636 us, now 1605; 128^2 x 8 738, 686).
+constexpr int kAdjThreads2 = 512;
+__global__ __launch_bounds__(kAdjThreads2) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_tile2(GridK g, AdjArgs a, const int64_t* __restrict__ tile_start,
                                                         int split)
 {
     constexpr int T = kAdjT2, M = kAdjM2, LF = kAdjLF2, LJ = kAdjLJ2, NF = kAdjNF2, NJ = kAdjNJ2;
@@ -873,11 +877,11 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
     // a thread takes whole cells, all of its loads in flight before the stores
     const bool small = nx < LJ || ny < LJ;
     auto wr = [&](int v, int n) { return small ? wrapi(v, n) : wrap1(v, n); };
-    constexpr int SF = (NF + kAdjThreads - 1) / kAdjThreads, SJ = (NJ + kAdjThreads - 1) / kAdjThreads;
+    constexpr int SF = (NF + kAdjThreads2 - 1) / kAdjThreads2, SJ = (NJ + kAdjThreads2 - 1) / kAdjThreads2;
     double vf[SF][6], vj[SJ][3];
 #pragma unroll
     for (int u = 0; u < SF; ++u) {
-        const int e = (int)threadIdx.x + u * kAdjThreads;
+        const int e = (int)threadIdx.x + u * kAdjThreads2;
         if (e < NF) {
             const int64_t cell = (int64_t)wr(T0[1] - 1 - M + e / LF, ny) * nx + wr(T0[0] - 1 - M + e % LF, nx);
 #pragma unroll
@@ -889,24 +893,24 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
     }
 #pragma unroll
     for (int u = 0; u < SJ; ++u) {
-        const int e = (int)threadIdx.x + u * kAdjThreads;
+        const int e = (int)threadIdx.x + u * kAdjThreads2;
         if (e < NJ) {
             const int64_t cell = (int64_t)wr(T0[1] - 2 - M + e / LJ, ny) * nx + wr(T0[0] - 2 - M + e % LJ, nx);
 #pragma unroll
             for (int k = 0; k < 3; ++k) vj[u][k] = a.lamJ[k * N + cell];
         }
     }
-    for (int e = threadIdx.x; e < 6 * NF; e += kAdjThreads) sacc[e] = 0.0;
+    for (int e = threadIdx.x; e < 6 * NF; e += kAdjThreads2) sacc[e] = 0.0;
 #pragma unroll
     for (int u = 0; u < SF; ++u) {
-        const int e = (int)threadIdx.x + u * kAdjThreads;
+        const int e = (int)threadIdx.x + u * kAdjThreads2;
         if (e < NF)
 #pragma unroll
             for (int k = 0; k < 6; ++k) sf[k * NF + e] = vf[u][k];
     }
 #pragma unroll
     for (int u = 0; u < SJ; ++u) {
-        const int e = (int)threadIdx.x + u * kAdjThreads;
+        const int e = (int)threadIdx.x + u * kAdjThreads2;
         if (e < NJ)
 #pragma unroll
             for (int k = 0; k < 3; ++k) sj[k * NJ + e] = vj[u][k];
@@ -916,7 +920,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
 
     double lbp[3] = {0.0, 0.0, 0.0};
     const int64_t begin = tile_start[tile], end = tile_start[tile + 1];
-    for (int64_t p = begin + part * kAdjThreads + threadIdx.x; p < end; p += (int64_t)split * kAdjThreads) {
+    for (int64_t p = begin + part * kAdjThreads2 + threadIdx.x; p < end; p += (int64_t)split * kAdjThreads2) {
         int i0[3];
         double d0[3], w0[3], qp;
         int64_t li;
@@ -942,7 +946,7 @@ __global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(2))
         }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 6 * NF; e += kAdjThreads) {
+    for (int e = threadIdx.x; e < 6 * NF; e += kAdjThreads2) {
         const double v = sacc[e];
         if (v == 0.0) continue;
         const int comp = e / NF, r = e - comp * NF;
@@ -1397,6 +1401,13 @@ hipError_t launch_adjoint_reorder(Ctx& c, const void* from, const void* to, cons
     return hipGetLastError();
 }
 
+// Staging and flush of the tile kernels, in particles (tile_split).  A gradient
+// through 8 steps, us, with enough workgroups for two per CU whatever they cost,
+// and with this: 45 x 37 x 29 x 6 (120 tiles) 2232 and 1656, 48^3 x 4 (216) 2512
+// and 2030, 58 x 26 x 60 x 8 (256) 3170 and 2860, 300 x 200 x 12 (247 tiles, 2D3V)
+// 1489 and 1296; the same where tiles are few (24^3 x 8) or many (64^3 x 8).
+constexpr int64_t kAdjFixed3 = 800, kAdjFixed2 = 500;
+
 hipError_t launch_adjoint_step(const Ctx& c, const void* record, bool by_id, double* lam, double* const* lam_x,
                                double* const* lam_w, double* lam_bext, hipStream_t s)
 {
@@ -1439,15 +1450,14 @@ hipError_t launch_adjoint_step(const Ctx& c, const void* record, bool by_id, dou
         a.qslot = sp.alt.id;
         const unsigned pb = (unsigned)((sp.n + kAdjThreads - 1) / kAdjThreads);
         if (c.k.dims == 3 && pv.tiles) {
-            const int split = (int)std::min<int64_t>(8, std::max<int64_t>(1, (512 + c.k.ntiles - 1) / c.k.ntiles));
+            const int split = std::min(8, tile_split(c.k.ntiles, sp.n, kAdjFixed3));
             hipLaunchKernelGGL(k_adj_tile3, dim3((unsigned)(c.k.ntiles * split)), dim3(kAdjThreads3), 0, s, c.k, a,
                                pv.tile_start, split);
         } else if (c.k.dims == 3) {
             hipLaunchKernelGGL(k_adj_particles<3>, dim3(pb), dim3(kAdjThreads), 0, s, c.k, a);
         } else if (pv.tiles) {
-            // enough workgroups to fill the chip: several per tile when tiles are few
-            const int split = (int)std::min<int64_t>(8, std::max<int64_t>(1, (512 + c.k.ntiles - 1) / c.k.ntiles));
-            hipLaunchKernelGGL(k_adj_tile2, dim3((unsigned)(c.k.ntiles * split)), dim3(kAdjThreads), 0, s, c.k, a,
+            const int split = std::min(8, tile_split(c.k.ntiles, sp.n, kAdjFixed2));
+            hipLaunchKernelGGL(k_adj_tile2, dim3((unsigned)(c.k.ntiles * split)), dim3(kAdjThreads2), 0, s, c.k, a,
                                pv.tile_start, split);
         } else {
             hipLaunchKernelGGL(k_adj_particles<2>, dim3(pb), dim3(kAdjThreads), 0, s, c.k, a);
