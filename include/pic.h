@@ -328,6 +328,21 @@ int pic_adjoint_reorder(pic_ctx* ctx, const void* from, const void* to, size_t b
 int pic_solve_poisson(pic_ctx* ctx, int neutralize, double tol, int64_t* iterations, double* residual,
                       void* stream);
 
+/* Tuning of pic_solve_poisson.  Where its workgroups can all run at once (grids
+ * of up to 524288 cells on a device with CUs enough, one such solve on a device
+ * at a time) it takes all iterations in one launch; a workgroup that waits too
+ * long for the others gives up, and the solve starts again in separate launches.
+ *
+ * pic_poisson_limits: the workgroups that may be counted on to run at once, the
+ * reads of another workgroup's sum before giving up, and the iterations of one
+ * launch, for this context's solves; negative: the library's own.  With
+ * workgroups 0 every solve takes separate launches.
+ * pic_last_poisson_form: how the context's last solve ran: 0 none yet, 1 in
+ * separate launches, 2 in one launch (or several, by the limit on iterations),
+ * 3 in separate launches after the other form had given up. */
+int pic_poisson_limits(pic_ctx* ctx, int workgroups, int polls, int iterations);
+int pic_last_poisson_form(const pic_ctx* ctx);
+
 /* Vector-potential form (field_form 1): pic_set_vector_potential copies A
  * (3 N FP64 device array, the layout of E: A^x at (i, j+1/2, k+1/2), ...)
  * as A^{n-1/2} of the current state and sets the B planes to curl_h A;

@@ -28,7 +28,7 @@ EXPORTS = (
     "pic_adjoint_seed_field_energy", "pic_adjoint_step", "pic_adjoint_record_bytes",
     "pic_adjoint_record", "pic_adjoint_step_record", "pic_adjoint_step_record_ordered",
     "pic_adjoint_reorder", "pic_solve_poisson", "pic_set_vector_potential",
-    "pic_get_vector_potential",
+    "pic_get_vector_potential", "pic_poisson_limits", "pic_last_poisson_form",
     "pic_last_error", "pic_version",
 )
 
@@ -128,6 +128,8 @@ def load(path: str = LIB_PATH):
         "pic_adjoint_reorder": (I, [P, P, P, ctypes.c_size_t, ctypes.POINTER(P), ctypes.POINTER(P),
                                     ctypes.POINTER(P), ctypes.POINTER(P), P]),
         "pic_solve_poisson": (I, [P, I, D, ctypes.POINTER(I64), ctypes.POINTER(D), P]),
+        "pic_poisson_limits": (I, [P, I, I, I]),
+        "pic_last_poisson_form": (I, [P]),
         "pic_set_vector_potential": (I, [P, P, P]),
         "pic_get_vector_potential": (I, [P, P, P]),
         "pic_destroy": (None, [P]),

@@ -637,6 +637,15 @@ int pic_solve_poisson(pic_ctx* ctx, int neutralize, double tol, int64_t* iterati
     return PIC_OK;
 }
 
+int pic_poisson_limits(pic_ctx* ctx, int workgroups, int polls, int iterations)
+{
+    if (!ctx) return fail(nullptr, PIC_EINVAL, "null context");
+    ctx->c.poisson_limits = PoissonLimits{workgroups, polls, iterations};
+    return PIC_OK;
+}
+
+int pic_last_poisson_form(const pic_ctx* ctx) { return ctx ? ctx->c.poisson_form : 0; }
+
 int pic_set_vector_potential(pic_ctx* ctx, const double* A, void* stream)
 {
     if (!ctx) return fail(nullptr, PIC_EINVAL, "null context");

@@ -123,6 +123,11 @@ struct GridK {
     int field_form;    // 0: B carried; 1: vector potential carried (B = curl A)
 };
 
+// Limits of the Poisson solve's one-launch form (pic_poisson_limits); negative: its own.
+struct PoissonLimits {
+    int workgroups = -1, polls = -1, iterations = -1;
+};
+
 struct Ctx {
     pic_grid_desc g{};
     GridK k{};
@@ -149,6 +154,8 @@ struct Ctx {
     int64_t step = 0;
     int since_sort = 0;
     bool r0_valid = false;
+    PoissonLimits poisson_limits;
+    int poisson_form = 0;  // of the last solve (pic_last_poisson_form)
     std::string err;
 };
 

@@ -281,9 +281,9 @@ __device__ __forceinline__ double wave_sum63(double v)
 }
 
 // Iterations it0 .. it1 - 1, fewer once r.r has reached the target s[2].  s[6]:
-// r.r before and after.
+// r.r before and after.  polls: reads of a slot before giving up.
 template <int CPT>
-__global__ __launch_bounds__(kRunThreads) void k_cg_run(GridK g, int it0, int it1, double* __restrict__ s,
+__global__ __launch_bounds__(kRunThreads) void k_cg_run(GridK g, int it0, int it1, int polls, double* __restrict__ s,
                                                         unsigned long long* slots, unsigned long long* status,
                                                         double* r, double* __restrict__ phi, double* __restrict__ p)
 {
@@ -316,10 +316,11 @@ __global__ __launch_bounds__(kRunThreads) void k_cg_run(GridK g, int it0, int it
         double v = 0.0;
         if (t < W) {
             const double* slot = (const double*)slots + (e & 3) * kCus + t;
-            int polls = 0;
-            do v = load_agent(slot);
-            while ((unsigned long long)__double_as_longlong(v) == kEmpty && ++polls < kRunPolls);
-            if ((unsigned long long)__double_as_longlong(v) == kEmpty) gave_up = 1;
+            unsigned long long b = kEmpty;
+            for (int q = 0; q < polls && b == kEmpty; ++q)
+                b = (unsigned long long)__double_as_longlong(load_agent(slot));
+            if (b == kEmpty) gave_up = 1;
+            v = __longlong_as_double((long long)b);
         }
         if (t < kCus) {
             v = wave_sum63(v);
@@ -365,7 +366,8 @@ __global__ __launch_bounds__(kRunThreads) void k_cg_run(GridK g, int it0, int it
             double x[7];
             x[0] = rv[u];
 #pragma unroll
-            for (int k = 1; k < 7; ++k) x[k] = st.q[k] - base < (uint32_t)K ? lr[st.q[k] - base] : load_agent(r + st.q[k]);
+            for (int k = 1; k < 7; ++k)
+                x[k] = st.q[k] - base < (uint32_t)K ? lr[st.q[k] - base] : load_agent(r + st.q[k]);
 #pragma unroll
             for (int k = 0; k < 7; ++k) pv[u][k] = it == 0 ? x[k] : x[k] + beta * pv[u][k];
             ap[u] = neg_lap(g, pv[u]);
@@ -504,19 +506,26 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
     // In one launch: one workgroup per CU at most, all of which have to be
     // running at once.  If one is kept waiting too long (by another process on
     // the GPU) all give up, and the solve starts again in separate launches.
+    c.poisson_form = 1;
     const RunTurn turn;
     const int cells = (int)((n + (int64_t)kCus * kRunThreads - 1) / ((int64_t)kCus * kRunThreads));
-    if (turn.mine() && bb > 0.0 && rr > target && it < max_iter && n <= (int64_t)kCus * kRunThreads * kRunCells) {
+    const int cpt = cells <= 1 ? 1 : kRunCells;
+    auto* run = cpt == 1 ? k_cg_run<1> : k_cg_run<kRunCells>;
+    const int64_t wgs = (n + kRunThreads * cpt - 1) / (kRunThreads * cpt);
+    const PoissonLimits& lim = c.poisson_limits;
+    const int polls = lim.polls < 0 ? kRunPolls : lim.polls;
+    const int iters_max = lim.iterations < 0 ? kRunIters : lim.iterations;
+    if (turn.mine() && bb > 0.0 && rr > target && it < max_iter &&
+        wgs <= (lim.workgroups < 0 ? kCus : std::min(kCus, lim.workgroups))) {
+        c.poisson_form = 2;
         unsigned long long* slots = (unsigned long long*)(sc + 16);
-        const int cpt = cells <= 1 ? 1 : kRunCells;
-        const dim3 grid((unsigned)((n + kRunThreads * cpt - 1) / (kRunThreads * cpt)));
+        const dim3 grid((unsigned)wgs);
         hipLaunchKernelGGL(k_scale, dim3(1), dim3(64), 0, s, sc, 6, 4, 1.0);
         while (rr > target && it < max_iter) {
             hipLaunchKernelGGL(k_run_prepare, dim3(4 * kCus / kThreads), dim3(kThreads), 0, s, slots, 4 * kCus,
                                (unsigned long long*)status);
-            const int last = (int)std::min<int64_t>(max_iter, it + kRunIters);
-            auto* run = cpt == 1 ? k_cg_run<1> : k_cg_run<kRunCells>;
-            hipLaunchKernelGGL(run, grid, dim3(kRunThreads), 0, s, c.k, (int)it, last, sc, slots,
+            const int last = (int)std::min<int64_t>(max_iter, it + iters_max);
+            hipLaunchKernelGGL(run, grid, dim3(kRunThreads), 0, s, c.k, (int)it, last, polls, sc, slots,
                                (unsigned long long*)status, r, phi, p[0]);
             e = hipMemcpyAsync(host, sc, sizeof(host), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -524,6 +533,7 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
             unsigned long long st[2];
             std::memcpy(st, host + 8, sizeof(st));
             if (st[1]) {
+                c.poisson_form = 3;
                 it = 0;
                 rr = bb;
                 hipLaunchKernelGGL(k_cg_init, dim3(gb), dim3(kThreads), 0, s, n, rho, sc, phi, r, part);
