@@ -505,7 +505,8 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
     const double target = tol * tol * bb;
     // In one launch: one workgroup per CU at most, all of which have to be
     // running at once.  If one is kept waiting too long (by another process on
-    // the GPU) all give up, and the solve starts again in separate launches.
+    // the GPU) all give up, and the solve starts again in separate launches; so
+    // it does if a launch made no iteration.
     c.poisson_form = 1;
     const RunTurn turn;
     const int cells = (int)((n + (int64_t)kCus * kRunThreads - 1) / ((int64_t)kCus * kRunThreads));
@@ -527,12 +528,13 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
             const int last = (int)std::min<int64_t>(max_iter, it + iters_max);
             hipLaunchKernelGGL(run, grid, dim3(kRunThreads), 0, s, c.k, (int)it, last, polls, sc, slots,
                                (unsigned long long*)status, r, phi, p[0]);
-            e = hipMemcpyAsync(host, sc, sizeof(host), hipMemcpyDeviceToHost, s);
+            e = hipGetLastError();  // a launch that was refused leaves the status as it was prepared
+            if (e == hipSuccess) e = hipMemcpyAsync(host, sc, sizeof(host), hipMemcpyDeviceToHost, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             if (e != hipSuccess) return e;
             unsigned long long st[2];
             std::memcpy(st, host + 8, sizeof(st));
-            if (st[1]) {
+            if (st[1] || (int64_t)st[0] <= it) {
                 c.poisson_form = 3;
                 it = 0;
                 rr = bb;

@@ -83,3 +83,11 @@ def test_second_solve_at_a_time_takes_separate_launches():
         stop.set()
         thread.join()
     assert SEPARATE in forms and GAVE_UP not in forms, forms
+
+
+@pytest.mark.parametrize("n", GRIDS)
+def test_launch_without_progress_ends_the_form(n):
+    """A launch that makes no iteration (none allowed; a refused launch looks
+    the same) is not repeated for ever: separate launches solve."""
+    sim, E = _poisson_case(n, 61)
+    assert _solve(sim, E, iterations=0)[1] == GAVE_UP
