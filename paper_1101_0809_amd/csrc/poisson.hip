@@ -235,7 +235,9 @@ __global__ __launch_bounds__(kThreads) void k_cg_update(int64_t n, int it, int n
 // ---------------------------------------------------------------------------
 constexpr int kRunThreads = 1024, kRunCells = 2;  // cells per thread at most (4 spill)
 constexpr int kRunIters = 2048;                  // iterations of a launch at most
-constexpr int kRunPolls = 1 << 15;               // reads of a slot (a microsecond each) before giving up
+// Reads of a slot (a microsecond each) before giving up: what a wait in vain costs
+// is then no more than the solve in separate launches that follows it (64^3: 4 ms).
+constexpr int kRunPolls = 1 << 12;
 constexpr unsigned long long kEmpty = 0xfff8dead00000001ull;  // a slot not written yet (a NaN no sum yields)
 
 // status[0]: iterations done; status[1]: nonzero if a workgroup gave up.
@@ -468,6 +470,17 @@ class RunTurn {
     std::atomic<bool>* flag_ = nullptr;
 };
 
+// Workgroups of the one-launch form that the current device runs at once.
+int resident_workgroups(const void* kernel)
+{
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, kRunThreads, 0) != hipSuccess)
+        return 0;
+    return std::min(kCus, cus * per);
+}
+
 unsigned grid_for(int64_t n) { return (unsigned)std::min<int64_t>(kBlocks, (n + kThreads - 1) / kThreads); }
 
 }  // namespace
@@ -504,9 +517,10 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
     double rr = bb;
     const double target = tol * tol * bb;
     // In one launch: one workgroup per CU at most, all of which have to be
-    // running at once.  If one is kept waiting too long (by another process on
-    // the GPU) all give up, and the solve starts again in separate launches; so
-    // it does if a launch made no iteration.
+    // running at once, so the device has to hold them (one that shows fewer CUs
+    // would lose the wait in every solve).  If one is kept waiting too long (by
+    // another process or stream on the GPU) all give up, and the solve starts
+    // again in separate launches; so it does if a launch made no iteration.
     c.poisson_form = 1;
     const RunTurn turn;
     const int cells = (int)((n + (int64_t)kCus * kRunThreads - 1) / ((int64_t)kCus * kRunThreads));
@@ -516,8 +530,8 @@ hipError_t solve_poisson(Ctx& c, double* rho, bool neutralize, double tol, int64
     const PoissonLimits& lim = c.poisson_limits;
     const int polls = lim.polls < 0 ? kRunPolls : lim.polls;
     const int iters_max = lim.iterations < 0 ? kRunIters : lim.iterations;
-    if (turn.mine() && bb > 0.0 && rr > target && it < max_iter &&
-        wgs <= (lim.workgroups < 0 ? kCus : std::min(kCus, lim.workgroups))) {
+    const int held = lim.workgroups < 0 ? resident_workgroups((const void*)run) : std::min(kCus, lim.workgroups);
+    if (turn.mine() && bb > 0.0 && rr > target && it < max_iter && wgs <= held) {
         c.poisson_form = 2;
         unsigned long long* slots = (unsigned long long*)(sc + 16);
         const dim3 grid((unsigned)wgs);

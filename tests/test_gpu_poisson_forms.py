@@ -91,3 +91,12 @@ def test_launch_without_progress_ends_the_form(n):
     the same) is not repeated for ever: separate launches solve."""
     sim, E = _poisson_case(n, 61)
     assert _solve(sim, E, iterations=0)[1] == GAVE_UP
+
+
+@pytest.mark.parametrize("n,needed", [((16, 8, 8), 1), ((41, 25, 1), 2), ((64, 64, 64), 256), ((128, 64, 64), 256)])
+def test_one_launch_only_where_its_workgroups_fit(n, needed):
+    """With fewer workgroups at once than the grid needs the solve takes separate
+    launches at once, with as many one."""
+    sim, E = _poisson_case(n, 67)
+    assert _solve(sim, E, workgroups=needed - 1)[1] == SEPARATE
+    assert _solve(sim, E, workgroups=needed)[1] == ONE_LAUNCH
