@@ -857,20 +857,44 @@ struct LdsAcc2 {
     }
 };
 
+// The workgroups that work on a tile of n particles, of the `parts` launched for
+// each: `split` of them, more where it holds over twice the mean (shares of about
+// `share` particles), none where it is empty.  The host knows only the mean, and
+// with one number for all tiles either the full or the even ones lose.  A gradient
+// through 8 steps, us, with parts for every tile, split for every tile, and this:
+// 48^3 x 4 2882, 2136, 2148 evenly filled, 3637, 4602, 3200 in a quarter of the box
+// along x, 5186, 8111, 4903 in an eighth; 300 x 200 x 12 (2D3V) in a sixteenth 7564,
+// 8464, 5047; 32^3 x 8 in a quarter 3567, 2673, 2911.  (Twice: from 1.5 on, a ragged
+// box's whole tiles take one more and fill a second round, 45 x 37 x 29 x 6 1728,
+// here 1739, then 2089.)
+struct Shares {
+    int split, parts;
+    int64_t share;
+    __device__ __forceinline__ int of(int64_t n) const
+    {
+        if (n <= 2 * split * share) return n > 0 ? split : 0;
+        return (int)min((int64_t)parts, (n + share / 2) / share);
+    }
+};
+
 // 256 VGPRs, two waves per SIMD: one workgroup of 512 threads to a CU, so that the
 // staging and the flush are done once for its eight waves (two of 256 threads:
 // a gradient through 8 steps of 256^2 x 16 1636 us, now 1605; 128^2 x 8 738, 686).
 constexpr int kAdjThreads2 = 512;
-__global__ __launch_bounds__(kAdjThreads2) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_tile2(GridK g, AdjArgs a, const int64_t* __restrict__ tile_start,
-                                                        int split)
+__global__ __launch_bounds__(kAdjThreads2) __attribute__((amdgpu_waves_per_eu(2)))
+void k_adj_tile2(GridK g, AdjArgs a, const int64_t* __restrict__ tile_start, Shares shares)
 {
     constexpr int T = kAdjT2, M = kAdjM2, LF = kAdjLF2, LJ = kAdjLJ2, NF = kAdjNF2, NJ = kAdjNJ2;
     __shared__ double sf[6 * NF];
     __shared__ double sj[3 * NJ];
     __shared__ double sacc[6 * NF];
     __shared__ double sb[3];
-    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
-    const int tile = unit / split, part = unit - tile * split;
+    // the first shares of all tiles, then the second ones: those that a tile has
+    // not are dispatched last
+    const int part = blockIdx.x / g.ntiles, tile = xcd_tile(blockIdx.x - part * g.ntiles, g.ntiles);
+    const int64_t begin = tile_start[tile], end = tile_start[tile + 1];
+    const int split = shares.of(end - begin);
+    if (part >= split) return;
     const int T0[2] = {(tile % g.nt[0]) * T, (tile / g.nt[0]) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1];
@@ -919,7 +943,6 @@ __global__ __launch_bounds__(kAdjThreads2) __attribute__((amdgpu_waves_per_eu(2)
     __syncthreads();
 
     double lbp[3] = {0.0, 0.0, 0.0};
-    const int64_t begin = tile_start[tile], end = tile_start[tile + 1];
     for (int64_t p = begin + part * kAdjThreads2 + threadIdx.x; p < end; p += (int64_t)split * kAdjThreads2) {
         int i0[3];
         double d0[3], w0[3], qp;
@@ -1050,7 +1073,7 @@ __device__ __forceinline__ bool tile_place3(const GridK& g, const AdjArgs& a, in
 }
 
 __global__ __launch_bounds__(kAdjThreads3) void k_adj_tile3(GridK g, AdjArgs a, const int64_t* __restrict__ tile_start,
-                                                            int split)
+                                                            Shares shares)
 {
     constexpr int T = kAdjT3, M = kAdjM3, LF = kAdjLF3, LJ = kAdjLJ3, NF = kAdjNF3, NJ = kAdjNJ3, NT = kAdjThreads3;
     constexpr int C = kAdjC3;
@@ -1061,8 +1084,12 @@ __global__ __launch_bounds__(kAdjThreads3) void k_adj_tile3(GridK g, AdjArgs a, 
     __shared__ unsigned short queue[kAdjQ3];  // phase 1: the particles off the tile; phase 2: the class queue
     double* const sf = lds;  // phase 1: E, B^n; phase 2: lambda_E, lambda_B
     double* const sj = lds + 6 * NF;
-    const int unit = xcd_tile(blockIdx.x, g.ntiles * split);
-    const int tile = unit / split, part = unit - tile * split;
+    // the first shares of all tiles, then the second ones: those that a tile has
+    // not are dispatched last
+    const int part = blockIdx.x / g.ntiles, tile = xcd_tile(blockIdx.x - part * g.ntiles, g.ntiles);
+    const int64_t begin = tile_start[tile], end = tile_start[tile + 1];
+    const int split = shares.of(end - begin);
+    if (part >= split) return;
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T, (tile / (g.nt[0] * g.nt[1])) * T};
     const int64_t N = g.ncell;
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
@@ -1093,7 +1120,6 @@ __global__ __launch_bounds__(kAdjThreads3) void k_adj_tile3(GridK g, AdjArgs a, 
 
     // phase 1
     double lbp[3] = {0.0, 0.0, 0.0};
-    const int64_t begin = tile_start[tile], end = tile_start[tile + 1];
     for (int64_t p = begin + part * NT + threadIdx.x; p < end; p += (int64_t)split * NT) {
         int i0[3], rel[3];
         double d0[3], w0[3], qp, lEB[6];
@@ -1408,6 +1434,15 @@ hipError_t launch_adjoint_reorder(Ctx& c, const void* from, const void* to, cons
 // 1489 and 1296; the same where tiles are few (24^3 x 8) or many (64^3 x 8).
 constexpr int64_t kAdjFixed3 = 800, kAdjFixed2 = 500;
 
+// Shares of evenly filled tiles as tile_split has them; a fuller tile has more of
+// them, up to two workgroups per CU in all.
+static Shares shares_for(int64_t ntiles, int64_t n, int64_t fixed)
+{
+    const int split = std::min(8, tile_split(ntiles, n, fixed));
+    const int parts = std::max(split, (int)std::min<int64_t>(8, (2 * kCus + ntiles - 1) / ntiles));
+    return Shares{split, parts, std::max<int64_t>(1, n / ntiles / split)};
+}
+
 hipError_t launch_adjoint_step(const Ctx& c, const void* record, bool by_id, double* lam, double* const* lam_x,
                                double* const* lam_w, double* lam_bext, hipStream_t s)
 {
@@ -1450,15 +1485,15 @@ hipError_t launch_adjoint_step(const Ctx& c, const void* record, bool by_id, dou
         a.qslot = sp.alt.id;
         const unsigned pb = (unsigned)((sp.n + kAdjThreads - 1) / kAdjThreads);
         if (c.k.dims == 3 && pv.tiles) {
-            const int split = std::min(8, tile_split(c.k.ntiles, sp.n, kAdjFixed3));
-            hipLaunchKernelGGL(k_adj_tile3, dim3((unsigned)(c.k.ntiles * split)), dim3(kAdjThreads3), 0, s, c.k, a,
-                               pv.tile_start, split);
+            const Shares shares = shares_for(c.k.ntiles, sp.n, kAdjFixed3);
+            hipLaunchKernelGGL(k_adj_tile3, dim3((unsigned)(c.k.ntiles * shares.parts)), dim3(kAdjThreads3), 0, s,
+                               c.k, a, pv.tile_start, shares);
         } else if (c.k.dims == 3) {
             hipLaunchKernelGGL(k_adj_particles<3>, dim3(pb), dim3(kAdjThreads), 0, s, c.k, a);
         } else if (pv.tiles) {
-            const int split = std::min(8, tile_split(c.k.ntiles, sp.n, kAdjFixed2));
-            hipLaunchKernelGGL(k_adj_tile2, dim3((unsigned)(c.k.ntiles * split)), dim3(kAdjThreads2), 0, s, c.k, a,
-                               pv.tile_start, split);
+            const Shares shares = shares_for(c.k.ntiles, sp.n, kAdjFixed2);
+            hipLaunchKernelGGL(k_adj_tile2, dim3((unsigned)(c.k.ntiles * shares.parts)), dim3(kAdjThreads2), 0, s,
+                               c.k, a, pv.tile_start, shares);
         } else {
             hipLaunchKernelGGL(k_adj_particles<2>, dim3(pb), dim3(kAdjThreads), 0, s, c.k, a);
         }
