@@ -210,24 +210,67 @@ __global__ __launch_bounds__(64 * kTileGroup) void k_tile_sums(const uint32_t* _
     }
 }
 
+// From kScanGroups groups on, one workgroup turns gsum into the particles before
+// each group: added up by every tile they cost reads as the square of the tiles.
+// A sort of 2^26 particles on 8192^2 cells (16384 groups): 5.69 ms with the tiles
+// adding, 5.25 like this; on 1024 x 512 x 1024 (65536) 25.7 and 17.7; of 2^22 on
+// 2048^2 (1024) 0.336 and 0.337.
+constexpr int kScanGroups = 1024;
+
+__global__ __launch_bounds__(1024) void k_group_scan(uint32_t* __restrict__ gsum, int groups)
+{
+    constexpr int NW = 16, U = 4;
+    __shared__ uint32_t wsum[NW];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    uint32_t carry = 0;
+    for (int g0 = t * U; g0 - t * U < groups; g0 += 1024 * U) {
+        uint32_t v[U], sum = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v[u] = g0 + u < groups ? gsum[g0 + u] : 0u;
+            sum += v[u];
+        }
+        uint32_t incl = sum;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t x = (uint32_t)__shfl_up((int)incl, off, 64);
+            if (lane >= off) incl += x;
+        }
+        if (lane == 63) wsum[wv] = incl;
+        __syncthreads();
+        uint32_t run = carry + incl - sum;
+        for (int w = 0; w < NW; ++w) {
+            run += w < wv ? wsum[w] : 0u;
+            carry += wsum[w];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (g0 + u < groups) gsum[g0 + u] = run;
+            run += v[u];
+        }
+        __syncthreads();
+    }
+}
+
 // The exclusive scan of the counts of tile t's TPD cells, one per thread of its
 // workgroup: replaces the thread's count in offs by its cell's first
 // cell-sorted position, which is returned; start: the tile's, cnt: the count,
-// nt: the tile's particles.  Every workgroup adds up the groups before its own:
-// that saves two launches and a pass over the keys.  With it and one gather in
-// place of 8 a sort has 6 launches in place of 14: 175 -> 145 us for 64^3 x 8,
-// 75 -> 45 us for 290,000 particles.
+// nt: the tile's particles.  Every workgroup adds up the groups before its own
+// (unless they are scanned, see above): that saves two launches and a pass over
+// the keys.  With it and one gather in place of 8 a sort has 6 launches in place
+// of 14: 175 -> 145 us for 64^3 x 8, 75 -> 45 us for 290,000 particles.
 template <int TPD>
 __device__ __forceinline__ uint32_t tile_offsets(uint32_t* __restrict__ offs, const uint32_t* __restrict__ tsum,
-                                                 const uint32_t* __restrict__ gsum, int t, uint32_t& start,
-                                                 uint32_t& cnt, uint32_t& nt)
+                                                 const uint32_t* __restrict__ gsum, bool scanned, int t,
+                                                 uint32_t& start, uint32_t& cnt, uint32_t& nt)
 {
     constexpr int NW = TPD / 64;
     __shared__ uint32_t before[NW], own[NW];
     const int c = threadIdx.x, lane = c & 63, wv = c >> 6;
     cnt = offs[(int64_t)t * TPD + c];
     uint32_t pre = 0;
-    for (int q = c; q < t / kTileGroup; q += TPD) pre += gsum[q];
+    if (scanned) pre = c == 0 ? gsum[t / kTileGroup] : 0u;
+    else
+        for (int q = c; q < t / kTileGroup; q += TPD) pre += gsum[q];
     for (int off = 32; off > 0; off >>= 1) pre += (uint32_t)__shfl_xor((int)pre, off, 64);
     uint32_t incl = cnt;
     for (int off = 1; off < 64; off <<= 1) {
@@ -257,7 +300,7 @@ __device__ __forceinline__ uint32_t tile_offsets(uint32_t* __restrict__ offs, co
 // tile, one thread per cell; only 4-byte writes.
 template <int TPD>
 __global__ __launch_bounds__(TPD) void k_dest(uint32_t* __restrict__ offs, const uint32_t* __restrict__ tsum,
-                                              const uint32_t* __restrict__ gsum, int64_t n,
+                                              const uint32_t* __restrict__ gsum, bool scanned, int64_t n,
                                               uint32_t* __restrict__ dest, int64_t* __restrict__ ts)
 {
     constexpr int NW = TPD / 64;
@@ -266,7 +309,7 @@ __global__ __launch_bounds__(TPD) void k_dest(uint32_t* __restrict__ offs, const
     const int c = threadIdx.x;
     const int lane = c & 63, wv = c >> 6;
     uint32_t base, cnt, nt;
-    const int64_t cb = tile_offsets<TPD>(offs, tsum, gsum, blockIdx.x, base, cnt, nt);
+    const int64_t cb = tile_offsets<TPD>(offs, tsum, gsum, scanned, blockIdx.x, base, cnt, nt);
     if (c == 0) ts[blockIdx.x] = base;  // the tile table of the new order
     if (c == 0 && blockIdx.x == gridDim.x - 1) ts[gridDim.x] = n;
     uint32_t m = cnt;
@@ -308,7 +351,8 @@ __global__ __launch_bounds__(TPD) void k_dest(uint32_t* __restrict__ offs, const
 template <int C>
 __global__ __launch_bounds__(kTile3 * kTile3 * kTile3) void k_dest3(uint32_t* __restrict__ offs,
                                                                      const uint32_t* __restrict__ tsum,
-                                                                     const uint32_t* __restrict__ gsum, int64_t n,
+                                                                     const uint32_t* __restrict__ gsum,
+                                                                     bool scanned, int64_t n,
                                                                      uint32_t* __restrict__ dest,
                                                                      int64_t* __restrict__ ts)
 {
@@ -317,7 +361,7 @@ __global__ __launch_bounds__(kTile3 * kTile3 * kTile3) void k_dest3(uint32_t* __
     __shared__ uint32_t ccnt[C], cbase[C], rows[C], hpre[C + 1], lpre[C + 1];
     const int c = threadIdx.x;
     uint32_t tb, cnt, nt;
-    const uint32_t cb = tile_offsets<TPD>(offs, tsum, gsum, blockIdx.x, tb, cnt, nt);
+    const uint32_t cb = tile_offsets<TPD>(offs, tsum, gsum, scanned, blockIdx.x, tb, cnt, nt);
     if (c == 0) ts[blockIdx.x] = tb;  // the tile table of the new order
     if (c == 0 && blockIdx.x == gridDim.x - 1) ts[gridDim.x] = n;
     if (nt == 0) return;
@@ -461,11 +505,13 @@ hipError_t sort_impl(Ctx& c, Species& sp, hipStream_t s)
         hipLaunchKernelGGL((k_histogram<R, D, T>), dim3(nblk(n)), dim3(kSortThreads), 0, s, c.k,
                            sp.cur, n, sp.key, sp.rank, c.hist);
     hipLaunchKernelGGL((k_tile_sums<TPD>), dim3(groups), dim3(64 * kTileGroup), 0, s, c.hist, c.k.ntiles, tsum, gsum);
+    const bool scanned = groups >= kScanGroups;
+    if (scanned) hipLaunchKernelGGL(k_group_scan, dim3(1), dim3(1024), 0, s, gsum, (int)groups);
     if (D == 3)
-        hipLaunchKernelGGL((k_dest3<lane_classes<R>()>), dim3(c.k.ntiles), dim3(TPD), 0, s, c.hist, tsum, gsum, n,
-                           sp.dest, sp.tile_start);
+        hipLaunchKernelGGL((k_dest3<lane_classes<R>()>), dim3(c.k.ntiles), dim3(TPD), 0, s, c.hist, tsum, gsum,
+                           scanned, n, sp.dest, sp.tile_start);
     else
-        hipLaunchKernelGGL((k_dest<TPD>), dim3(c.k.ntiles), dim3(TPD), 0, s, c.hist, tsum, gsum, n, sp.dest,
+        hipLaunchKernelGGL((k_dest<TPD>), dim3(c.k.ntiles), dim3(TPD), 0, s, c.hist, tsum, gsum, scanned, n, sp.dest,
                            sp.tile_start);
     if (n > 0) {
         // the inverse of the final slots, and one gather into the spare copy,
