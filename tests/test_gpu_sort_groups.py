@@ -15,3 +15,11 @@ def test_sort_of_scanned_groups(n, precision):
     if precision == "fp32c" and n[1] > 2048:
         n = (n[0], 2048, 1)  # FP32 mode's largest axes
     test_gpu_kernel_edges.test_sort_moves_particles_whole(n, 300_000, precision)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32c"])
+@pytest.mark.parametrize("count", [15, 8191, 8192, 8193, 24_600])
+def test_sort_rounds_of_a_tile(count, precision):
+    """One tile whose waves hold no particle or one, just under, exactly and just
+    over one round of slots, and a few rounds."""
+    test_gpu_kernel_edges.test_sort_moves_particles_whole((8, 8, 8), count, precision)
