@@ -118,10 +118,15 @@ constexpr int kCvNTb = 768, kCvUb = 2;  // pass 2
 // (1780 a tile) 225 -> 216, but 64^3 x 2 (1024) 124.3 -> 125.4.
 constexpr int kCvNTbFull = 1024, kCvFull = 1400;
 constexpr int64_t kCvFixed = 800;       // staging and flush, in particles (tile_split)
-// Current region: 16 cells per axis in rows of 17 and planes of 272 + 3 doubles,
-// so that the classes of a tile's cells (first index modulo 16) vary along
-// every axis.
-constexpr int kCvRowJ = 17, kCvPlaneJ = 16 * 17 + 3;
+// Field region: 13 cells per axis in rows of 14 and planes of 182 + 2 doubles,
+// modulo 16 those of the sort's lane classes; current region: 16 cells in rows of
+// 18 and planes of 288 + 8.  The rows give every z layer of a tile's cells each
+// class as often: a dense tile's chunk holds one or two layers, and where a class
+// runs out its rows are incomplete.  20 steps of 64^3 x 32, w_th = 0.02: 27.2 ms
+// with rows of 13 and 17 (24.4 in storage order), 21.1 like this; x 2: 2.46, 2.42.
+constexpr int kCvRowF = 14, kCvPlaneF = 13 * 14 + 2;
+constexpr int kCvRowJ = 18, kCvPlaneJ = 16 * 18 + 8;
+static_assert(even_layers(kCvRowF) && even_layers(kCvRowJ), "a layer holds every class as often");
 
 // Pass 1's word on a particle's move: bits 2 ax .. 2 ax + 1 the cell shift plus
 // one, bit 6 no shift on any axis, bit 7 the particle within the current
@@ -140,8 +145,10 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
                                                      const double* __restrict__ bfield, int split)
 {
     constexpr int T = kTile3, M = kCvM3a, NT = kCvNTa;
-    constexpr int LF = T + 3 + 2 * M, NF = LF * LF * LF;  // cells T0-1-M .. T0+T+1+M
+    constexpr int LF = T + 3 + 2 * M;  // cells T0-1-M .. T0+T+1+M
+    constexpr int ROW = kCvRowF, PLANE = kCvPlaneF, NF = LF * PLANE;
     constexpr int MB = kCvM3b;
+    static_assert(ROW >= LF && PLANE >= LF * ROW, "rows and planes hold the region");
     __shared__ double sf[6 * NF];
     __shared__ ClassRows<NT, kCvUa> rows;
     __shared__ unsigned int n_fallback;
@@ -155,7 +162,7 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
     if (begin >= end) return;
     {
         const bool small = nx < LF || ny < LF || nz < LF;
-        const Columns<LF, LF, LF> cols(g, T0[0] - 1 - M, T0[1] - 1 - M, small);
+        const Columns<LF, LF, ROW> cols(g, T0[0] - 1 - M, T0[1] - 1 - M, small);
         stage_planes<6 * LF, NT, kAllPlanes<6 * LF, NT>, double>(
             cols,
             [&](int t) {
@@ -163,7 +170,7 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
                 return (comp < 3 ? fields + comp * N : bfield + (comp - 3) * N) +
                        plane_offset(g, T0[2] - 1 - M + t - comp * LF, small);
             },
-            [&](int t) { return sf + t * (LF * LF); });
+            [&](int t) { return sf + t * PLANE; });
     }
     if (threadIdx.x == 0) n_fallback = 0;
     const double c2 = g.c * g.c;
@@ -188,9 +195,9 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
         place(i0, rel);
         double E[3], B[3];
         if (kTileFields) {
-            const int fb = (rel[0] + 1 + M) + (rel[1] + 1 + M) * LF + (rel[2] + 1 + M) * LF * LF;
+            const int fb = (rel[0] + 1 + M) + (rel[1] + 1 + M) * ROW + (rel[2] + 1 + M) * PLANE;
             auto F = [&](int comp, int oa, int ob, int oc) -> double {
-                return sf[comp * NF + fb + oa + ob * LF + oc * LF * LF];
+                return sf[comp * NF + fb + oa + ob * ROW + oc * PLANE];
             };
             gather3_conv<double>(ax0, F, E, B);
         } else {
@@ -233,7 +240,7 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
                 out[atomicAdd(&n_fallback, 1u)] = (uint32_t)(cb - begin + sl);
                 return -1;
             }
-            return (rel[0] + M + (rel[1] + M) * LF + (rel[2] + M) * LF * LF) & (kRowClasses - 1);
+            return (rel[0] + M + (rel[1] + M) * ROW + (rel[2] + M) * PLANE) & (kRowClasses - 1);
         });
         for (int q = threadIdx.x; q < nin; q += NT) advance(cb + rows.perm[q], std::true_type{});
     }

@@ -211,6 +211,7 @@ __global__ __launch_bounds__(kO2NTa) void k_push_o2_3d(GridK g, StepArgs a, Part
     constexpr int T = kTile3, M = kO2M3a, NT = kO2NTa;
     constexpr int LF = T + 4 + 2 * M, NF = LF * LF * LF;
     constexpr int MB = kO2M3b, LJ = T + 6 + 2 * MB;
+    static_assert(even_layers(LF) && even_layers(LJ), "a layer holds every class as often");
     __shared__ double sf[6 * NF];
     __shared__ ClassRows<NT, kO2Ua> rows;
     __shared__ unsigned int n_fallback;

@@ -134,6 +134,17 @@ __device__ __forceinline__ int field_plane3(int t, int& lz)
 // ---------------------------------------------------------------------------
 constexpr int kRowClasses = 16;
 
+// Whether every z layer of a 3D tile's cells, kept in rows of `row`, holds each
+// class as often.
+constexpr bool even_layers(int row)
+{
+    int n[kRowClasses] = {};
+    for (int c = 0; c < kTile3 * kTile3; ++c) ++n[(c % kTile3 + c / kTile3 * row) % kRowClasses];
+    for (int k = 0; k < kRowClasses; ++k)
+        if (n[k] != kTile3 * kTile3 / kRowClasses) return false;
+    return true;
+}
+
 template <int NT, int U, int C = kRowClasses>
 struct ClassRows {
     static constexpr int W = NT * U, NW = NT / 64;
