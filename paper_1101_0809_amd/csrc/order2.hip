@@ -13,6 +13,7 @@
 // plus M) in LDS, added to the grid once at the end; in 3D the two regions
 // are handled by two passes.  A particle further than M cells from its tile
 // reads and adds in global memory instead.
+#include <algorithm>
 #include <type_traits>
 
 #include "tile_io.h"
@@ -475,24 +476,29 @@ struct Rows3 {
     const double* x[3];
 };
 
-// The same for a cell-sorted species, one workgroup per tile: particles within M
-// cells of their tile accumulate into an LDS density tile (cells T0-2-M ..
+// The same for a cell-sorted species, `split` workgroups per tile: particles
+// within M cells of their tile accumulate into an LDS density tile (cells T0-2-M ..
 // T0+T+1+M), added to the grid once; the rest go straight to global memory.
 // 64 global atomics per particle took 944 us of an energy sample at 64^3 x 2;
-// the tile takes 40.
+// the tile takes 40.  On few tiles one workgroup each was the slower form (13 x 14
+// x 15 x 4, 8 tiles: an energy sample 94 us with global atomics, 138 with a
+// workgroup per tile, 69 with shares of kRhoShare particles).
+constexpr int kRhoShare = 64;
+
 template <int D, int T, int M, int NT>
 __global__ __launch_bounds__(NT) void k_rho_o2_tiled(GridK g, Rows3 pos, const double* __restrict__ weight,
-                                                     const int64_t* __restrict__ ts, double q,
+                                                     const int64_t* __restrict__ ts, int split, double q,
                                                      double* __restrict__ rho)
 {
     constexpr int L = T + 4 + 2 * M, LZ = D == 3 ? L : 1, NL = L * L * LZ;
     __shared__ double sr[NL];
-    const int tile = xcd_tile(blockIdx.x, g.ntiles);
+    const int unit = xcd_tile(blockIdx.x, g.ntiles * split), tile = unit / split;
     const int T0[3] = {(tile % g.nt[0]) * T, ((tile / g.nt[0]) % g.nt[1]) * T,
                        D == 3 ? (tile / (g.nt[0] * g.nt[1])) * T : 0};
     const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int64_t begin = ts[tile], end = ts[tile + 1];
-    if (begin == end) return;
+    int64_t begin = ts[tile], end = ts[tile + 1];
+    tile_share(unit - tile * split, split, begin, end);
+    if (begin >= end) return;
     for (int e = threadIdx.x; e < NL; e += NT) sr[e] = 0.0;
     __syncthreads();
     for (int64_t p = begin + threadIdx.x; p < end; p += NT) {
@@ -621,12 +627,16 @@ hipError_t launch_rho_o2(const Ctx& c, const double* const x[3], const double* w
 {
     if (n == 0) return hipSuccess;
     Rows3 pos{{x[0], x[1], x[2]}};
+    // shares of kRhoShare particles, up to two workgroups per CU in all
+    const int64_t avg = n / c.k.ntiles;
+    const int split = (int)std::max<int64_t>(1, std::min(2 * kCus / c.k.ntiles, (int)(avg / kRhoShare)));
+    const dim3 grid((unsigned)(c.k.ntiles * split));
     if (tile_start && c.k.dims == 3)
-        hipLaunchKernelGGL((k_rho_o2_tiled<3, kTile3, 2, 256>), dim3(c.k.ntiles), dim3(256), 0, s, c.k, pos, weight,
-                           tile_start, q, rho);
+        hipLaunchKernelGGL((k_rho_o2_tiled<3, kTile3, 2, 256>), grid, dim3(256), 0, s, c.k, pos, weight, tile_start,
+                           split, q, rho);
     else if (tile_start)
-        hipLaunchKernelGGL((k_rho_o2_tiled<2, kTile2, 2, 256>), dim3(c.k.ntiles), dim3(256), 0, s, c.k, pos, weight,
-                           tile_start, q, rho);
+        hipLaunchKernelGGL((k_rho_o2_tiled<2, kTile2, 2, 256>), grid, dim3(256), 0, s, c.k, pos, weight, tile_start,
+                           split, q, rho);
     else if (c.k.dims == 3)
         hipLaunchKernelGGL(k_rho_o2<3>, dim3(blocks256(n)), dim3(256), 0, s, c.k, pos, weight, n, q, rho);
     else

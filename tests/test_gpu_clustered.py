@@ -48,3 +48,29 @@ def test_reverse_step_of_clustered_particles(box, counts):
     for a, b in ((got[:3], ref[0]), (got[3:], ref[1]), (lx.cpu().numpy()[:dims], ref[2][:dims]),
                  (lw.cpu().numpy(), ref[3]), (lb.cpu().numpy(), ref[4])):
         assert np.max(np.abs(a - b)) <= 1e-12 * np.max(np.abs(b))
+
+
+@pytest.mark.parametrize("box,counts", [
+    ((13, 14, 15), (2000, 0)), ((8, 8, 8), (70, 0)), ((24, 20, 17), (300, 2500)), ((48, 40, 41), (4000, 3000)),
+    ((17, 16, 1), (150, 0)), ((32, 32, 1), (400, 3000)), ((100, 70, 1), (5000, 900))])
+def test_density_shares_at_order_2(box, counts):
+    """The order-2 1/2 charge density of a sorted species, by shares of a tile,
+    against that of the same species unsorted (every contribution its own global
+    add), cell by cell: the Gauss drift between two diagnostics with a sort in
+    between is their difference.  Two sums of n terms of one sign differ by 2 n
+    roundings at most."""
+    from paper_1101_0809_amd import Sim
+    dims = 2 if box[2] == 1 else 3
+    n = sum(counts)
+    x, w, weight = picgen.beams(box, n, 79, w_th=0.3, drift=0.2, dims=dims)
+    for a in range(dims):  # the rest into the first tile
+        x[a, counts[0]:] *= (16.0 if dims == 2 else 8.0) / box[a]
+    sim = Sim(*box, 0.4, dims=dims, order=2, sort_every=0)
+    sim.add_species(-1.0, 1.0, n)
+    sim.load(0, x, w, weight)
+    before = sim.diagnostics()
+    sim.sort()
+    after = sim.diagnostics()
+    bound = 2 * n * 2.0 ** -53
+    assert after["gauss_abs"] <= bound * after["rho_mobile_max"]
+    assert abs(after["charge"] - before["charge"]) <= bound * abs(before["charge"])
