@@ -951,7 +951,7 @@ void k_adj_tile2(GridK g, AdjArgs a, const int64_t* __restrict__ tile_start, Sha
         int rel[2];
         bool inside = true;
         for (int ax = 0; ax < 2; ++ax) {
-            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }
@@ -1065,7 +1065,7 @@ __device__ __forceinline__ bool tile_place3(const GridK& g, const AdjArgs& a, in
         const double fl = floor(x);
         i0[ax] = (int)fl;
         d0[ax] = x - fl;
-        const int r = tile_rel(i0[ax], T0[ax], g.n[ax], kAdjT3);
+        const int r = tile_rel(i0[ax], T0[ax], g.n[ax], kAdjT3, kAdjM3);
         rel[ax] = r;
         inside = inside && r >= -kAdjM3 && r <= kAdjT3 - 1 + kAdjM3;
     }

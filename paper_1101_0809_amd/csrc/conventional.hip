@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kCvNT2) void k_step_conv2(GridK g, StepArgs a, cons
         const double qp = a.q * ((const double*)a.weight)[p];
         AxisC<double> ax0[3];
         for (int ax = 0; ax < 3; ++ax) ax0[ax] = form_factor_conv<double>(d0[ax]);
-        const int rel[2] = {tile_rel(i0[0], T0[0], nx, T), tile_rel(i0[1], T0[1], ny, T)};
+        const int rel[2] = {tile_rel(i0[0], T0[0], nx, T, M), tile_rel(i0[1], T0[1], ny, T, M)};
         const bool inside = rel[0] >= -M && rel[0] <= T - 1 + M && rel[1] >= -M && rel[1] <= T - 1 + M;
         double E[3], B[3];
         if (inside) {
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
     auto place = [&](const int i0[3], int rel[3]) -> bool {  // true inside the field region
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         return inside;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(NT) void k_deposit_conv3(GridK g, StepArgs a, PartA
                 window<double>(s0[ax], s1[ax], delta, dm[ax], dp[ax]);
             }
             s[ax] = (delta < 0 ? -1 : 0) - 1;
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
         }
         const double qp = a.q * ((const double*)a.weight)[p];
         double jfac[3];

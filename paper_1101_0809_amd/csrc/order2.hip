@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kO2NT2) void k_step_o2(GridK g, StepArgs a, const d
         int rel[3] = {0, 0, 0};
         bool inside = true;
         for (int ax = 0; ax < D; ++ax) {
-            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kO2NTa) void k_push_o2_3d(GridK g, StepArgs a, Part
     auto place = [&](const int i0[3], int rel[3]) -> bool {
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         return inside;
@@ -340,7 +340,7 @@ __device__ __forceinline__ void o2_windows(const GridK& g, const StepArgs& a, co
         const int shift = delta + e1.h - e0.h;
         window5_reg(e0.s, e1.s, shift, dm[ax], dp[ax]);
         mv.s[ax] = e0.h + (shift < 0 ? shift : 0) - 2;
-        mv.rel[ax] = tile_rel(mv.i0[ax], T0[ax], g.n[ax], kTile3);
+        mv.rel[ax] = tile_rel(mv.i0[ax], T0[ax], g.n[ax], kTile3, kO2M3b);
     }
 }
 
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(NT) void k_rho_o2_tiled(GridK g, Rows3 pos, const d
                 const double f = floor(x);
                 i0[ax] = (int)f;
                 d = x - f;
-                rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+                rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
                 inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
             }
             w[ax] = form_factor2<double>(d);

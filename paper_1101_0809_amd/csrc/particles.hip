@@ -130,7 +130,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2
     auto place = [&](const int i0[3], int rel[2]) -> bool {
         bool inside = true;
         for (int ax = 0; ax < 2; ++ax) {
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         return inside;
@@ -477,7 +477,7 @@ __device__ __forceinline__ bool relative3(const GridK& g, const int T0[3], const
     bool in = true;
     for (int ax = 0; ax < 3; ++ax) {
         const int m = ax == 0 ? Tile3<R>::MX : Tile3<R>::M;
-        const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T);
+        const int r = tile_rel(i0[ax], T0[ax], g.n[ax], T, m);
         rel[ax] = r;
         in = in && (r >= -m) && (r <= T - 1 + m);
     }
@@ -1440,7 +1440,7 @@ __global__ __launch_bounds__(NT) void k_rho_tiled(GridK g, PartArrays src, const
         int rel[3] = {0, 0, 0};
         bool inside = true;
         for (int ax = 0; ax < D; ++ax) {
-            const int r = tile_rel(i[ax], T0[ax], g.n[ax], T);
+            const int r = tile_rel(i[ax], T0[ax], g.n[ax], T, M);
             rel[ax] = r;
             inside = inside && r >= -M && r <= T - 1 + M;
         }
