@@ -171,7 +171,7 @@ size_t workspace_bytes(const GridK& k, uint32_t nkeys)
     size_t b = 0;
     b += 3 * align_up((size_t)k.ncell * 8, kAlign);                     // rho_bg, r0, rho_m
     b += align_up(((size_t)nkeys + 1) * 4, kAlign);                      // hist
-    b += align_up(((size_t)nkeys / 1024 + 2) * 4, kAlign);               // scan partials
+    b += align_up(((size_t)nkeys / 1024 + 2) * 4, kAlign);               // unused: the layout of saved workspaces
     b += align_up(diag_partials_doubles(kMaxSpecies) * 8, kAlign);       // reductions
     b += align_up(8 * sizeof(unsigned long long), kAlign);               // counters
     b += align_up(3 * (size_t)k.ncell * 8, kAlign);                      // B^n for the particles
@@ -320,7 +320,7 @@ int pic_init_grid(const pic_grid_desc* g, void* fields, size_t field_bytes, void
     c.r0 = (double*)take((size_t)k.ncell * 8);
     c.rho_m = (double*)take((size_t)k.ncell * 8);
     c.hist = (uint32_t*)take(((size_t)nkeys + 1) * 4);
-    c.scan_part = (uint32_t*)take(((size_t)nkeys / 1024 + 2) * 4);
+    take(((size_t)nkeys / 1024 + 2) * 4);  // unused (see workspace_bytes)
     c.red = (double*)take(diag_partials_doubles(kMaxSpecies) * 8);
     c.counters = (unsigned long long*)take(8 * sizeof(unsigned long long));
     c.work = (unsigned int*)c.red;  // (4 KB of it) within a step; the reductions run between steps

@@ -139,7 +139,6 @@ struct Ctx {
     double* r0 = nullptr;       // Gauss reference R^0
     double* rho_m = nullptr;    // scratch: mobile charge density
     uint32_t* hist = nullptr;   // nkeys + 1 counts / offsets
-    uint32_t* scan_part = nullptr;
     double* red = nullptr;      // reduction partials
     double* bn = nullptr;       // B^n of the current step (3 planes), read by the particles
     double* adj = nullptr;      // adjoint scratch (3 planes): lambda_J of a reverse step
