@@ -837,16 +837,16 @@ __device__ __forceinline__ int wrapi(int v, int n)
 }
 
 // Cell i relative to a tile of edge T whose first cell is t0, on a periodic
-// axis of n cells: the image within M cells of the tile if there is one, else the
-// nearest.  (On an axis of up to 2 (T - 1 + M) cells the nearest image of a cell of
-// the tile's upper half, or of one above it, can lie below the tile, which sent
-// such particles to global memory: 100 us per step for 13 x 14 x 17 cells x 3 per
-// cell, 50 us like this.)
+// axis of n cells: the nearest image, but the tile's own cells and the M above them
+// as they are, and on an axis shorter than two tiles the image within M cells of
+// the tile if there is one.  (There the nearest image of a cell of the tile's upper
+// half, or of one above it, can lie below the tile, which sent such particles to
+// global memory: 100 us per step for 13 x 14 x 17 cells x 3 per cell, 50 us with
+// the tile's own cells as they are, 37 like this.)
 __device__ __forceinline__ int tile_rel(int i, int t0, int n, int T, int M)
 {
     const int r = i - t0, h = n / 2, top = T - 1 + M;
-    const int hi = h > top ? h : top;
-    const int far = -h > top + 1 - n ? -h : top + 1 - n, lo = far < -M ? far : -M;
+    const int hi = h > top ? h : top, lo = n < 2 * T && top + 1 - n > -h ? min(top + 1 - n, -M) : -h;
     return r > hi ? r - n : (r < lo ? r + n : r);
 }
 
