@@ -320,11 +320,13 @@ int pic_adjoint_reorder(pic_ctx* ctx, const void* from, const void* to, size_t b
  * side, and with neutralize = 1 it is also added, with the opposite sign, to
  * the background as a uniform charge (the uniform neutralizing background of
  * a start without co-located ions).  A species just loaded is put into
- * cell order first (its storage order, pic_sort), as its first step would.  Conjugate gradients on the GPU to a
- * relative residual tol (<= 0: 1e-13); *iterations and *residual (either may
- * be NULL) report the count and the reached relative residual.  The Gauss
- * reference R^0 is recaptured before the next step.  Synchronizes the
- * stream.  PIC_ESTATE if the tolerance was not reached. */
+ * cell order first (its storage order, pic_sort), as its first step would.
+ * Conjugate gradients on the GPU to a relative residual tol (<= 0: 1e-13);
+ * *iterations and *residual (either may be NULL) report the count, in whole
+ * checks of 16 iterations (the last check past convergence leaves the solution
+ * as it is), and the reached relative residual.  The Gauss reference R^0 is
+ * recaptured before the next step.  Synchronizes the stream.  PIC_ESTATE if the
+ * tolerance was not reached. */
 int pic_solve_poisson(pic_ctx* ctx, int neutralize, double tol, int64_t* iterations, double* residual,
                       void* stream);
 

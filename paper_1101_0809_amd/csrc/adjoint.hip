@@ -820,7 +820,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adj_particles(GridK g, AdjArgs 
 }
 
 // 2D tile kernel.  The particles are grouped by the tiles of the last sort
-// (tile_start); kAdjSplit blocks share a tile's particles.  Each block stages
+// (tile_start); several blocks share a tile's particles (Shares).  Each block stages
 // E, B^n (cells T0-1-M .. T0+T+M) and lambda_J (T0-2-M .. T0+T+1+M) of its
 // tile in LDS and accumulates lambda_E, lambda_B over the field region in LDS,
 // added to the grid once at the end; a particle more than M cells outside its

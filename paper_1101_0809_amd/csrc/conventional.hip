@@ -114,8 +114,8 @@ constexpr int kCvM3a = 1, kCvM3b = 2;
 constexpr int kCvNTa = 512, kCvUa = 4;  // pass 1: threads, slots per thread ordered at a time
 constexpr int kCvNTb = 768, kCvUb = 2;  // pass 2
 // From kCvFull particles in a workgroup's share on, pass 2 has four waves per
-// SIMD (128 VGPRs, no spills): 64^3 x 8 333 -> 320 us a step, 89 x 30 x 88 x 4
-// (1780 a tile) 225 -> 216, but 64^3 x 2 (1024) 124.3 -> 125.4.
+// SIMD (128 VGPRs, no spills): 64^3 x 8 315 -> 306 us a step, 89 x 30 x 88 x 4
+// (1780 a tile) 222 -> 213, but 64^3 x 2 (1024) 134.5 -> 135.3.
 constexpr int kCvNTbFull = 1024, kCvFull = 1400;
 constexpr int64_t kCvFixed = 800;       // staging and flush, in particles (tile_split)
 // Field region: 13 cells per axis in rows of 14 and planes of 182 + 2 doubles,
@@ -138,7 +138,7 @@ constexpr int kCvStill = 64, kCvInside = 128;
 // (order_rows) of their cell, pass 2 (54 or 144 LDS atomics) in those of their
 // window: LDS bank conflicts were 36 and 18% of the CU-busy cycles in storage
 // order.  82 and 58 -> 71 and 49 us at 64^3 x 2 per cell; 20 steps of 64^3 x 6
-// per cell with the energies 6.25 -> 5.5 ms, hot (w_th = 0.2) 13.3 -> 10.0 ms.
+// per cell with the energies 6.25 -> 5.25 ms, hot (w_th = 0.2) 13.3 -> 8.3 ms.
 // All fields of a tile in flight at once: 20 steps of 64^3 x 2 2830 -> 2655 us.
 __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, PartArrays spare,
                                                      const double* __restrict__ fields,

@@ -532,8 +532,8 @@ __global__ __launch_bounds__(NT) void k_rho_o2_tiled(GridK g, Rows3 pos, const d
                         atomicAdd(&sr[lb + a + L * (b + L * c)], v);
                     } else {
                         const int64_t kz = D == 3 ? (int64_t)wrapi(i0[2] + w[2].h - 2 + c, nz) * ny : 0;
-                        add_global(&rho[(kz + wrapi(i0[1] + w[1].h - 2 + b, ny)) * nx + wrapi(i0[0] + w[0].h - 2 + a, nx)],
-                                   v);
+                        const int64_t jy = (kz + wrapi(i0[1] + w[1].h - 2 + b, ny)) * nx;
+                        add_global(&rho[jy + wrapi(i0[0] + w[0].h - 2 + a, nx)], v);
                     }
                 }
         }

@@ -4,8 +4,9 @@
 // momentum advance (Eq. p2 and the three-stage split before it), position
 // advance (Eq. coordscheme) and the charge-conserving current of Eq. current.
 //
-// Kernel organisation (one workgroup per cell tile; particles are cell-sorted
-// so a tile's particles are contiguous):
+// Kernel organisation (a workgroup works on a cell tile, on a share of one
+// where tiles are few, or on tile after tile; particles are cell-sorted so a
+// tile's particles are contiguous):
 //   1. stage E^n and B^n of the tile plus guard cells into LDS (R precision);
 //   2. clear an LDS current tile covering the deposit reach plus guards;
 //   3. each thread advances particles of the tile; a particle whose cell lies
@@ -63,9 +64,9 @@ __device__ __forceinline__ void global_add(double* p, double v)
 // of the order's barriers (32^2 x 4 per cell: 19.1 us per step against 22.1).
 // ---------------------------------------------------------------------------
 template <class R, int T, int M, int NT, int U, bool ROWS>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2))) void k_particle_step2(GridK g, StepArgs a, const double* __restrict__ fields,
-                                                      const double* __restrict__ bfield, double* __restrict__ Jg,
-                                                      int split)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2)))
+void k_particle_step2(GridK g, StepArgs a, const double* __restrict__ fields, const double* __restrict__ bfield,
+                      double* __restrict__ Jg, int split)
 {
     constexpr int LF = T + 2 + 2 * M;  // field region: cells T0-1-M .. T0+T+M
     constexpr int LJ = T + 4 + 2 * M;  // current region: T0-2-M .. T0+T+1+M
@@ -196,7 +197,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2
             R jfac[3], dm[3][4], dp[3][4];
             for (int ax = 0; ax < 3; ++ax) jfac[ax] = (R)g.jscale[ax] * mv.qp;
             windows(mv.d0, mv.d1, mv.delta, dm, dp);
-            const int jb = (rel[0] + (mv.delta[0] < 0 ? -1 : 0) + 1 + M) + (rel[1] + (mv.delta[1] < 0 ? -1 : 0) + 1 + M) * ROW;
+            const int jb = (rel[0] + (mv.delta[0] < 0 ? -1 : 0) + 1 + M) +
+                           (rel[1] + (mv.delta[1] < 0 ? -1 : 0) + 1 + M) * ROW;
             deposit2<R>(dm, dp, jfac, mv.jz,
                         [&](int comp, int ix, int iy, int, double x) { sj.add(comp * NJ + jb + ix + iy * ROW, x); });
         }
@@ -273,8 +275,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2
                 }
                 windows(d0, d1, delta, dm, dp);
                 const int jb = s[0] + s[1] * ROW;
-                deposit2<R>(dm, dp, jfac, ((const R*)a.qd0[2])[e],
-                            [&](int comp, int ix, int iy, int, double x) { sj.add(comp * NJ + jb + ix + iy * ROW, x); });
+                deposit2<R>(dm, dp, jfac, ((const R*)a.qd0[2])[e], [&](int comp, int ix, int iy, int, double x) {
+                    sj.add(comp * NJ + jb + ix + iy * ROW, x);
+                });
             }
             __syncthreads();
         }
@@ -348,10 +351,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(ROWS ? 4 : 2
 //       any other particle has left the region: it joins the tile's migrant
 //       list with its rank among the migrants to its neighbour tile (one
 //       further away takes a bucket slot at once);
-//   (b) one ballot per rank r < 16 gives row r, the classes with more than r
-//       particles in the chunk, so a row holds distinct classes;
+//   (b) one ballot per rank r < RW (10 or 12) gives row r, the classes with
+//       more than r particles in the chunk, so a row holds distinct classes;
 //   (c) each particle's place is its row's start plus the number of smaller
-//       classes in the row (ranks from 16 on follow the rows), written into
+//       classes in the row (ranks from RW on follow the rows), written into
 //       the wave's permutation of the chunk;
 //   (d) lane t advances the particle at place t, t + 64, ...: gather (LDS),
 //       push, move (state stored), and, if it stays in its cell, its 54
@@ -1547,13 +1550,14 @@ constexpr int kThreads2 = 256;
 constexpr int kRows2 = 2;          // 2D: slots per thread ordered at a time
 constexpr int kMargin2 = 2;
 
-// Workgroups per tile of the 2D3V step: enough to fill the chip four times over
-// (as many fit a CU's LDS) with two particles per thread each, or once with a
-// particle per eight threads (with 128, 64 and 32 particles to a workgroup 32^2 x
-// 4 takes 18.2, 17.7 and 17.3 us per step, 16^2 x 1 13.7, 13.3 and 13.2).  us per
-// step at 1, 2, 3, 4, 8 workgroups per tile: 78, 61, 56, 57, 69 for 256^2 x 16 per
-// cell (4 taken); 35, 35, 38, 41, 51 for 256^2 x 4 (2 taken); 40, 30, 28, 27, 24
-// for 100 x 70 x 8 (7 taken); 164, 173, 177, 186, 223 for 512^2 x 16 (1 taken).
+// Workgroups per tile of the 2D3V step, of 256 threads (launch_step2 halves them
+// where it makes them wider): enough to fill the chip four times over (as many fit
+// a CU's LDS) with two particles per thread each, or once with a particle per
+// eight threads (with 128, 64 and 32 particles to a workgroup 32^2 x 4 takes 18.2,
+// 17.7 and 17.3 us per step, 16^2 x 1 13.7, 13.3 and 13.2).  us per step at 1, 2, 3,
+// 4, 8 workgroups per tile: 78, 61, 56, 57, 69 for 256^2 x 16 per cell (4 here, 2
+// wide ones launched); 35, 35, 38, 41, 51 for 256^2 x 4 (2, 1 wide); 40, 30, 28, 27,
+// 24 for 100 x 70 x 8 (7, as many wide); 164, 173, 177, 186, 223 for 512^2 x 16 (1).
 int split2(int64_t ntiles, int64_t n)
 {
     const int64_t avg = n / ntiles;
@@ -1588,8 +1592,8 @@ void launch_step2(const Ctx& c, const StepArgs& a, int64_t n, hipStream_t s)
         hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2Wide, kRows2, true>), grid,
                            dim3(kThreads2Wide), 0, s, c.k, a, c.fields, c.bn, J, split);
     else
-        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2, kRows2, true>), grid, dim3(kThreads2), 0, s,
-                           c.k, a, c.fields, c.bn, J, split);
+        hipLaunchKernelGGL((k_particle_step2<R, kTile2, kMargin2, kThreads2, kRows2, true>), grid, dim3(kThreads2), 0,
+                           s, c.k, a, c.fields, c.bn, J, split);
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
