@@ -114,16 +114,16 @@ constexpr int kCvM3a = 1, kCvM3b = 2;
 constexpr int kCvNTa = 512, kCvUa = 4;  // pass 1: threads, slots per thread ordered at a time
 constexpr int kCvNTb = 768, kCvUb = 2;  // pass 2
 // From kCvFull particles in a workgroup's share on, pass 2 has four waves per
-// SIMD (128 VGPRs, no spills): 64^3 x 8 315 -> 306 us a step, 89 x 30 x 88 x 4
-// (1780 a tile) 222 -> 213, but 64^3 x 2 (1024) 134.5 -> 135.3.
+// SIMD (128 VGPRs, no spills): 64^3 x 8 278 -> 268 us a step, 89 x 30 x 88 x 4
+// (1780 a tile) 199 -> 188, but 64^3 x 2 (1024) 118.2 -> 118.9.
 constexpr int kCvNTbFull = 1024, kCvFull = 1400;
 constexpr int64_t kCvFixed = 800;       // staging and flush, in particles (tile_split)
 // Field region: 13 cells per axis in rows of 14 and planes of 182 + 2 doubles,
 // modulo 16 those of the sort's lane classes; current region: 16 cells in rows of
 // 18 and planes of 288 + 8.  The rows give every z layer of a tile's cells each
 // class as often: a dense tile's chunk holds one or two layers, and where a class
-// runs out its rows are incomplete.  20 steps of 64^3 x 32, w_th = 0.02: 27.2 ms
-// with rows of 13 and 17 (24.4 in storage order), 21.1 like this; x 2: 2.46, 2.42.
+// runs out its rows are incomplete.  20 steps of 64^3 x 32, w_th = 0.02: 26.1 ms
+// with rows of 13 and 17 (24.4 in storage order), 19.3 like this; x 2: 2.31, 2.30.
 constexpr int kCvRowF = 14, kCvPlaneF = 13 * 14 + 2;
 constexpr int kCvRowJ = 18, kCvPlaneJ = 16 * 18 + 8;
 static_assert(even_layers(kCvRowF) && even_layers(kCvRowJ), "a layer holds every class as often");
@@ -137,8 +137,8 @@ constexpr int kCvStill = 64, kCvInside = 128;
 // Pass 1 (252 LDS reads per particle) takes the particles in class rows
 // (order_rows) of their cell, pass 2 (54 or 144 LDS atomics) in those of their
 // window: LDS bank conflicts were 36 and 18% of the CU-busy cycles in storage
-// order.  82 and 58 -> 71 and 49 us at 64^3 x 2 per cell; 20 steps of 64^3 x 6
-// per cell with the energies 6.25 -> 5.25 ms, hot (w_th = 0.2) 13.3 -> 8.3 ms.
+// order.  82 and 58 -> 56 and 50 us at 64^3 x 2 per cell; 20 steps of 64^3 x 6
+// per cell with the energies 6.25 -> 4.55 ms, hot (w_th = 0.2) 13.3 -> 7.5 ms.
 // All fields of a tile in flight at once: 20 steps of 64^3 x 2 2830 -> 2655 us.
 __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, PartArrays spare,
                                                      const double* __restrict__ fields,
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kCvNTa) void k_push_conv3(GridK g, StepArgs a, Part
     auto place = [&](const int i0[3], int rel[3]) -> bool {  // true inside the field region
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
+            rel[ax] = tile_rel_long(i0[ax], T0[ax], g.n[ax], T, M);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         return inside;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(NT) void k_deposit_conv3(GridK g, StepArgs a, PartA
                 window<double>(s0[ax], s1[ax], delta, dm[ax], dp[ax]);
             }
             s[ax] = (delta < 0 ? -1 : 0) - 1;
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
+            rel[ax] = tile_rel_long(i0[ax], T0[ax], g.n[ax], T, M);
         }
         const double qp = a.q * ((const double*)a.weight)[p];
         double jfac[3];

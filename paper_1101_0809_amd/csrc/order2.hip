@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kO2NTa) void k_push_o2_3d(GridK g, StepArgs a, Part
     auto place = [&](const int i0[3], int rel[3]) -> bool {
         bool inside = true;
         for (int ax = 0; ax < 3; ++ax) {
-            rel[ax] = tile_rel(i0[ax], T0[ax], g.n[ax], T, M);
+            rel[ax] = tile_rel_long(i0[ax], T0[ax], g.n[ax], T, M);
             inside = inside && rel[ax] >= -M && rel[ax] <= T - 1 + M;
         }
         return inside;
@@ -340,7 +340,7 @@ __device__ __forceinline__ void o2_windows(const GridK& g, const StepArgs& a, co
         const int shift = delta + e1.h - e0.h;
         window5_reg(e0.s, e1.s, shift, dm[ax], dp[ax]);
         mv.s[ax] = e0.h + (shift < 0 ? shift : 0) - 2;
-        mv.rel[ax] = tile_rel(mv.i0[ax], T0[ax], g.n[ax], kTile3, kO2M3b);
+        mv.rel[ax] = tile_rel_long(mv.i0[ax], T0[ax], g.n[ax], kTile3, kO2M3b);
     }
 }
 
